@@ -345,16 +345,10 @@ DSIM_API dsim_status dsim_simulate_tables(const dsim_tables *tables, int64_t n_c
  * through a permutation held in `workspace`: a device buffer of at least
  * dsim_parametric_workspace(n_cand) bytes (about 12 bytes per candidate,
  * DSIM_ENOSPC if shorter), owned by the caller, in use until hip_stream has
- * passed the call; no word of it needs clearing.  Transformer grids of
- * 8,192 or more candidates are simulated by two kernels, one for the
- * candidates of 1 to 8 stages (1 to 4 with the overlapped all-reduce, or with
- * ZeRO and no recomputation) and
- * one for the others; they run side by side
- * when side_stream is a second stream (hip_stream's earlier work is awaited
- * on it and the call's work on side_stream is awaited on hip_stream before
- * anything later, through two events the call creates and destroys), and
- * one after the other on hip_stream when side_stream is NULL or equal to
- * it; the results are the same.  n_cand < 2^31, and n_cand * W below
+ * passed the call; no word of it needs clearing (calls of at most 4,096
+ * candidates check it but do not use it).  Every kernel runs on hip_stream;
+ * side_stream is accepted and not used (one kernel simulates every
+ * candidate).  n_cand < 2^31, and n_cand * W below
  * 2^32 - 2^9 lanes, W = min(row_width, 64, n_layers) rounded up to a power
  * of two (DSIM_ERANGE otherwise: split the call).
  */

@@ -76,6 +76,14 @@ struct Ctx {
     uint64_t mult_dev, mult_tp, mult_dp;
 };
 
+// Quotient and remainder of a <= 1e15 (the size rule's bound on every model
+// dimension) by b in [1, 2^31): a / b is at least 1 / b away from the next
+// integer above it, more than half an ulp of a quotient of a 53-bit number,
+// so the rounded quotient's whole part is the exact one.  About a fifth of
+// the instructions of a 64-bit integer division.
+__device__ __forceinline__ uint64_t div_dim(uint64_t a, int b) { return (uint64_t)((double)a / (double)b); }
+__device__ __forceinline__ uint64_t mod_dim(uint64_t a, int b) { return a - div_dim(a, b) * (uint64_t)b; }
+
 // Preconditions of the transform (evenly divisible batch, heads and hidden
 // sizes; K <= rows per replica; P <= layers; with H > 1 every MLP stage holds
 // whole column/row layer pairs).
@@ -84,9 +92,9 @@ __device__ inline bool strategy_ok(const dsim_model &m, int D, int H, int P, int
     if (D < 1 || H < 1 || P < 1 || K < 1) return false;
     if ((int64_t)D * H * P > kMaxDevices) return false;
     const int64_t B = m.global_batch;
-    if (B % D != 0 || (int64_t)K > B / D || P > m.n_layers) return false;
+    if (mod_dim((uint64_t)B, D) != 0 || (int64_t)K > (int64_t)div_dim((uint64_t)B, D) || P > m.n_layers) return false;
     if (m.family == DSIM_MLP) {
-        if (m.d_model % H != 0) return false;
+        if (mod_dim((uint64_t)m.d_model, H) != 0) return false;
         if (H > 1) {
             const int q = m.n_layers / P, r = m.n_layers % P;
             if ((q & 1) != 0 && r < P) return false;          // stages with q layers
@@ -94,7 +102,7 @@ __device__ inline bool strategy_ok(const dsim_model &m, int D, int H, int P, int
         }
         return true;
     }
-    return m.n_heads % H == 0 && m.d_model % H == 0 && m.d_ff % H == 0;
+    return m.n_heads % H == 0 && mod_dim((uint64_t)m.d_model, H) == 0 && mod_dim((uint64_t)m.d_ff, H) == 0;
 }
 
 // M: the model (dsim_model, in any address space); c: the device constants
@@ -121,14 +129,14 @@ __device__ inline void make_ctx(const MM &M, const CC &c, const dsim_strategy &s
     x.seq = (uint64_t)M.seq_len;
     x.vocab = (uint64_t)M.vocab;
     x.heads = (uint64_t)M.n_heads;
-    x.rows = (uint64_t)M.global_batch / (uint64_t)x.D;
-    x.mq = x.rows / (uint64_t)x.K;
-    x.mr = x.rows % (uint64_t)x.K;
-    x.dH = x.d / (uint64_t)x.H;
-    x.FH = x.mlp ? 0 : x.dff / (uint64_t)x.H;
-    x.Vh = x.mlp ? 0 : (x.vocab + (uint64_t)x.H - 1) / (uint64_t)x.H;
-    x.aH = x.mlp ? 0 : x.heads / (uint64_t)x.H;
-    x.hd = x.mlp ? 0 : x.d / x.heads;
+    x.rows = div_dim((uint64_t)M.global_batch, x.D);
+    x.mq = div_dim(x.rows, x.K);
+    x.mr = mod_dim(x.rows, x.K);
+    x.dH = div_dim(x.d, x.H);
+    x.FH = x.mlp ? 0 : div_dim(x.dff, x.H);
+    x.Vh = x.mlp ? 0 : div_dim(x.vocab + (uint64_t)x.H - 1, x.H);
+    x.aH = x.mlp ? 0 : (uint64_t)(M.n_heads / x.H);
+    x.hd = x.mlp ? 0 : div_dim(x.d, M.n_heads);
     x.inv_f = c.inv_f;
     x.inv_b = c.inv_b;
     x.inv_l = c.inv_l;

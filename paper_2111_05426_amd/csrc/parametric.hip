@@ -28,19 +28,22 @@
 //     as the maximum over the replicas in closed form (see zero_block).
 //
 // The layers of a stage repeat one op sequence (for the MLP with H > 1, one
-// column/row layer pair), so each lane records that sequence's op costs once
-// per microbatch size and direction (LDS, [entry][lane]) together with its
-// memory summary (net bytes, peak above the starting live bytes, op counts),
-// and walks a block's layers as a chain of fp64 adds over the recorded costs.
-// Adding the same costs in the same order gives the same rounding as the op
-// by op walk, and the memory summary is exact integer arithmetic.  Ops outside
-// the repeating part (embedding, LM head, loss, the stage's first MLP layer in
-// backward, the last layer in inference) and backward blocks of microbatch 0
-// (which have no gradient accumulation) are walked op by op.
+// column/row layer pair) that does not depend on the stage, so the lanes of a
+// segment record a candidate's programs once, together: the op costs of that
+// unit and of the edges (embedding, LM head, loss, the MLP's first unit in
+// backward) for every kind of block -- forward, backward without and with
+// gradient accumulation, each for the two microbatch sizes -- and every
+// block's memory (net bytes, highest point).  A block is then one addition:
+// inside one binade of the clock, rounding to nearest adds each cost as a
+// whole number of ulps, so the block adds a tabulated whole number (built by
+// the wavefront when a candidate's clocks enter a binade).  A block that
+// leaves the binade, and one whose costs include an exact half ulp, is walked
+// cost by cost; adding the same costs in the same order gives the same
+// rounding either way, and the memory is exact integer arithmetic.
 //
 // A counting-sort pre-pass groups the candidates by segment width into a
 // temporary permutation (stable, so the grid's own order keeps wavefronts
-// uniform in K).
+// uniform in K); a small grid needs none, each candidate has a wavefront.
 #include <mutex>
 #include <type_traits>
 
@@ -119,10 +122,10 @@ struct ParArgs {
     int64_t n_cand;
     int32_t row_width;
     int32_t p_bound;
-    const uint32_t *perm;   // candidates grouped by segment class
-    const uint32_t *meta;   // [0,8) class totals, [8,16) first perm index, [16,24) first lane
-    int32_t narrow_end;     // classes the narrow launch takes: [0, narrow_end)
-    const uint32_t *order;  // the wide launch's wavefronts, longest first
+    const uint32_t *perm;   // candidates grouped by segment class; NULL: one candidate per wavefront, in order
+    const uint32_t *meta;   // [0,8) class totals, [8,16) first perm index, [16,24) first wavefront
+    const uint32_t *order;  // the wavefronts, longest first
+    uint32_t wave0;         // the launch's first entry of order
     double *makespan;
     double *finish;
     uint64_t *peak;
@@ -133,11 +136,18 @@ struct ParArgs {
     ParConsts c;
 };
 
+// A grid shares wavefronts between segments of at least 16 lanes: more than
+// four candidates in one wavefront make the rare events of each (a clock
+// crossing into the next binade, a change of the microbatch size, a phase
+// that cannot skip) so frequent that nearly every slot pays for one.
+constexpr int kMinClass = 4;
+constexpr int kMaxSeg = kLanes >> kMinClass;
+
 __device__ __forceinline__ int seg_class(const dsim_strategy &st, int p_bound)
 {
     const int P = st.P;
-    if (P < 1 || P > p_bound) return 0;
-    int j = 0;
+    if (P < 1 || P > p_bound) return kMinClass;
+    int j = kMinClass;
     while ((1 << j) < P) ++j;
     return j;
 }
@@ -145,158 +155,98 @@ __device__ __forceinline__ int seg_class(const dsim_strategy &st, int p_bound)
 // ---------------------------------------------------------------------------
 // Sinks
 // ---------------------------------------------------------------------------
-// The lane's stage replica, op by op (splits, the weight update and, under
-// overlap, the last backward block).  With ZeRO, live counts the largest
-// owned resident and z describes the stage's ownership: a reduce samples the
-// owner holding the reduced gradient and the other replicas, then every
-// gradient dies; the owner's optimizer op frees the reduced gradient again
-// (below that sample).  Under overlap tm is the communication stream's
-// clock: a hand-over or hand-back is a Send between the two streams (both
-// clocks meet at its end), the all-reduce advances tm alone (every replica's
-// communication stream is at the same time).
-struct Walk {
-    const Ctx &x;
-    double clk;
-    int64_t live, peak;
-    uint64_t walked, nops;
-    const ZStage *z;
-    double tm = 0.0;
-
-    __device__ __forceinline__ void meet(uint64_t by)
-    {
-        const double st = clk > tm ? clk : tm;
-        clk = st + cost_stream(x, by);
-        tm = clk;
-    }
-    __device__ __forceinline__ void handover(uint64_t by)
-    {
-        meet(by);
-        tm = tm + cost_ar_dp(x, by);
-        walked += 2;
-        nops += x.mult_dev + x.mult_dp;
-    }
-    __device__ __forceinline__ void handback(uint64_t by)
-    {
-        meet(by);
-        walked += 1;
-        nops += x.mult_dev;
-    }
-
-    __device__ __forceinline__ void op(double c, uint64_t al, uint64_t fr)
-    {
-        clk = clk + c;
-        live += (int64_t)al;
-        peak = live > peak ? live : peak;
-        live -= (int64_t)fr;
-        walked += 1;
-        nops += x.mult_dev;
-    }
-    __device__ __forceinline__ void local(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr)
-    {
-        op(cost_local(x, fl, by), al, fr);
-    }
-    __device__ __forceinline__ void mm(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr, uint64_t k)
-    {
-        op(cost_mm(x, fl, by, k), al, fr);
-    }
-    __device__ __forceinline__ void ar_tp(uint64_t by)
-    {
-        if (x.H <= 1) return;
-        clk = clk + cost_ar_tp(x, by);
-        walked += 1;
-        nops += x.mult_tp;
-    }
-    __device__ __forceinline__ void ar_dp(uint64_t by)
-    {
-        if (x.D <= 1) return;
-        clk = clk + cost_ar_dp(x, by);
-        walked += 1;
-        nops += x.mult_dp;
-    }
-    __device__ __forceinline__ void bcast(uint64_t by, int)
-    {
-        if (!x.zero) return;
-        clk = clk + cost_chain_d(x, by);
-        walked += 1;
-        nops += x.mult_dp;
-    }
-    __device__ __forceinline__ void reduce(uint64_t by, int grp)
-    {
-        clk = clk + cost_chain_d(x, by);
-        walked += 1;
-        nops += x.mult_dp;
-        const int o = grp % x.D;
-        const int64_t own = (int64_t)z_owned(x, *z, o) + (int64_t)by;
-        const int64_t other = (int64_t)(o == z->arg ? z->rsec : z->rmax);
-        const int64_t hi = live - (int64_t)z->rmax + (own > other ? own : other);
-        peak = hi > peak ? hi : peak;
-        live -= (int64_t)by;
-    }
-    __device__ __forceinline__ void owner_local(uint64_t fl, uint64_t by, uint64_t, uint64_t, int)
-    {
-        clk = clk + cost_local(x, fl, by);
-        walked += 1;
-        nops += x.mult_dp;
-    }
-};
-
-// Records ops' costs into a region of LDS and summarises their memory effect
-// relative to the live bytes at the region's start.
+// Records ops' costs into a region of LDS.
 struct Record {
     const Ctx &x;
-    double *base;      // entry j at base[(j / 2) * step + (j & 1)]
-    int step;          // doubles between consecutive entry pairs
+    double *base;
     int n;
-    int64_t cur, top;  // net bytes so far; max of (bytes after an op's allocation)
 
-    __device__ __forceinline__ void put(double c)
+    __device__ __forceinline__ void put(double c) { base[n++] = c; }
+    __device__ __forceinline__ void pad(int entries)
     {
-        base[(n >> 1) * step + (n & 1)] = c;
-        ++n;
+        while (n < entries) put(0.0);   // clock + 0.0 == clock
     }
-    __device__ __forceinline__ void pad(int entries2)
+    __device__ __forceinline__ void local(uint64_t fl, uint64_t by, uint64_t, uint64_t) { put(cost_local(x, fl, by)); }
+    __device__ __forceinline__ void mm(uint64_t fl, uint64_t by, uint64_t, uint64_t, uint64_t k)
     {
-        while (n < 2 * entries2) put(0.0);   // clock + 0.0 == clock
-    }
-    __device__ __forceinline__ void op(double c, uint64_t al, uint64_t fr)
-    {
-        put(c);
-        const int64_t a = cur + (int64_t)al;
-        top = a > top ? a : top;
-        cur = a - (int64_t)fr;
-    }
-    __device__ __forceinline__ void local(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr)
-    {
-        op(cost_local(x, fl, by), al, fr);
-    }
-    __device__ __forceinline__ void mm(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr, uint64_t k)
-    {
-        op(cost_mm(x, fl, by, k), al, fr);
+        put(cost_mm(x, fl, by, k));
     }
     __device__ __forceinline__ void ar_tp(uint64_t by)
     {
         if (x.H <= 1) return;
         put(cost_ar_tp(x, by));
     }
-    __device__ __forceinline__ void ar_dp(uint64_t by)
-    {
-        if (x.D <= 1) return;
-        put(cost_ar_dp(x, by));
-    }
-    // a broadcast's cost; with ZeRO the memory summary comes from MemZ
     __device__ __forceinline__ void bcast(uint64_t by, int)
     {
         if (!x.zero) return;
         put(cost_chain_d(x, by));
     }
-    __device__ __forceinline__ void reduce(uint64_t by, int) { put(cost_chain_d(x, by)); }
-    __device__ __forceinline__ void owner_local(uint64_t fl, uint64_t by, uint64_t, uint64_t, int)
-    {
-        put(cost_local(x, fl, by));
-    }
-    // recorded programs hold no last block of an overlapped stage
+    // hand-overs are marked beside the program (Marks)
     __device__ __forceinline__ void handover(uint64_t) {}
-    __device__ __forceinline__ void handback(uint64_t) {}
+};
+
+// A hand-over in a recorded program: before entry `pos`, both streams meet
+// and take `send`, then the communication stream's all-reduce takes `ar`.
+struct Mark {
+    int pos;
+    double send, ar;
+};
+// Where the edges' programs of the last backward block hand gradients over.
+struct Marks {
+    const Ctx &x;
+    Mark *at;
+    int n;   // entries so far
+
+    __device__ __forceinline__ void local(uint64_t, uint64_t, uint64_t, uint64_t) { ++n; }
+    __device__ __forceinline__ void mm(uint64_t, uint64_t, uint64_t, uint64_t, uint64_t) { ++n; }
+    __device__ __forceinline__ void ar_tp(uint64_t)
+    {
+        if (x.H > 1) ++n;
+    }
+    __device__ __forceinline__ void bcast(uint64_t, int) {}   // no ZeRO under overlap
+    __device__ __forceinline__ void handover(uint64_t by)
+    {
+        at->pos = n;
+        at->send = cost_stream(x, by);
+        at->ar = cost_ar_dp(x, by);
+    }
+};
+
+// The repeating unit of an overlapped last backward block, padded with zero
+// costs so that its hand-overs come before fixed entries whether or not it
+// accumulates or all-reduces (the transformer's four weight gradients; the
+// MLP layer's, or the row and the column layer's).
+template <bool TF> struct OvUnit {
+    static constexpr int kMarks = TF ? 4 : 2, kEntries = TF ? 22 : 9;
+    static constexpr int pos(int i) { return TF ? (i == 0 ? 3 : (i == 1 ? 8 : (i == 2 ? 13 : 20))) : (i == 0 ? 3 : 7); }
+    double cost[kEntries];
+    double send[kMarks], ar[kMarks];   // send < 0: no such hand-over
+};
+template <bool TF> struct RecordOv {
+    const Ctx &x;
+    OvUnit<TF> &u;
+    int n, k;   // entries and hand-overs so far
+
+    __device__ __forceinline__ void put(double c) { u.cost[n++] = c; }
+    __device__ __forceinline__ void local(uint64_t fl, uint64_t by, uint64_t, uint64_t) { put(cost_local(x, fl, by)); }
+    __device__ __forceinline__ void mm(uint64_t fl, uint64_t by, uint64_t, uint64_t, uint64_t r)
+    {
+        put(cost_mm(x, fl, by, r));
+    }
+    __device__ __forceinline__ void ar_tp(uint64_t by) { put(x.H > 1 ? cost_ar_tp(x, by) : 0.0); }
+    __device__ __forceinline__ void bcast(uint64_t, int) {}   // no ZeRO under overlap
+    __device__ __forceinline__ void handover(uint64_t by)
+    {
+        while (n < OvUnit<TF>::pos(k)) put(0.0);
+        u.send[k] = cost_stream(x, by);
+        u.ar[k] = cost_ar_dp(x, by);
+        ++k;
+    }
+    __device__ __forceinline__ void pad()
+    {
+        while (n < OvUnit<TF>::kEntries) put(0.0);
+        for (; k < OvUnit<TF>::kMarks; ++k) u.send[k] = -1.0;
+    }
 };
 
 // Memory summary only (net bytes, peak above the start), no costs.
@@ -314,12 +264,8 @@ struct Mem {
         local(fl, by, al, fr);
     }
     __device__ __forceinline__ void ar_tp(uint64_t) {}
-    __device__ __forceinline__ void ar_dp(uint64_t) {}
     __device__ __forceinline__ void bcast(uint64_t, int) {}
-    __device__ __forceinline__ void reduce(uint64_t, int) {}
-    __device__ __forceinline__ void owner_local(uint64_t, uint64_t, uint64_t, uint64_t, int) {}
     __device__ __forceinline__ void handover(uint64_t) {}   // allocates nothing
-    __device__ __forceinline__ void handback(uint64_t) {}
 };
 
 // ZeRO memory summary of ops that read the weights of one parameter group:
@@ -343,7 +289,6 @@ struct MemZ {
         local(fl, by, al, fr);
     }
     __device__ __forceinline__ void ar_tp(uint64_t) {}
-    __device__ __forceinline__ void ar_dp(uint64_t) {}
     __device__ __forceinline__ void bcast(uint64_t by, int)
     {
         if (!x.zero) return;
@@ -351,10 +296,7 @@ struct MemZ {
         to = cur > to ? cur : to;
         pend = (int64_t)by;
     }
-    __device__ __forceinline__ void reduce(uint64_t, int) {}
-    __device__ __forceinline__ void owner_local(uint64_t, uint64_t, uint64_t, uint64_t, int) {}
     __device__ __forceinline__ void handover(uint64_t) {}   // allocates nothing
-    __device__ __forceinline__ void handback(uint64_t) {}
 };
 
 // Liveness of a forward unit.  kFwdBlock: as in a forward block (training
@@ -368,22 +310,22 @@ enum FwdLive { kFwdBlock = 0, kFwdFirst = 1, kFwdReplay = 2 };
 // layer; one MLP layer (H = 1) or column/row pair (H > 1), in walk order.
 // acc: with gradient accumulation (every backward microbatch but the first).
 template <bool TF, class S>
-__device__ void record_unit(const Ctx &x, bool bwd, uint64_t m, bool acc, S &r, int live = kFwdBlock)
+__device__ void record_unit(const Ctx &x, bool bwd, uint64_t m, bool acc, S &r, int live = kFwdBlock, bool last = false)
 {
     if (TF) {
         const TfSz z = tf_sizes(x, m);
         if (bwd) {
-            tf_layer_bwd(x, r, z, acc, 0);
+            tf_layer_bwd(x, r, z, acc, 0, last);
         } else {
             const bool save = live == kFwdReplay || (live == kFwdBlock && x.train && !x.rc);
             tf_layer_fwd(x, r, z, save, save || live == kFwdFirst, true, 0);
         }
     } else if (bwd) {
         if (x.H > 1) {
-            mlp_layer_bwd(x, r, m, kRow, false, false, acc, 0);
-            mlp_layer_bwd(x, r, m, kCol, false, false, acc, 0);
+            mlp_layer_bwd(x, r, m, kRow, false, false, acc, 0, last);
+            mlp_layer_bwd(x, r, m, kCol, false, false, acc, 0, last);
         } else {
-            mlp_layer_bwd(x, r, m, kPlain, false, false, acc, 0);
+            mlp_layer_bwd(x, r, m, kPlain, false, false, acc, 0, last);
         }
     } else {
         // free_in of the unit's first layer and of its second (pair) layer
@@ -472,13 +414,13 @@ __device__ __forceinline__ void compose_first(int64_t pd, int64_t pt, int64_t fd
 // Units walked per block: every layer (transformer); every layer or layer
 // pair (MLP) except the last unit in inference (last stage) and the
 // stage's first unit in backward, which the block records separately.
-__device__ __forceinline__ int block_units(const dsim_model &M, int P, int H, int s, bool bwd, bool TF)
+__device__ __forceinline__ int block_units(const Ctx &x, int s, bool bwd, bool TF)
 {
-    const int L = M.n_layers, nl = L / P + (s < L % P ? 1 : 0);
+    const int nl = stage_nl(x, s);
     if (TF) return nl;
-    const int per = H > 1 ? 2 : 1;
+    const int per = x.H > 1 ? 2 : 1;
     if (bwd) return nl / per - 1;
-    return nl / per - ((M.mode == DSIM_INFER && s == P - 1) ? 1 : 0);
+    return nl / per - ((!x.train && s == x.P - 1) ? 1 : 0);
 }
 
 // Counts ops (walked and program ops) without simulating them.
@@ -500,12 +442,6 @@ struct Count {
         walked += 1;
         nops += x.mult_tp;
     }
-    __device__ __forceinline__ void ar_dp(uint64_t)
-    {
-        if (x.D <= 1) return;
-        walked += 1;
-        nops += x.mult_dp;
-    }
     // ZeRO collectives: one per tensor rank
     __device__ __forceinline__ void bcast(uint64_t, int)
     {
@@ -513,53 +449,70 @@ struct Count {
         walked += 1;
         nops += x.mult_dp;
     }
-    __device__ __forceinline__ void reduce(uint64_t, int)
+    __device__ __forceinline__ void handover(uint64_t) {}
+    __device__ __forceinline__ void add(uint64_t n, const Count &c)
     {
-        walked += 1;
-        nops += x.mult_dp;
-    }
-    __device__ __forceinline__ void owner_local(uint64_t, uint64_t, uint64_t, uint64_t, int)
-    {
-        walked += 1;
-        nops += x.mult_dp;
-    }
-    // overlap: a hand-over per replica and an all-reduce per tensor rank; a hand-back per replica
-    __device__ __forceinline__ void handover(uint64_t)
-    {
-        walked += 2;
-        nops += x.mult_dev + x.mult_dp;
-    }
-    __device__ __forceinline__ void handback(uint64_t)
-    {
-        walked += 1;
-        nops += x.mult_dev;
+        walked += n * c.walked;
+        nops += n * c.nops;
     }
 };
 
-// ops of stage s's blocks and sends: K forward blocks; in training one
-// backward block without and K - 1 with gradient accumulation, the last of
-// which hands the gradients over under overlap.  Op counts do not depend on
-// the microbatch size.
-__device__ __forceinline__ void count_blocks(const Ctx &x, int s, uint64_t &walked, uint64_t &nops)
+// Ops of stage s of one replica: splits, K forward blocks, in training K
+// backward blocks (all but the first with gradient accumulation; the last
+// one hands the gradients over under overlap), the Sends after them and the
+// weight update.  Op counts do not depend on the microbatch size, and a
+// block's layers all count alike.
+template <bool TF>
+__device__ __forceinline__ void count_stage(const Ctx &x, int s, uint64_t &walked, uint64_t &nops)
 {
-    Count f{x, 0, 0}, b0{x, 0, 0}, b1{x, 0, 0}, bl{x, 0, 0};
-    block_fwd(x, f, s, 0);
-    const uint64_t K = (uint64_t)x.K;
-    const uint64_t fs = s < x.P - 1 ? 1 : 0;   // Send after each forward block
-    walked += K * (f.walked + fs);
-    nops += K * (f.nops + fs * x.mult_dev);
-    if (!x.train) return;
-    const uint64_t bs = s > 0 ? 1 : 0;         // Send after each backward block
-    walked += K * bs;
-    nops += K * bs * x.mult_dev;
-    block_bwd(x, b0, s, 0);                    // microbatch 0 (the last one if K = 1)
-    walked += b0.walked;
-    nops += b0.nops;
-    if (K == 1) return;
-    block_bwd(x, b1, s, 1);                    // microbatches 1 .. K-2 (K >= 3)
-    block_bwd(x, bl, s, x.K - 1);              // microbatch K-1
-    walked += (K - 2) * b1.walked + bl.walked;
-    nops += (K - 2) * b1.nops + bl.nops;
+    const bool first = s == 0, last = s == x.P - 1;
+    const int nl = stage_nl(x, s), per = (!TF && x.H > 1) ? 2 : 1;
+    const uint64_t K = (uint64_t)x.K, units = (uint64_t)(nl / per);
+    const TfSz z = {};
+    Count uf{x, 0, 0}, all{x, 0, 0};
+    record_unit<TF>(x, false, 1, false, uf);
+    Count op{x, 1, x.mult_dev};   // a compute op or a Send
+    if (x.K > 1) all.add((first ? 1 : 0) + (x.train && last ? 1 : 0), op);
+    Count f{x, 0, 0};
+    if (TF && first) tf_fwd_first(x, f, z);
+    if (TF && last) tf_fwd_last(x, f, z);
+    f.add(units, uf);
+    if (!last) f.add(1, op);
+    all.add(K, f);
+    if (x.train) {
+        const uint64_t params = TF ? 4 * (uint64_t)nl + (first ? 1 : 0) + (last ? 1 : 0) : (uint64_t)nl;
+        for (int acc = 0; acc < 2; ++acc) {
+            Count b{x, 0, 0}, u{x, 0, 0};
+            if (last) {
+                if (TF) tf_bwd_last(x, b, z, acc != 0);
+                else mlp_loss(x, b, 1);
+            }
+            if (x.rc) {
+                b.add(units - 1, uf);
+                record_partial<TF>(x, 1, b);
+            }
+            record_unit<TF>(x, true, 1, acc != 0, u);
+            b.add(units, u);
+            if (TF && first) tf_bwd_first(x, b, z, acc != 0);
+            if (!TF && first && x.H > 1) {   // layer 0's input gradient is not all-reduced
+                b.walked -= 1;
+                b.nops -= x.mult_tp;
+            }
+            if (!first) b.add(1, op);
+            all.add(acc ? K - 1 : 1, b);
+        }
+        const Count dp{x, 1, x.mult_dp};   // a collective over the replicas, or an owner's op
+        if (x.ov) {
+            all.add(2 * params, op);       // hand-over and hand-back
+            all.add(params, dp);
+            all.add(params, op);
+        } else {
+            if (x.D > 1) all.add(params, dp);
+            all.add(params, x.zero ? dp : op);
+        }
+    }
+    walked = all.walked;
+    nops = all.nops;
 }
 
 // ---------------------------------------------------------------------------
@@ -786,46 +739,6 @@ __device__ __forceinline__ double units_exact(const double2 (&r)[U2n], double cl
     return clk;
 }
 
-// the clock part of a block: pre, n units, suf (entry counts per region;
-// PST / UST: double2 stride of the edge / unit entries)
-template <int P2, int U2n, int S2, int PST, int UST>
-__device__ __forceinline__ double walk3(const double2 *pre, const double2 *unit, const double2 *suf, double clk, int n,
-                                        bool fast)
-{
-#pragma unroll
-    for (int j = 0; j < P2; ++j) {
-        const double2 v = pre[j * PST];
-        clk = clk + v.x;
-        clk = clk + v.y;
-    }
-    double2 r[U2n];
-#pragma unroll
-    for (int j = 0; j < U2n; ++j) r[j] = unit[j * UST];
-    if (fast) {
-        clk = units_exact(r, clk, n);
-    } else {
-        for (int u = 0; u < n; ++u) clk = units_seq(r, clk);
-    }
-#pragma unroll
-    for (int j = 0; j < S2; ++j) {
-        const double2 v = suf[j * PST];
-        clk = clk + v.x;
-        clk = clk + v.y;
-    }
-    return clk;
-}
-
-// the first n entries of a unit program (the replay's partial unit)
-template <int UST>
-__device__ __forceinline__ double walk_prefix(const double2 *unit, int n, double clk)
-{
-    for (int j = 0; j < n; ++j) {
-        const double2 v = unit[(j >> 1) * UST];
-        clk = clk + ((j & 1) ? v.y : v.x);
-    }
-    return clk;
-}
-
 // ---------------------------------------------------------------------------
 // Cross-lane helpers
 // ---------------------------------------------------------------------------
@@ -849,7 +762,7 @@ __device__ __forceinline__ uint64_t shl1(uint64_t v)
     return ((uint64_t)(uint32_t)shl1((int)(v >> 32)) << 32) | (uint32_t)shl1((int)(uint32_t)v);
 }
 
-__device__ __forceinline__ uint64_t ballot(bool b) { return __ballot(b); }
+__device__ __forceinline__ uint64_t ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 
 // DPP moves within the wavefront: row_shr:n (0x110 + n, lane i of a row of
 // 16 receives lane i - n of the same row), row_bcast:15 (0x142, lane 15 of
@@ -865,46 +778,6 @@ template <int CTRL, int ROWS> __device__ __forceinline__ double dpp(double v)
     return __hiloint2double(dpp<CTRL, ROWS>(__double2hiint(v)), dpp<CTRL, ROWS>(__double2loint(v)));
 }
 
-// Inclusive scan by op over the segments of the wavefront: each lane
-// combines the values of its segment from the segment's first lane (spos = 0
-// there) up to itself.  Rows of 16 lanes scan first, treating a row's first
-// lane as a segment start (shift-and-combine over 2^nlev > the largest spos
-// positions); then lanes whose segment began in an earlier row take the
-// carries, lane 15 of rows 0 and 2 into rows 1 and 3, then lane 31 into rows
-// 2 and 3 (cross: some segment spans a row boundary; nlev and cross are
-// uniform).  op is exact and associative on the values met, so the result is
-// the plain left-to-right one.
-template <class T, class Op>
-__device__ __forceinline__ T seg_scan(T v, int spos, int lane, int nlev, bool cross, Op op)
-{
-    const int rl = lane & 15;
-    const int sr = spos < rl ? spos : rl;
-    T up;
-    if (nlev > 0) {
-        up = dpp<0x111, 0xf>(v);
-        v = sr >= 1 ? op(v, up) : v;
-    }
-    if (nlev > 1) {
-        up = dpp<0x112, 0xf>(v);
-        v = sr >= 2 ? op(v, up) : v;
-    }
-    if (nlev > 2) {
-        up = dpp<0x114, 0xf>(v);
-        v = sr >= 4 ? op(v, up) : v;
-    }
-    if (nlev > 3) {
-        up = dpp<0x118, 0xf>(v);
-        v = sr >= 8 ? op(v, up) : v;
-    }
-    if (cross) {
-        up = dpp<0x142, 0xa>(v);
-        v = ((lane & 16) != 0 && spos > rl) ? op(v, up) : v;
-        up = dpp<0x143, 0xc>(v);
-        v = (lane >= 32 && spos >= lane - 31) ? op(v, up) : v;
-    }
-    return v;
-}
-
 // max of two clocks, which are never NaN or -0.0: the bare instruction
 // (fmax would canonicalize both operands first, two more dependent steps)
 __device__ __forceinline__ double max_nn(double a, double b)
@@ -912,6 +785,40 @@ __device__ __forceinline__ double max_nn(double a, double b)
     double r;
     asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
+}
+
+// Inclusive maximum over the segments of the wavefront (values never NaN):
+// each lane over its segment from the segment's first lane (spos = 0 there)
+// up to itself.  Rows of 16 lanes scan first, treating a row's first lane as
+// a segment start; then lanes whose segment began in an earlier row take the
+// carries, lane 15 of rows 0 and 2 into rows 1 and 3, then lane 31 into rows
+// 2 and 3 (cross, uniform: some segment spans a row boundary).
+__device__ __forceinline__ double seg_max(double v, int spos, int lane, bool cross)
+{
+    const int rl = lane & 15;
+    const int sr = spos < rl ? spos : rl;
+    double up = max_nn(v, dpp<0x111, 0xf>(v));
+    v = sr >= 1 ? up : v;
+    up = max_nn(v, dpp<0x112, 0xf>(v));
+    v = sr >= 2 ? up : v;
+    up = max_nn(v, dpp<0x114, 0xf>(v));
+    v = sr >= 4 ? up : v;
+    up = max_nn(v, dpp<0x118, 0xf>(v));
+    v = sr >= 8 ? up : v;
+    if (cross) {
+        up = max_nn(v, dpp<0x142, 0xa>(v));
+        v = ((lane & 16) != 0 && spos > rl) ? up : v;
+        up = max_nn(v, dpp<0x143, 0xc>(v));
+        v = (lane >= 32 && spos >= lane - 31) ? up : v;
+    }
+    return v;
+}
+
+// max of two byte counts in [0, 2^62) as one fp64 max of their bit patterns
+// (non-negative doubles below 2^62's pattern order like the integers)
+__device__ __forceinline__ int64_t max_bytes(int64_t a, int64_t b)
+{
+    return __double_as_longlong(max_nn(__longlong_as_double(a), __longlong_as_double(b)));
 }
 
 // The Sends of one slot as prefix scans, exact.
@@ -924,57 +831,69 @@ __device__ __forceinline__ double max_nn(double a, double b)
 // z_r being the larger of the Send's own two stage clocks before the slot's
 // Sends (a stage without a Send that received one from its left carries
 // v_{r-1} on; any other position starts the recurrence afresh).  While every
-// v stays in the binade [2^E, 2^(E+1)) of the first one, rounding to nearest
-// adds each w_r as the whole number W_r of ulps 2^(E-52) nearest to it,
-// whatever v is, unless w_r lies exactly half way between two (then ties to
-// even depend on v).  In integer ulps K_r = z_r / ulp, with Q_r = W_0 + ... +
-// W_r, the recurrence is then v_r = Q_r + max_{i <= r} (K_i - Q_{i-1}): an
-// inclusive sum scan and an inclusive max scan, in exact integer-valued fp64
-// (below 2^53), over the positions of each segment.  A position that starts
-// afresh starts a segment.  Returns false, changing nothing, if some lane
-// leaves those conditions (a first value that is 0, not finite or below
-// 2^-1022; a cost that is not finite or a half-way case; a result past the
-// binade); the caller then walks the Sends step by step.  nlev: scan levels,
-// 2^nlev > the largest position.
-__device__ __forceinline__ bool send_scan(double &clk, int sdir, double scost, bool from_left, bool from_right,
-                                          int lane, int nlev)
+// v stays in one binade [2^E, 2^(E+1)), rounding to nearest adds each w_r as
+// the whole number W_r of ulps 2^(E-52) nearest to it, whatever v is, unless
+// w_r lies exactly half way between two (then ties to even depend on v).  In
+// integer ulps K_r = z_r / ulp, with Q_r = W_0 + ... + W_r, the recurrence is
+// then v_r = Q_r + max_{i <= r} (K_i - Q_{i-1}) over a segment (a position
+// that starts afresh starts one): a sum scan -- over the whole wavefront,
+// what earlier segments add to Q cancels -- and a max scan within each
+// segment, in exact integer-valued fp64 (below 2^53).  E is the binade of
+// the first value at the candidate's first involved stage.
+// Returns false, changing nothing, if some lane leaves those conditions (a
+// start in another binade, 0, not finite or below 2^-500; a cost that is
+// not finite or a half-way case; a result past the binade); the caller then
+// walks the Sends step by step.  src: lanes with a Send (sdir its direction,
+// scost its cost), left / right: lanes that receive from their left / right.
+__device__ __forceinline__ bool send_scan(double &clk, bool bwd, double scost, uint64_t src, uint64_t left,
+                                          uint64_t right, int lane, int W, uint64_t segmask)
 {
+    auto in = [](uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); };
+    const bool sends = in(src);
     const double cl = shr1(clk), cr = shl1(clk);
-    const double z = sdir > 0 ? max_nn(clk, cr) : (sdir < 0 ? max_nn(clk, cl) : clk);
-    const bool carry = sdir < 0 || from_left;
-    const bool involved = sdir != 0 || from_left || from_right;
-    const uint64_t starts = ballot(!carry);
-    const uint64_t upto = starts & (lane == 63 ? ~0ull : ((2ull << lane) - 1));
+    double z = max_nn(clk, bwd ? cl : cr);
+    z = sends ? z : clk;
+    const uint64_t back = ballot(sends && bwd);
+    const uint64_t carry = back | left;
+    const uint64_t involved = src | left | right;
+    const uint64_t upto = ~carry & (lane == 63 ? ~0ull : ((2ull << lane) - 1));
     const int spos = lane - (63 - __builtin_clzll(upto));
-    bool bad = false;
-    int e = INT_MIN;   // the binade of the segment's first value, at its first lane
-    if (!carry) {
-        e = 0;
-        if (involved) {
-            bad = !(z > 0.0 && z <= 0x1.fffffffffffffp+1023);
-            if (!bad) e = ilogb(z);
-            bad = bad || e < -1022;
-        }
+    // the first involved segment start (a run starts at one)
+    const uint64_t begins = involved & ~carry;
+    if (begins == 0) return false;
+    const int hi = __double2hiint(z);
+    int e;
+    if (W == 64) {
+        e = __builtin_amdgcn_readlane(hi, __builtin_ctzll(begins));
+    } else {
+        const uint64_t mine = begins & segmask;
+        e = __shfl(hi, mine != 0 ? __builtin_ctzll(mine) : lane, kLanes);
     }
-    const bool cross = ballot(spos > (lane & 15)) != 0;
-    e = seg_scan(e, spos, lane, nlev, cross, [](int a, int b) { return a > b ? a : b; });
-    const int sh = 52 - e;
+    e = (int)((uint32_t)e >> 20);
+    const int sh = 1075 - e;
+    // a start in another binade, or a cost whose whole ulps are unknown
+    bool bad = in(begins) && ((int)((uint32_t)hi >> 20) != e || e < 1023 - 500 || e >= 0x7ff);
+    const double t = ldexp(scost, sh);
+    double w = rint(t);
+    bad = bad || (sends && !(fabs(t - w) < 0.5));   // (false also for t not finite)
+    w = sends ? w : 0.0;
     const double K = ldexp(z, sh);
-    double w = 0.0;
-    if (sdir != 0) {
-        const double t = ldexp(scost, sh);
-        w = rint(t);
-        bad = bad || !(scost >= 0.0 && scost <= 0x1.fffffffffffffp+1023) || fabs(t - w) == 0.5;
-    }
-    const double q = seg_scan(w, spos, lane, nlev, cross, [](double a, double b) { return a + b; });
-    const double y = seg_scan(K - (q - w), spos, lane, nlev, cross, [](double a, double b) { return a > b ? a : b; });
+    double q = w;   // (below 2^53 or the result below leaves the binade)
+    q += dpp<0x111, 0xf>(q);
+    q += dpp<0x112, 0xf>(q);
+    q += dpp<0x114, 0xf>(q);
+    q += dpp<0x118, 0xf>(q);
+    q += dpp<0x142, 0xa>(q);
+    q += dpp<0x143, 0xc>(q);
+    bad = bad || !(q < 0x1p53);
+    const bool cross = ballot(spos > (lane & 15)) != 0;
+    const double y = seg_max(K - (q - w), spos, lane, cross);
     const double v = q + y;
-    bad = bad || (involved && !(v < 0x1p53));
+    bad = bad || (in(involved) && !(v < 0x1p53));
     if (ballot(bad) != 0) return false;
     const double vd = ldexp(v, -sh);
     const double vr = shl1(vd);
-    if (from_right) clk = vr;
-    else if (sdir != 0 || from_left) clk = vd;
+    clk = in(right) ? vr : (in(src | left) ? vd : clk);
     return true;
 }
 
@@ -990,185 +909,293 @@ __device__ __forceinline__ T seg_reduce(T v, int W, Op op)
 // before it) and of all periods counted have the same directions, the same
 // microbatch size class (the first mr are one row longer) and the same
 // accumulation; the last backward block is left out under overlap (it hands
-// the gradients over).  pos: the stage's next block; pair: its last two
-// blocks were a forward and a backward one (1F1B), else both were bwd.
-__device__ __forceinline__ int repeats(bool pair, bool bwd, int pos, int P, int s, int K, int mr, int back, bool ov)
+// the gradients over).  nf, nb: the blocks run so far; pair: the last two
+// were a forward and a backward one (1F1B), else both were bwd.
+__device__ __forceinline__ int repeats(bool pair, bool bwd, int nf, int nb, int K, int mr, int back, bool ov)
 {
-    if (pair) {
-        const int wu = (P - 1 - s) < K ? (P - 1 - s) : K;
-        const int j = pos - 2 - 2 * back - wu;       // first block looked at
-        if (j < 2) return 0;                         // in the warm-up, or microbatch 0's backward
-        const int f0 = wu + ((j + 1) >> 1), b0 = j >> 1;
-        const int f = f0 + 1 + back, b = b0 + 1 + back;   // the next period's microbatches
-        int n = (2 * K - wu - pos) >> 1;
-        if (f0 < mr) n = n < mr - f ? n : mr - f;
-        if (b0 < mr) n = n < mr - b ? n : mr - b;
-        if (ov) n = n < K - 1 - b ? n : K - 1 - b;
-        return n;
+    const int step = pair ? 1 : 2;
+    int n = INT_MAX;
+    if (pair || !bwd) {
+        const int k0 = nf - step * (1 + back);
+        n = K - nf;
+        if (k0 < mr && mr - nf < n) n = mr - nf;
     }
-    const int k = bwd ? pos - K : pos;               // next microbatch
-    const int k0 = k - 2 - 2 * back;
-    if (k0 < (bwd ? 1 : 0)) return 0;
-    int end = bwd && ov ? K - 1 : K;
-    if (k0 < mr && mr < end) end = mr;
-    return (end - k) >> 1;
+    if (pair || bwd) {
+        const int k0 = nb - step * (1 + back);
+        if (k0 < 1) return 0;   // microbatch 0 does not accumulate
+        const int e = (ov ? K - 1 : K) - nb;
+        if (e < n) n = e;
+        if (k0 < mr && mr - nb < n) n = mr - nb;
+    }
+    return n / step;
 }
 
 // ---------------------------------------------------------------------------
 // The simulation kernel
 // ---------------------------------------------------------------------------
-// a wavefront whose blocks repeat a unit at least this many times sums the
-// repeats binade-wise (units_exact), else unit by unit: below it the walk's
-// dependent adds cost less than the binade arithmetic
+// a stage with at least this many layers sums its weight update binade-wise
+// (units_exact), else layer by layer: below it the dependent adds cost less
+// than the binade arithmetic
 constexpr int kFastUnits = 12;
-constexpr int kScanMinRun = 12;   // the last run position from which the Sends take send_scan
-constexpr int kKeys = 6;          // forward: 2 row classes; backward: 2 row classes x accumulation
-constexpr int kMaxSegShared = 16; // segments of >= 4 lanes per wavefront
+constexpr int kKeys = 6;    // forward: 2 row classes; backward: 2 row classes x accumulation
+constexpr int kRoles = 4;   // stage 0; a middle stage of q + 1 or of q layers; the last stage (P > 1)
+// binade tables are built for clocks of at least this biased exponent (below,
+// a cost over the ulp could overflow) and below that of infinity
+constexpr int kMinExp = 1023 - 500, kInfExp = 0x7ff;
+// whole ulps of a block that has to be walked: added to a finite clock they
+// leave its binade
+constexpr int64_t kWalk = (int64_t)1 << 61;
 
-// Per-lane programs (segments of 1 or 2 lanes): each lane records its own
-// block program per direction, again whenever the microbatch size class or
-// the accumulation changes, with the block's composed memory summary.
-template <class Sh> struct LdsLane {
-    double2 prog[2][Sh::PRE2 + Sh::U2 + Sh::SUF2][kLanes];
-    int64_t sum[2][2][kLanes];   // [backward][delta, top][lane]
-};
-// Shared programs (segments of >= 4 lanes): the repeating unit does not
-// depend on the stage, so each segment records the unit of every key once,
-// cooperatively; the stage edges stay per lane (transformer: stages 0 and
-// P-1 only).
-template <class Sh> struct LdsSeg {
-    double2 unit[kMaxSegShared][kKeys][Sh::U2];
-    int64_t usum[kMaxSegShared][kKeys][2];
-    int64_t xsum[kMaxSegShared][2][6];   // recomputation, per forward key: first unit, replay unit, partial
-    double2 edge[2][Sh::PRE2 + Sh::SUF2][kLanes];
-    int64_t esum[2][4][kLanes];  // [backward][pre delta, pre top, suf delta, suf top][lane]
-};
+// rounds of eight lanes over n entries
+template <int N> using Rounds = std::integral_constant<int, (N + 7) / 8>;
 
-template <class Sh> union LdsNarrow {
-    LdsLane<Sh> a;
-    LdsSeg<Sh> b;
-};
-
-// Wide segments (>= 16 lanes, transformer): at most 4 segments per
-// wavefront, and only stages 0 and P-1 have edge ops, so the edge programs
-// are kept per segment; middle stages walk a zero program.  About 7 KB.
-// Their stages hold few layers, so the kernel adds units one by one: without
-// the binade arithmetic's registers four wavefronts share a SIMD.  With the
-// overlapped gradient all-reduce the wide kernel keeps that arithmetic (its
-// registers are taken anyway) and also takes segments of 8 lanes (8 per
-// wavefront, about 14 KB).
-// (ZeRO without recomputation moves its 8-lane segments to the wide launch
-// too: its narrow kernel holds 48 KB of LDS, three wavefronts per CU)
-template <bool OV, bool ZR> constexpr int first_wide_class() { return (OV || ZR) ? 3 : 4; }
-inline int first_wide_class(bool ov, bool zr) { return (ov || zr) ? 3 : 4; }
-constexpr int64_t kSplitMinCand = 8192;
-template <class Sh, int NS> struct LdsWide {
-    double2 unit[NS][kKeys][Sh::U2];
-    int64_t usum[NS][kKeys][2];
-    int64_t xsum[NS][2][6];
-    double2 edge[NS][2][2][Sh::PRE2 + Sh::SUF2];   // [segment][stage 0, P-1][backward]
-    int64_t esum[NS][2][2][4];
-    double2 zero[Sh::PRE2 + Sh::SUF2];
-    int64_t zsum[4];
-};
-
-// Records a lane-owned block program of one direction (pre, unit, suf
-// regions from pp, lane stride kLanes) and its composed memory summary: n
-// units; under recomputation the forward block's first unit keeps its input
-// and the backward block replays n_r forward units and the partial unit
-// after its pre ops.
-template <bool TF, class Sh>
-__device__ void record_lane(const Ctx &x, int s, bool bwd, uint64_t m, bool acc, int n, int n_r, double2 *pp,
-                            int64_t &delta, int64_t &top)
+// clk plus the NB (backward) or NF (forward) entry pairs at a, in order
+template <int NF, int NB> __device__ __forceinline__ double walk(const double *a, bool bwd, double clk)
 {
-    double *base = reinterpret_cast<double *>(pp);
-    Record rp{x, base, 2 * kLanes, 0, 0, 0};
-    Record ru{x, base + Sh::PRE2 * 2 * kLanes, 2 * kLanes, 0, 0, 0};
-    Record rs{x, base + (Sh::PRE2 + Sh::U2) * 2 * kLanes, 2 * kLanes, 0, 0, 0};
-    record_edges<TF>(x, s, bwd, m, acc, rp, rs);
-    record_unit<TF>(x, bwd, m, acc, ru);
-    rp.pad(Sh::PRE2);
-    ru.pad(Sh::U2);
-    rs.pad(Sh::SUF2);
-    int64_t d = 0, t = 0;
-    if (!x.rc || (!bwd && n < 1)) {
-        compose(rp.cur, rp.top, ru.cur, ru.top, n, rs.cur, rs.top, d, t);
+    const double2 *v = reinterpret_cast<const double2 *>(a);
+    double2 r[NF < NB ? NB : NF];
+#pragma unroll
+    for (int j = 0; j < (NF < NB ? NB : NF); ++j) {
+        const bool has = j < (bwd ? NB : NF);
+        r[j] = v[has ? j : 0];
+        if (!has) r[j] = make_double2(0.0, 0.0);   // clock + 0.0 == clock
+    }
+#pragma unroll
+    for (int j = 0; j < (NF < NB ? NB : NF); ++j) {
+        clk = clk + r[j].x;
+        clk = clk + r[j].y;
+    }
+    return clk;
+}
+
+// One candidate's programs, recorded once by all lanes of its segment.  A
+// block of a stage is pre, its repeating units, suf; every stage has the same
+// unit, stage 0 and the last stage have edges: the transformer's embedding,
+// head and loss; the MLP's loss (pre) and, on stage 0, the first unit's
+// backward (suf), whose input gradient is not all-reduced (every other MLP
+// stage's first unit costs what its others do).
+template <bool TF, bool ZR, bool OV> struct Prog {
+    using Sh = Shape<TF, ZR>;
+    double2 uf[2][Sh::F_U2], ub[4][Sh::U2];
+    double2 pf[2][Sh::F_PRE2 > 0 ? Sh::F_PRE2 : 1], pb[4][Sh::PRE2];
+    double2 sf[2][Sh::F_SUF2], sb[4][Sh::SUF2];
+    double2 wu[5];                        // weight update: a layer's parameters, [4] the embedding / head
+    int64_t mem[kKeys][kRoles][2];        // a block's net bytes, highest point above its start
+    int64_t blk[2][kKeys][kRoles];        // a block's whole ulps in the binade held for each exponent parity, or kWalk
+    double2 unit_ulps[2][kKeys];          // one unit's, and their reciprocal; negative: walk it
+    int nu[2][kRoles], nrep[kRoles];      // units walked [backward], replayed
+    int npart, single;                    // entries of the replay's partial unit; P == 1
+    typename std::conditional<OV, OvUnit<TF>, int>::type ov;   // the last backward block's unit
+    Mark mark[OV ? 2 : 1];                // and its hand-overs in pre and suf (transformer)
+
+    __device__ __forceinline__ const double *unit(int key) const { return key < 2 ? &uf[key][0].x : &ub[key - 2][0].x; }
+    __device__ __forceinline__ const double *pre(int key) const { return key < 2 ? &pf[key][0].x : &pb[key - 2][0].x; }
+    __device__ __forceinline__ const double *suf(int key) const { return key < 2 ? &sf[key][0].x : &sb[key - 2][0].x; }
+    // entries of each
+    static __device__ __forceinline__ int n_unit(bool bwd) { return bwd ? 2 * Sh::U2 : 2 * Sh::F_U2; }
+    static __device__ __forceinline__ int n_pre(bool bwd) { return bwd ? 2 * Sh::PRE2 : 2 * Sh::F_PRE2; }
+    static __device__ __forceinline__ int n_suf(bool bwd) { return bwd ? 2 * Sh::SUF2 : 2 * Sh::F_SUF2; }
+    // whether a stage of these places has them
+    static __device__ __forceinline__ bool has_pre(bool bwd, bool first, bool last) { return bwd ? last : (TF && first); }
+    static __device__ __forceinline__ bool has_suf(bool bwd, bool first, bool last) { return bwd ? first : (TF && last); }
+};
+
+// a stage of the given role (-1: the strategy has none)
+__device__ __forceinline__ int role_stage(const Ctx &x, int role)
+{
+    if (role == 0) return 0;
+    if (role == 3) return x.P > 1 ? x.P - 1 : -1;
+    if (x.P < 3) return -1;
+    if (role == 1) return x.r > 1 ? 1 : -1;
+    return x.P - 2 >= x.r ? x.P - 2 : -1;
+}
+
+// The memory of stage s's block of one kind: net bytes and highest point
+// above its start; under recomputation the forward block's first unit keeps
+// its input and the backward block replays units and the partial unit after
+// its pre ops.
+template <bool TF, bool RC>
+__device__ void block_mem(const Ctx &x, int s, bool bwd, uint64_t m, bool acc, int64_t &d, int64_t &t)
+{
+    Mem p{x, 0, 0}, f{x, 0, 0}, u{x, 0, 0};
+    record_edges<TF>(x, s, bwd, m, acc, p, f);
+    record_unit<TF>(x, bwd, m, acc, u);
+    const int n = block_units(x, s, bwd, TF);
+    if (!RC || (!bwd && n < 1)) {
+        compose(p.cur, p.top, u.cur, u.top, n, f.cur, f.top, d, t);
     } else if (!bwd) {
-        Mem f{x, 0, 0};
-        record_unit<TF>(x, false, m, false, f, kFwdFirst);
-        compose_first(rp.cur, rp.top, f.cur, f.top, ru.cur, ru.top, n, rs.cur, rs.top, d, t);
+        Mem q{x, 0, 0};
+        record_unit<TF>(x, false, m, false, q, kFwdFirst);
+        compose_first(p.cur, p.top, q.cur, q.top, u.cur, u.top, n, f.cur, f.top, d, t);
     } else {
-        Mem u{x, 0, 0}, q{x, 0, 0};
-        record_unit<TF>(x, false, m, false, u, kFwdReplay);
+        Mem v{x, 0, 0}, q{x, 0, 0};
+        record_unit<TF>(x, false, m, false, v, kFwdReplay);
         record_partial<TF>(x, m, q);
-        compose(rp.cur, rp.top, u.cur, u.top, n_r, q.cur, q.top, d, t);
+        const int nl = stage_nl(x, s);
+        compose(p.cur, p.top, v.cur, v.top, TF ? nl - 1 : nl / (x.H > 1 ? 2 : 1) - 1, q.cur, q.top, d, t);
         int64_t d2, t2;
-        compose(0, 0, ru.cur, ru.top, n, rs.cur, rs.top, d2, t2);
+        compose(0, 0, u.cur, u.top, n, f.cur, f.top, d2, t2);
         chain(d, t, d2, t2);
     }
-    delta = d;
-    top = t;
 }
 
-// WIDE: the launch for wide segments of a transformer; otherwise every class
-// of an MLP, or the narrow classes of a transformer.  RC: training with
-// activation recomputation; ZR: training with ZeRO; OV: training with the
-// gradient all-reduce on the communication streams (separate instantiations
-// keep the replay, the broadcasts and the two-stream walk out of the other
-// kernels).
-// The kernel's argument block (its only argument, at offset 0 of the
-// kernarg segment), addressed through a pointer the compiler cannot see
-// through.  The recording paths inside the slot loop and the weight update
-// after it read the model and the device constants through it: those values
-// are then loaded again with scalar loads where they are needed instead of
-// being kept live across the loop, where they would not fit the scalar
-// registers and would be spilled to vector-register lanes and read back in
-// every slot.
-template <class T> __device__ __forceinline__ const __attribute__((address_space(4))) T *kernel_args()
+// Records one of a candidate's programs: jobs 0-5 a unit, 6-11 a kind's
+// edges, 12 the weight update's parameters, 13 an overlapped last backward
+// block.
+constexpr int kJobs = 14;
+template <bool TF, bool ZR, bool OV>
+__device__ __forceinline__ void record_job(const Ctx &x, Prog<TF, ZR, OV> &q, int job)
 {
-    auto p = (const __attribute__((address_space(4))) T *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return p;
+    using Pr = Prog<TF, ZR, OV>;
+    const int key = job < kKeys ? job : job - kKeys;
+    const bool bwd = key >= 2, acc = key >= 4;
+    const uint64_t m = x.mq + (uint64_t)(key & 1);
+    if (job < kKeys) {
+        Record r{x, const_cast<double *>(q.unit(key)), 0};
+        record_unit<TF>(x, bwd, m, acc, r);
+        r.pad(Pr::n_unit(bwd));
+    } else if (job < 2 * kKeys) {
+        Record p{x, const_cast<double *>(q.pre(key)), 0}, f{x, const_cast<double *>(q.suf(key)), 0};
+        if (TF) {
+            const TfSz z = tf_sizes(x, m);
+            if (bwd) {
+                tf_bwd_last(x, p, z, acc);
+                tf_bwd_first(x, f, z, acc);
+            } else {
+                tf_fwd_first(x, p, z);
+                tf_fwd_last(x, f, z);
+            }
+        } else if (bwd) {
+            mlp_loss(x, p, m);
+            for (int i = x.H > 1 ? 1 : 0; i >= 0; --i) mlp_layer_bwd(x, f, m, mlp_kind(x, i), false, i == 0, acc, 0);
+        }
+        p.pad(Pr::n_pre(bwd));
+        f.pad(Pr::n_suf(bwd));
+    } else if (job == 12) {
+        // (collective or hand-back, optimizer) of each parameter
+        auto param = [&](uint64_t N) {
+            uint64_t fl, by;
+            opt_cost(x, N, fl, by);
+            const double coll = x.zero ? cost_chain_d(x, x.e * N)
+                                       : (x.ov ? cost_stream(x, x.e * N) : (x.D > 1 ? cost_ar_dp(x, x.e * N) : 0.0));
+            return make_double2(coll, cost_local(x, fl, by));
+        };
+        if (TF) {
+            q.wu[0] = param(x.d * 3 * x.dH);
+            q.wu[1] = param(x.dH * x.d);
+            q.wu[2] = param(x.d * x.FH);
+            q.wu[3] = param(x.FH * x.d);
+            q.wu[4] = param(x.Vh * x.d);
+        } else {
+            q.wu[0] = param(x.d * x.dH);
+        }
+    } else if constexpr (OV) {
+        const bool a = x.K > 1;
+        RecordOv<TF> u{x, q.ov, 0, 0};
+        record_unit<TF>(x, true, x.mq, a, u, kFwdBlock, true);
+        u.pad();
+        if (TF) {
+            Marks p{x, &q.mark[0], 0}, f{x, &q.mark[1], 0};
+            const TfSz z = tf_sizes(x, x.mq);
+            tf_bwd_last(x, p, z, a, true);
+            tf_bwd_first(x, f, z, a, true);
+        }
+    }
 }
 
-template <bool TF, bool WIDE, bool RC, bool ZR, bool OV>
+// ZeRO's weight update: the highest point above the live bytes at its start.
+// At each parameter's reduce the owner holds the reduced gradient beside
+// every replica's own, then every gradient dies; the owner's optimizer op
+// frees the reduced one again.  The live bytes only fall, so of the groups
+// of one owner the stage's first is enough.
+template <bool TF>
+__device__ __forceinline__ int64_t update_top(const Ctx &x, int s, const ZStage &z)
+{
+    int64_t live = 0, top = 0;
+    uint64_t own = 0, other = 0;
+    auto owner = [&](int grp) {
+        const int o = grp % x.D;
+        own = z_owned(x, z, o);
+        other = o == z.arg ? z.rsec : z.rmax;
+    };
+    auto reduce = [&](uint64_t N) {
+        const int64_t by = (int64_t)(x.e * N);
+        const int64_t mine = (int64_t)own + by, rest = (int64_t)other;
+        const int64_t hi = live - (int64_t)z.rmax + (mine > rest ? mine : rest);
+        top = hi > top ? hi : top;
+        live -= by;
+    };
+    const int l0 = stage_l0(x, s), nl = stage_nl(x, s);
+    if (!TF) {
+        const int per = x.H > 1 ? 2 : 1;
+        for (int i = 0; i < nl && i / per < x.D; ++i) {
+            owner(mlp_group(x, l0 + i));
+            reduce(x.d * x.dH);
+        }
+        return top;
+    }
+    if (s == 0) {
+        owner(0);
+        reduce(x.Vh * x.d);
+    }
+    const int64_t before = live;
+    for (int i = 0; i < nl && i < x.D; ++i) {
+        owner(tf_group_layer(l0 + i));
+        reduce(x.d * 3 * x.dH);
+        reduce(x.dH * x.d);
+        reduce(x.d * x.FH);
+        reduce(x.FH * x.d);
+    }
+    if (s == x.P - 1) {
+        live = before - (int64_t)(x.e * (uint64_t)nl * (4 * x.d * x.dH + 2 * x.d * x.FH));
+        owner(tf_group_head(x));
+        reduce(x.Vh * x.d);
+    }
+    return top;
+}
+
+// RC: training with activation recomputation; ZR: training with ZeRO; OV:
+// training with the gradient all-reduce on the communication streams
+// (separate instantiations keep the replay, the broadcasts and the two-stream
+// walk out of the other kernels).
+//
+// The kernel's time is the slots' instructions and their latency (a slot is
+// a serial chain, and a wavefront's slots follow one another), so a slot
+// does as little as it can: which blocks and Sends run is held in wave-wide
+// masks, the blocks' memory and, in the clocks' binade, the whole ulps a
+// block adds are tabulated per candidate, and whole periods are skipped.
+// Against two launches (1-8 and 16-64 lanes) that walked every block's costs
+// and re-recorded a program whenever a lane's block kind changed: 39,965
+// GPT-3-shaped strategies 2.03 -> 1.09 ms, with ZeRO 3.10 -> 1.83, two-stream
+// 3.59 -> 1.42, 2,240 MLP ones 350 -> 152 us, 398 GPT-2-small-shaped training
+// ones 195 -> 110 us; vector instructions per GPT-3-shaped call 929M (before
+// either change) -> 527M, which keep the SIMDs' issue about 85% busy.
+template <bool TF, bool RC, bool ZR, bool OV>
 __device__ __forceinline__ void parametric_body(const ParArgs &g)
 {
-    using Sh = Shape<TF, ZR>;
-    constexpr int PST = WIDE ? 1 : kLanes;   // double2 stride of a lane's edge program
-    // at most 64 / 2^(first wide class) segments per wide wavefront
-    __shared__ typename std::conditional<WIDE, LdsWide<Sh, (kLanes >> first_wide_class<OV, ZR && !RC>())>, LdsNarrow<Sh>>::type L;
+    using Pr = Prog<TF, ZR, OV>;
+    __shared__ Pr L[kMaxSeg];
+    // ZeRO: the highest point of every block kind over the stage's replicas
+    __shared__ int64_t s_ztop[ZR ? kKeys : 1][kLanes];
 
     const int lane = threadIdx.x;
-    // the binade-wise unit sums: not in the wide kernels (but in the one
-    // with the overlapped all-reduce, whose registers it does not raise)
-    constexpr bool kBinadeSums = !WIDE || OV;
-    // Wavefronts start longest first, so that short ones fill the tail: the
-    // wide launch in the pre-pass's order (by the estimated length of each
-    // wavefront), the only launch widest class first, each class from its
-    // last wavefront (the strategy grid lists microbatch counts ascending).
-    // The narrow launch beside a wide one runs in lane order.  The grid is
-    // sized for the worst case; wavefronts beyond the launch's own exit.
-    uint32_t blk = 0xffffffffu;
-    if constexpr (WIDE) {
-        const uint32_t n_wide = (g.meta[16 + kClasses] - g.meta[16 + first_wide_class<OV, ZR && !RC>()]) / (uint32_t)kLanes;
-        if (blockIdx.x < n_wide) blk = g.order[blockIdx.x];
-    } else {
-        const uint32_t nw = g.meta[16 + kClasses] / (uint32_t)kLanes;   // wavefronts holding classes
-        if (blockIdx.x < nw) blk = g.narrow_end == kClasses ? nw - 1 - blockIdx.x : blockIdx.x;
+    int cls = kClasses - 1;
+    int64_t c = (int64_t)blockIdx.x;
+    if (g.perm) {
+        // wavefronts start longest first (the pre-pass's order), so that
+        // short ones fill the tail; the grid is sized for the worst case
+        const uint32_t b = g.wave0 + blockIdx.x;
+        if (b >= g.meta[16 + kClasses]) return;
+        const uint32_t w = g.order[b];
+        cls = kMinClass;
+        while (cls + 1 < kClasses && w >= g.meta[16 + cls + 1]) ++cls;
+        const uint32_t slot = ((w - g.meta[16 + cls]) << (6 - cls)) + (uint32_t)(lane >> cls);
+        c = slot < g.meta[cls] ? (int64_t)g.perm[g.meta[8 + cls] + slot] : -1;
     }
-    if (blk == 0xffffffffu) return;
-    const uint32_t gl = blk * (uint32_t)kLanes;
-    int cls = 0;
-    while (cls + 1 < kClasses && gl >= g.meta[16 + cls + 1]) ++cls;
-    if (WIDE ? cls < first_wide_class<OV, ZR && !RC>() : cls >= g.narrow_end) return;   // the other launch's classes
     const int W = 1 << cls;
-    const bool shared = WIDE || W >= 4;
-    const uint32_t local = gl + lane - g.meta[16 + cls];
-    const uint32_t slot = local >> cls;
-    const int s = (int)(local & (uint32_t)(W - 1));   // stage of this lane
     const int seg = lane >> cls;
-    const int64_t c = slot < g.meta[cls] ? (int64_t)g.perm[g.meta[8 + cls] + slot] : -1;
+    const int s = lane & (W - 1);   // stage of this lane
+    const uint64_t segmask = W == 64 ? ~0ull : (((1ull << W) - 1) << (lane & ~(W - 1)));
 
     const dsim_model &M = g.m;
     dsim_strategy st = {1, 1, 1, 1};
@@ -1180,130 +1207,243 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
     }
     const int P = ok ? st.P : 0, K = st.K;
     const bool train = M.mode != DSIM_INFER;
-    bool live_stage = s < P;
+    const bool live_stage = s < P;
     int32_t status = (c >= 0 && !ok) ? DSIM_ST_BAD_STRATEGY : 0;
+    const bool first = s == 0, last = s == P - 1;
+    const bool ov_c = OV && M.overlap != 0 && st.D > 1;
+    const bool zero_c = ZR && M.zero != 0 && st.D > 1;
+    const bool f1b = train && M.schedule != DSIM_SCHED_GPIPE;
 
     double clk = 0.0;
     double clkm = 0.0;   // overlap: the communication stream's clock
-    const bool ov_c = OV && train && M.overlap != 0 && st.D > 1;
-    int64_t live = 0, peak = 0;
+    int64_t live = 0, peak = 0, wu_top = 0;
     uint64_t walked = 0, nops = 0;
-    uint64_t mq = 0, rb_f = 0, rb_b = 0;   // rows of a short microbatch; Send bytes per row
-    int pos = 0, nf = 0, nb = 0, len = 0, mr = 0, n_f = 0, n_b = 0;
-    constexpr bool rc = RC;   // the launch checks it against the model
-    int n_r = 0, n_part = 0;                     // replayed units, entries of the partial unit
-    // ZeRO: the highest point of every block kind over the stage's replicas
-    const bool zero_c = ZR && train && M.zero != 0 && st.D > 1;
-    __shared__ int64_t s_ztop[ZR ? kKeys : 1][kLanes];
-    if (live_stage) {
+    int nf = 0, nb = 0, len = 0, mr = 0, wu = 0, role = 0, nl = 0;
+    double cl0 = 0.0, cl1 = 0.0, cr0 = 0.0, cr1 = 0.0;   // Send costs over the left / right link, by size class
+    int64_t sz0 = 0, sz1 = 0;                            // and bytes
+    if (ok) {
         Ctx x = {};
         make_ctx(M, g.c, st, x);
         x.mlp = !TF;   // the family is uniform per launch: compiles out the other
-        uint64_t res0;
-        ZStage zs;
-        if (ZR && x.zero) {
-            z_stage(x, s, zs);
-            res0 = resident_inputs(x, s) + zs.rmax;
-        } else {
-            res0 = resident(x, s);
+        Pr &q = L[seg];
+        for (int job = s; job < (OV ? kJobs : kJobs - 1); job += W) record_job<TF, ZR, OV>(x, q, job);
+        for (int job = s; job < kKeys * kRoles; job += W) {
+            const int key = job / kRoles, ss = role_stage(x, job % kRoles);
+            int64_t d = 0, t = 0;
+            if (ss >= 0) block_mem<TF, RC>(x, ss, key >= 2, x.mq + (uint64_t)(key & 1), key >= 4, d, t);
+            q.mem[key][job % kRoles][0] = d;
+            q.mem[key][job % kRoles][1] = t;
         }
-        Walk w{x, 0.0, (int64_t)res0, 0, 0, 0, nullptr};
-        w.peak = w.live;
-        // microbatch splits before the pipeline
-        if (x.K > 1) {
-            if (s == 0) split(x, w);
-            if (x.train && s == x.P - 1) split(x, w);
+        if (s < kRoles) {
+            const int ss = role_stage(x, s), per = (!TF && x.H > 1) ? 2 : 1;
+            const int units = ss >= 0 ? stage_nl(x, ss) / per : 0;
+            q.nu[0][s] = units;
+            q.nu[1][s] = units - ((!TF && s == 0) ? 1 : 0);
+            q.nrep[s] = units - 1;
+            if (s == 0) {
+                Count n{x, 0, 0};
+                if (RC) record_partial<TF>(x, 1, n);
+                q.npart = (int)n.walked;
+                q.single = P == 1;
+            }
         }
-        clk = w.clk;
-        live = w.live;
-        peak = w.peak;
-        walked = w.walked;
-        nops = w.nops;
-        len = train ? 2 * K : K;
-        mq = x.mq;
-        mr = (int)x.mr;
-        n_f = block_units(M, P, st.H, s, false, TF);
-        n_b = block_units(M, P, st.H, s, true, TF);
-        if (rc) {
-            const int nl = stage_nl(x, s);
-            n_r = TF ? nl - 1 : nl / (st.H > 1 ? 2 : 1) - 1;
-            Count c{x, 0, 0};
-            record_partial<TF>(x, 1, c);
-            n_part = (int)c.walked;
-        }
-        if constexpr (ZR) {
-            if (zero_c) {
-                // all six kinds up front: every lane of the wavefront at once
+        if (live_stage) {
+            uint64_t res0;
+            if (ZR && x.zero) {
+                ZStage zs;
+                z_stage(x, s, zs);
+                res0 = resident_inputs(x, s) + zs.rmax;
+#pragma unroll 1
                 for (int key = 0; key < kKeys; ++key) {
                     const bool bwd = key >= 2;
-                    const int mc = bwd ? ((key - 2) & 1) : key;
-                    s_ztop[key][lane] = zero_top<TF>(x, s, zs, bwd, x.mq + (uint64_t)mc, key >= 4, bwd ? n_b : n_f, n_r);
+                    s_ztop[key][lane] = zero_top<TF>(x, s, zs, bwd, x.mq + (uint64_t)(key & 1), key >= 4,
+                                                     block_units(x, s, bwd, TF),
+                                                     TF ? stage_nl(x, s) - 1 : stage_nl(x, s) / (x.H > 1 ? 2 : 1) - 1);
                 }
+                wu_top = update_top<TF>(x, s, zs);
+            } else {
+                res0 = resident(x, s);
             }
-        }
-        uint64_t sz, fre;
-        send_size(x, s, 1, false, sz, fre);
-        rb_f = sz;
-        send_size(x, s, 1, true, sz, fre);
-        rb_b = sz;
-        if constexpr (!WIDE) {
-            if (shared) {
-                // empty edges unless a later record fills them
-                for (int d = 0; d < 2; ++d) {
-                    Record e{x, reinterpret_cast<double *>(&L.b.edge[d][0][lane]), 2 * kLanes, 0, 0, 0};
-                    e.pad(Sh::PRE2 + Sh::SUF2);
-                    for (int f = 0; f < 4; ++f) L.b.esum[d][f][lane] = 0;
-                }
+            live = peak = (int64_t)res0;
+            // microbatch splits before the pipeline: the replica's whole
+            // input (stage 0) and target (last stage, training)
+            const int splits = x.K > 1 ? (first ? 1 : 0) + (train && last ? 1 : 0) : 0;
+            if (splits > 0) {
+                const uint64_t whole = input_row(x) * x.rows;
+                const double cs = cost_local(x, 0, 2 * whole);
+                peak = live + (int64_t)whole;
+                for (int i = 0; i < splits; ++i) clk = clk + cs;
             }
+            len = train ? 2 * K : K;
+            wu = f1b ? ((P - 1 - s) < K ? P - 1 - s : K) : K;   // forwards before the first backward
+            mr = (int)x.mr;
+            nl = stage_nl(x, s);
+            role = first ? 0 : (last ? 3 : (s < x.r ? 1 : 2));
+            // a stage's activations and gradients have the same size
+            uint64_t rb, fre;
+            send_size(x, s, 1, false, rb, fre);
+            sz0 = (int64_t)(x.mq * rb);
+            sz1 = (int64_t)((x.mq + 1) * rb);
+            const bool nl_ = send_spans(g.c.node, st.D, st.H, s, s - 1), nr_ = send_spans(g.c.node, st.D, st.H, s, s + 1);
+            cl0 = (nl_ ? g.c.net_lat : g.c.lat) + (double)(uint64_t)sz0 * (nl_ ? g.c.net_inv_l : g.c.inv_l);
+            cl1 = (nl_ ? g.c.net_lat : g.c.lat) + (double)(uint64_t)sz1 * (nl_ ? g.c.net_inv_l : g.c.inv_l);
+            cr0 = (nr_ ? g.c.net_lat : g.c.lat) + (double)(uint64_t)sz0 * (nr_ ? g.c.net_inv_l : g.c.inv_l);
+            cr1 = (nr_ ? g.c.net_lat : g.c.lat) + (double)(uint64_t)sz1 * (nr_ ? g.c.net_inv_l : g.c.inv_l);
+            count_stage<TF>(x, s, walked, nops);
         }
     }
-    if (shared) {
-        if (ok) {
-            Ctx x = {};
-            make_ctx(kernel_args<ParArgs>()->m, kernel_args<ParArgs>()->c, st, x);
-            x.mlp = !TF;
-            for (int key = s; key < kKeys; key += W) {
-                const bool bwd = key >= 2;
-                const int mc = bwd ? ((key - 2) & 1) : key;
-                double2 *u;
-                int64_t *us;
-                if constexpr (WIDE) {
-                    u = &L.unit[seg][key][0];
-                    us = &L.usum[seg][key][0];
-                } else {
-                    u = &L.b.unit[seg][key][0];
-                    us = &L.b.usum[seg][key][0];
-                }
-                Record r{x, reinterpret_cast<double *>(u), 2, 0, 0, 0};
-                const uint64_t m = x.mq + (uint64_t)mc;
-                record_unit<TF>(x, bwd, m, key >= 4, r);
-                r.pad(Sh::U2);
-                us[0] = r.cur;
-                us[1] = r.top;
-                if (rc && !bwd) {
-                    int64_t *xs;
-                    if constexpr (WIDE) xs = &L.xsum[seg][key][0];
-                    else xs = &L.b.xsum[seg][key][0];
-                    Mem f{x, 0, 0}, u2{x, 0, 0}, q{x, 0, 0};
-                    record_unit<TF>(x, false, m, false, f, kFwdFirst);
-                    record_unit<TF>(x, false, m, false, u2, kFwdReplay);
-                    record_partial<TF>(x, m, q);
-                    xs[0] = f.cur;
-                    xs[1] = f.top;
-                    xs[2] = u2.cur;
-                    xs[3] = u2.top;
-                    xs[4] = q.cur;
-                    xs[5] = q.top;
-                }
+    // op counts (they depend on the strategy alone)
+    walked = seg_reduce(walked, W, [](uint64_t a, uint64_t b) { return a + b; });
+    nops = seg_reduce(nops, W, [](uint64_t a, uint64_t b) { return a + b; });
+    if (c >= 0 && first) {
+        if (g.n_ops) g.n_ops[c] = nops;
+        if (g.walked) g.walked[c] = walked;
+    }
+    __syncthreads();
+    const Pr &prog = L[seg];
+
+    // The whole ulps of candidate sg's blocks and units while the clock has
+    // the biased exponent e: inside one binade, rounding to nearest adds each
+    // cost as the whole number of ulps nearest to it, whatever the clock is,
+    // unless the cost lies exactly half way between two.
+    // Eight lanes per block kind.
+    int tag0 = -1, tag1 = -1;   // exponents held for this lane's segment, by parity
+    auto build = [&](int sg, int e) {
+        Pr &q = L[sg];
+        const double sc = ldexp(1.0, 1075 - e);   // 1 / ulp
+        const int key = lane >> 3, part = lane & 7;
+        const bool bwd = key >= 2;
+        double u = 0.0, p = 0.0, f = 0.0, up = 0.0;
+        bool tie = false;
+        // entry j = part, part + 8, ... of n (at most 8 * MAX); *head: the
+        // sum over the first nh
+        auto add = [&](auto max, const double *a, int n, double &sum, double *head, int nh) {
+            double t[max.value];
+#pragma unroll
+            for (int i = 0; i < max.value; ++i) t[i] = part + 8 * i < n ? a[part + 8 * i] * sc : 0.0;
+#pragma unroll
+            for (int i = 0; i < max.value; ++i) {
+                const double r = rint(t[i]);
+                tie = tie || fabs(t[i] - r) == 0.5;
+                sum += r;
+                if (RC && head) *head += part + 8 * i < nh ? r : 0.0;
             }
+        };
+        if (key < kKeys) {
+            add(Rounds<2 * Pr::Sh::U2>(), q.unit(key), Pr::n_unit(bwd), u, &up, q.npart);
+            add(Rounds<2 * Pr::Sh::PRE2>(), q.pre(key), Pr::n_pre(bwd), p, nullptr, 0);
+            add(Rounds<2 * Pr::Sh::SUF2>(), q.suf(key), Pr::n_suf(bwd), f, nullptr, 0);
         }
-        if constexpr (WIDE) {
-            if (lane < Sh::PRE2 + Sh::SUF2) L.zero[lane] = make_double2(0.0, 0.0);
-            if (lane < 4) L.zsum[lane] = 0;
+        // lanes 1, 2 apart, then the other half of the eight
+        auto sum8 = [](double v) {
+            v += dpp<0xb1, 0xf>(v);
+            v += dpp<0x4e, 0xf>(v);
+            v += dpp<0x141, 0xf>(v);
+            return v;
+        };
+        u = sum8(u);
+        p = sum8(p);
+        f = sum8(f);
+        const uint64_t ties = ballot(tie);
+        bool bad = ((ties >> (lane & 56)) & 0xff) != 0;
+        double rep = 0.0, repp = 0.0;
+        if (RC) {
+            // backward blocks replay the forward units of their row class
+            up = sum8(up);
+            rep = __shfl(u, 8 * (key & 1), kLanes);
+            repp = __shfl(up, 8 * (key & 1), kLanes);
+            bad = bad || (bwd && ((ties >> (8 * (key & 1))) & 0xff) != 0);
         }
+        // (whole numbers: exact below 2^53; a block of 2^52 ulps or more
+        // leaves the binade anyway)
+        if (key < kKeys && part < kRoles) {
+            const bool fr = part == 0, ls = part == 3 || (part == 0 && q.single);
+            double t = (double)q.nu[bwd][part] * u;
+            if (Pr::has_pre(bwd, fr, ls)) t += p;
+            if (Pr::has_suf(bwd, fr, ls)) t += f;
+            if (RC && bwd) t += (double)q.nrep[part] * rep + repp;
+            q.blk[e & 1][key][part] = (!bad && t < 0x1p52) ? (int64_t)t : kWalk;
+        }
+        if (key < kKeys && part == 4) q.unit_ulps[e & 1][key] = (!bad && u < 0x1p52) ? make_double2(u, 1.0 / u) : make_double2(-1.0, 0.0);
         __syncthreads();
-    }
-    int key_f = -1, key_b = -1;   // key each lane-owned program was recorded for
+        if (seg == sg) {
+            if (e & 1) tag1 = e;
+            else tag0 = e;
+        }
+    };
+    // builds the tables that the lanes of `want` miss, one exponent per segment
+    auto build_for = [&](uint64_t want, int ex) {
+        while (want != 0) {
+            const int l0 = __builtin_ctzll(want);
+            build(l0 >> cls, __builtin_amdgcn_readlane(ex, l0));
+            want &= ~(W == 64 ? ~0ull : (((1ull << W) - 1) << (l0 & ~(W - 1))));
+        }
+    };
+    auto exponent = [](double v) { return (int)((uint32_t)__double2hiint(v) >> 20); };
+    auto held = [&](int ex) { return (ex & 1) ? tag1 : tag0; };
+    // n units of kind `key` on the lanes that are `on`: as many at once as
+    // stay in the clock's binade, the one that leaves it op by op
+    auto advance = [&](bool on, int key, int n) {
+        int left = on ? n : 0;
+        while (ballot(left > 0) != 0) {
+            const int ex = exponent(clk);
+            const uint64_t want = ballot(left > 1 && held(ex) != ex && ex >= kMinExp && ex < kInfExp);
+            if (want != 0) build_for(want, ex);
+            if (left > 1) {
+                if (ex == kInfExp) {
+                    left = 0;   // an overflowed clock stays +inf
+                } else if (held(ex) == ex) {
+                    const double2 u = prog.unit_ulps[ex & 1][key];
+                    if (u.x >= 0.0) {
+                        // the clock and its room in ulps, whole and below
+                        // 2^53; room / u may come out a little off
+                        const double at = ldexp(clk, 1075 - ex), room = (0x1p53 - 1.0) - at;
+                        double k = floor(fmin(room * u.y, (double)left));   // u = 0: +inf
+                        k = k * u.x > room ? k - 1.0 : k;
+                        clk = ldexp(at + k * u.x, ex - 1075);
+                        left -= (int)k;
+                    }
+                }
+            }
+            if (left > 0) {
+                // (the forward unit is the shorter one: the rest only where
+                // some lane's unit is a backward one)
+                const double *a = prog.unit(key);
+                clk = walk<Pr::Sh::F_U2, Pr::Sh::F_U2>(a, false, clk);
+                if (key >= 2) {
+                    constexpr int kRest = Pr::Sh::U2 - Pr::Sh::F_U2;
+                    clk = walk<kRest, kRest>(a + 2 * Pr::Sh::F_U2, false, clk);
+                }
+                --left;
+            }
+        }
+    };
+    // under overlap: a hand-over on both clocks, and the last backward
+    // block's programs (an edge with its one hand-over; a unit, the MLP's on
+    // stage 0 without the last entry, its input gradient's all-reduce)
+    auto hand = [&](double send, double ar) {
+        clk = max_nn(clk, clkm) + send;
+        clkm = clk + ar;
+    };
+    auto marked = [&](const double *a, int n, const Mark &mk) {
+        for (int j = 0; j < n; ++j) {
+            if (j == mk.pos) hand(mk.send, mk.ar);
+            clk = clk + a[j];
+        }
+        if (mk.pos >= n) hand(mk.send, mk.ar);
+    };
+    auto ov_unit = [&](bool whole) {
+        if constexpr (OV) {
+            using U = OvUnit<TF>;
+#pragma unroll
+            for (int j = 0; j < U::kEntries; ++j) {
+#pragma unroll
+                for (int i = 0; i < U::kMarks; ++i)
+                    if (j == U::pos(i) && (TF || prog.ov.send[i] >= 0.0)) hand(prog.ov.send[i], prog.ov.ar[i]);
+                clk = clk + ((TF || whole || j + 1 < U::kEntries) ? prog.ov.cost[j] : 0.0);
+            }
+        }
+    };
 
     // Repeated periods.  In the steady phase of a schedule every stage runs
     // the same blocks again every two slots (1F1B: a forward and a backward
@@ -1317,292 +1457,156 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
     // then taken two at a time.  The remaining periods up to the next
     // binade, size class or phase are added at once: the doubles that walking
     // them gives.  Memory moves by the period's net bytes (whole numbers).
-    // (one wavefront's slots are a serial chain: 398 GPT-2-small-shaped
-    // training strategies went from 479 to 195 us, GPT-3-shaped with ZeRO from
-    // 3.42 to 3.10 ms)
-    __shared__ int64_t s_snap[3][kLanes];   // clock bits, live, peak at the period's start
-    __shared__ int64_t s_prev[kLanes];      // the last period's shift, -1: none
-    s_snap[0][lane] = 0;
-    s_snap[1][lane] = 0;
-    s_snap[2][lane] = 0;
-    s_prev[lane] = -1;
     const uint64_t stage_mask = ballot(live_stage);
-    const uint64_t next_mask = ballot(live_stage && s > 0);   // lanes compared with the stage before
-    const bool f1b = train && M.schedule != DSIM_SCHED_GPIPE;
+    const uint64_t next_mask = ballot(live_stage && !first);   // lanes compared with the stage before
+    const uint64_t last_mask = ballot(live_stage && last);
     uint64_t rdy_prev = 0, bwd_prev = 0;
+    int64_t c0 = 0, live0 = 0, peak0 = 0;   // clock bits and bytes at the period's start
+    int64_t d_prev = -1;                    // the last period's shift, -1: none
     bool odd = false;
 
     for (;;) {
-        const bool active = live_stage && pos < len;
-        const uint64_t act_mask = ballot(active);
-        if (act_mask == 0) break;
+        // forward-only, GPipe or synchronous 1F1B: the next block's direction
+        // (its microbatch is the count of blocks of that direction), ready
+        // once its input was produced in an earlier slot
+        const bool bwd = nf == K || nf - nb > wu;
         const int nf_left = shr1(nf), nb_right = shl1(nb);   // slot-start counters
-        bool bwd = false, ready = false;
-        int k = 0;
-        if (active) {
-            // forward-only / GPipe / synchronous 1F1B position -> (direction, microbatch)
-            if (!train) {
-                k = pos;
-            } else if (M.schedule == DSIM_SCHED_GPIPE) {
-                bwd = pos >= K;
-                k = bwd ? pos - K : pos;
-            } else {
-                const int wu = (P - 1 - s) < K ? (P - 1 - s) : K;
-                if (pos < wu) {
-                    k = pos;
-                } else if (pos < wu + 2 * (K - wu)) {
-                    const int j = pos - wu;
-                    bwd = (j & 1) != 0;
-                    k = bwd ? (j - 1) / 2 : wu + j / 2;
-                } else {
-                    bwd = true;
-                    k = pos - wu - (K - wu);
-                }
-            }
-            ready = !bwd ? (s == 0 || nf_left > k) : (s == P - 1 ? nf > k : nb_right > k);
-        }
+        const int k = bwd ? nb : nf;
+        const int avail = bwd ? (last ? nf : nb_right) : (first ? INT_MAX : nf_left);
+        const bool ready = nf + nb < len && avail > k;
         const uint64_t rdy_mask = ballot(ready);
-        const uint64_t segmask = W == 64 ? ~0ull : (((1ull << W) - 1) << (lane & ~(W - 1)));
-        if ((act_mask & segmask) != 0 && (rdy_mask & segmask) == 0) {
-            // no stage can proceed: impossible for 1F1B, stops the candidate
-            status |= DSIM_ST_BAD_STRATEGY;
-            live_stage = false;
-        }
+        if (rdy_mask == 0) break;
         const uint64_t bwd_mask = ballot(ready && bwd);
-        const bool all_fwd = bwd_mask == 0;
+        const bool mc = k < mr;
+        const uint64_t mc_mask = ballot(mc);
+        const int key = (mc ? 1 : 0) + (bwd ? (nb > 0 ? 4 : 2) : 0);
 
-        // long unit runs take the binade-wise path (uniform per wavefront)
-        const bool fast = kBinadeSums && ballot(ready && (bwd ? n_b : n_f) >= kFastUnits) != 0;
-        // under recomputation a wave with backward blocks walks the pre ops
-        // and the replay first (forward lanes: their pre ops, no units), then
-        // every lane's units and suf
-        const bool replay = rc && !all_fwd;
-        const bool fast_r = kBinadeSums && replay && ballot(ready && bwd && n_r >= kFastUnits) != 0;
-        const int d = bwd ? 1 : 0;
-        const int mc = k < mr ? 1 : 0;
-        const uint64_t m = mq + (uint64_t)mc;
+        // ---- the blocks
+        const int ex = exponent(clk);
+        if (ballot(ready && held(ex) != ex) != 0) {
+            const uint64_t miss = ballot(ready && held(ex) != ex && ex >= kMinExp && ex < kInfExp);
+            if (miss != 0) build_for(miss, ex);
+        }
+        const double next = __longlong_as_double(__double_as_longlong(clk) + prog.blk[ex & 1][key][role]);
+        bool fits = held(ex) == ex && exponent(next) == ex;
+        const bool hov = OV && ov_c && bwd && nb == K - 1;   // hands its gradients over
+        if (OV) fits = fits && !hov;
+        const uint64_t slow = ballot(ready && !fits);
+        if (ready && fits) clk = next;
+        if (slow != 0) {
+            const bool on = __builtin_amdgcn_inverse_ballot_w64(slow);
+            if (on && Pr::has_pre(bwd, first, last)) {
+                const double *a = prog.pre(key);
+                if (OV && TF && hov) marked(a, Pr::n_pre(true), prog.mark[0]);
+                else clk = walk<Pr::Sh::F_PRE2, Pr::Sh::PRE2>(a, bwd, clk);
+            }
+            if (RC) {
+                advance(on && bwd, mc ? 1 : 0, prog.nrep[role]);
+                if (on && bwd) {
+                    const double *a = prog.unit(mc ? 1 : 0);
+                    for (int j = 0; j < prog.npart; ++j) clk = clk + a[j];
+                }
+            }
+            if (OV && hov && on)
+                for (int i = 0; i < prog.nu[1][role]; ++i) ov_unit(true);
+            advance(on && !hov, key, prog.nu[bwd ? 1 : 0][role]);
+            if (on && Pr::has_suf(bwd, first, last)) {
+                const double *a = prog.suf(key);
+                if (OV && TF && hov) marked(a, Pr::n_suf(true), prog.mark[1]);
+                else if (OV && hov) ov_unit(false);
+                else clk = walk<Pr::Sh::F_SUF2, Pr::Sh::SUF2>(a, bwd, clk);
+            }
+        }
         if (ready) {
-            const bool acc = bwd && k >= 1;
-            const int key = bwd ? 2 + mc + (acc ? 2 : 0) : mc;
-            const int n = bwd ? n_b : n_f;
-            const int nr = bwd ? n_r : 0, np = bwd ? n_part : 0;
-            int64_t delta = 0, top = 0;
-            bool lane_done = false;
-            if constexpr (OV) {
-                if (ov_c && bwd && k == K - 1) {
-                    // the last backward block under overlap hands each
-                    // finished gradient to the communication stream: walked
-                    // op by op with both clocks, memory as it goes
-                    Ctx x = {};
-                    make_ctx(kernel_args<ParArgs>()->m, kernel_args<ParArgs>()->c, st, x);
-                    x.mlp = !TF;
-                    Walk w{x, clk, live, live, 0, 0, nullptr};
-                    w.tm = clkm;
-                    block_bwd(x, w, s, k);
-                    clk = w.clk;
-                    clkm = w.tm;
-                    delta = w.live - live;
-                    top = w.peak - live;
-                    lane_done = true;
-                }
-            }
-            if constexpr (!WIDE) {
-                if (!shared && !lane_done) {
-                    double2 *pp = &L.a.prog[d][0][lane];
-                    if ((bwd ? key_b : key_f) != key || (replay && bwd && key_f != mc)) {
-                        Ctx x = {};
-                        make_ctx(kernel_args<ParArgs>()->m, kernel_args<ParArgs>()->c, st, x);
-                        x.mlp = !TF;
-                        if ((bwd ? key_b : key_f) != key) {
-                            record_lane<TF, Sh>(x, s, bwd, m, acc, n, n_r, pp, L.a.sum[d][0][lane], L.a.sum[d][1][lane]);
-                            if (bwd) key_b = key;
-                            else key_f = key;
-                        }
-                        if (replay && bwd && key_f != mc) {   // the replay walks the forward unit of this size
-                            record_lane<TF, Sh>(x, s, false, m, false, n_f, n_r, &L.a.prog[0][0][lane], L.a.sum[0][0][lane],
-                                            L.a.sum[0][1][lane]);
-                            key_f = mc;
-                        }
-                    }
-                    const double2 *up = pp + Sh::PRE2 * kLanes, *sp = pp + (Sh::PRE2 + Sh::U2) * kLanes;
-                    if (replay) {
-                        const double2 *fu = &L.a.prog[0][Sh::PRE2][lane];
-                        clk = walk3<Sh::PRE2, Sh::F_U2, 0, kLanes, kLanes>(pp, fu, nullptr, clk, nr, fast_r);
-                        clk = walk_prefix<kLanes>(fu, np, clk);
-                        clk = walk3<0, Sh::U2, Sh::SUF2, kLanes, kLanes>(nullptr, up, sp, clk, n, fast);
-                    } else if (all_fwd) {
-                        clk = walk3<Sh::F_PRE2, Sh::F_U2, Sh::F_SUF2, kLanes, kLanes>(pp, up, sp, clk, n, fast);
-                    } else {
-                        clk = walk3<Sh::PRE2, Sh::U2, Sh::SUF2, kLanes, kLanes>(pp, up, sp, clk, n, fast);
-                    }
-                    delta = L.a.sum[d][0][lane];
-                    top = L.a.sum[d][1][lane];
-                    lane_done = true;
-                }
-            }
-            if (!lane_done) {
-                // edge program and summary of this lane and direction
-                const bool has_edges = !TF || s == 0 || s == P - 1;
-                double2 *ep;
-                int64_t *es;
-                int es_stride;
-                if constexpr (WIDE) {
-                    const int slot = s == 0 ? 0 : 1;
-                    ep = has_edges ? &L.edge[seg][slot][d][0] : &L.zero[0];
-                    es = has_edges ? &L.esum[seg][slot][d][0] : &L.zsum[0];
-                    es_stride = 1;
-                } else {
-                    ep = &L.b.edge[d][0][lane];
-                    es = &L.b.esum[d][0][lane];
-                    es_stride = kLanes;
-                }
-                // transformer edges sit on stages 0 and P-1 only; every MLP
-                // stage ends its backward with its first unit
-                if (has_edges && (bwd ? key_b : key_f) != key) {
-                    Ctx x = {};
-                    make_ctx(kernel_args<ParArgs>()->m, kernel_args<ParArgs>()->c, st, x);
-                    x.mlp = !TF;
-                    double *base = reinterpret_cast<double *>(ep);
-                    Record rp{x, base, 2 * PST, 0, 0, 0};
-                    Record rs{x, base + Sh::PRE2 * 2 * PST, 2 * PST, 0, 0, 0};
-                    record_edges<TF>(x, s, bwd, m, acc, rp, rs);
-                    rp.pad(Sh::PRE2);
-                    rs.pad(Sh::SUF2);
-                    es[0 * es_stride] = rp.cur;
-                    es[1 * es_stride] = rp.top;
-                    es[2 * es_stride] = rs.cur;
-                    es[3 * es_stride] = rs.top;
-                    if (bwd) key_b = key;
-                    else key_f = key;
-                }
-                const double2 *up, *fu, *sp = ep + Sh::PRE2 * PST;
-                const int64_t *us, *xs;
-                if constexpr (WIDE) {
-                    up = &L.unit[seg][key][0];
-                    us = &L.usum[seg][key][0];
-                    fu = &L.unit[seg][mc][0];
-                    xs = &L.xsum[seg][mc][0];
-                } else {
-                    up = &L.b.unit[seg][key][0];
-                    us = &L.b.usum[seg][key][0];
-                    fu = &L.b.unit[seg][mc][0];
-                    xs = &L.b.xsum[seg][mc][0];
-                }
-                if (replay) {
-                    clk = walk3<Sh::PRE2, Sh::F_U2, 0, PST, 1>(ep, fu, nullptr, clk, nr, fast_r);
-                    clk = walk_prefix<1>(fu, np, clk);
-                    clk = walk3<0, Sh::U2, Sh::SUF2, PST, 1>(nullptr, up, sp, clk, n, fast);
-                } else if (all_fwd) {
-                    clk = walk3<Sh::F_PRE2, Sh::F_U2, Sh::F_SUF2, PST, 1>(ep, up, sp, clk, n, fast);
-                } else {
-                    clk = walk3<Sh::PRE2, Sh::U2, Sh::SUF2, PST, 1>(ep, up, sp, clk, n, fast);
-                }
-                const int64_t pd = es[0], pt = es[1 * es_stride], sd = es[2 * es_stride], st2 = es[3 * es_stride];
-                if (!rc) {
-                    compose(pd, pt, us[0], us[1], n, sd, st2, delta, top);
-                } else if (!bwd) {
-                    compose_first(pd, pt, xs[0], xs[1], us[0], us[1], n, sd, st2, delta, top);
-                } else {
-                    compose(pd, pt, xs[2], xs[3], n_r, xs[4], xs[5], delta, top);
-                    int64_t d2, t2;
-                    compose(0, 0, us[0], us[1], n, sd, st2, d2, t2);
-                    chain(delta, top, d2, t2);
-                }
-            }
-            if constexpr (ZR) {
-                // the net bytes do not depend on ownership; the highest point does
-                if (zero_c) top = s_ztop[key][lane];
-            }
-            const int64_t hi = live + top;
-            peak = hi > peak ? hi : peak;
+            const int64_t delta = prog.mem[key][role][0];
+            int64_t top = prog.mem[key][role][1];
+            // with ZeRO the net bytes do not depend on ownership; the highest point does
+            if (ZR && zero_c) top = s_ztop[key][lane];
+            peak = max_bytes(live + top, peak);
             live += delta;
-            ++pos;
             if (bwd) ++nb;
             else ++nf;
         }
 
-        // the slot's sends, ascending by source stage
-        int sdir = 0;
-        double scost = 0.0;
-        uint64_t ssz = 0, sfre = 0;
-        if (ready && ((!bwd && s < P - 1) || (bwd && s > 0))) {
-            sdir = bwd ? -1 : 1;
-            ssz = m * (bwd ? rb_b : rb_f);
-            sfre = (TF || bwd || !train) ? ssz : 0;
-            const bool net = send_spans(g.c.node, st.D, st.H, s, bwd ? s - 1 : s + 1);
-            scost = (net ? g.c.net_lat : g.c.lat) + (double)ssz * (net ? g.c.net_inv_l : g.c.inv_l);
-        }
-        const int l_dir = shr1(sdir), r_dir = shl1(sdir);
-        const double l_cost = shr1(scost), r_cost = shl1(scost);
-        const uint64_t l_sz = shr1(ssz), r_sz = shl1(ssz);
-        const bool from_left = live_stage && s >= 1 && l_dir == 1;
-        const bool from_right = live_stage && s + 1 < P && r_dir == -1;
-        // Send s depends on send s-1 only if s-1 went forward (it moved clock
-        // s) or s goes backward (it reads clock s-1); elsewhere the chain
-        // splits into runs that touch disjoint clocks and proceed in parallel.
-        // rpos = position of the stage in its run.
-        const bool linked = s >= 1 && s < P && (l_dir == 1 || sdir == -1);
-        const uint64_t starts = ballot(!linked);
-        const uint64_t upto = starts & (lane == 63 ? ~0ull : ((2ull << lane) - 1));
-        const int rpos = lane - (63 - __builtin_clzll(upto));
-        // the last run position of the wave (a position without a Send
-        // changes nothing: its receivers need a sender there)
-        int last = 0;
-        for (int b = 32; b >= 1; b >>= 1)
-            if (ballot(rpos >= last + b) != 0) last += b;
-        // long runs (pipeline fill and drain) take the scans, short ones the steps
-        if (last < kScanMinRun || !send_scan(clk, sdir, scost, from_left, from_right, lane, 32 - __clz(last))) {
-        for (int r = 0; r <= last; ++r) {
-            const bool src = rpos == r && sdir != 0;
-            const double cl = shr1(clk), cr = shl1(clk);
-            const bool tl = rpos == r + 1 && from_left;
-            const bool tr = rpos == r - 1 && from_right;
-            const double a = ((src && sdir < 0) || tl) ? cl : cr;
-            // clocks are sums of costs >= 0 from +0.0: never NaN or -0.0,
-            // so the bare maximum instruction gives the larger value (fmax
-            // would first canonicalize both operands)
-            const double e = max_nn(a, clk) + (src ? scost : (tl ? l_cost : r_cost));
-            if (src || tl || tr) clk = e;
-        }
-        }
-        if (live_stage) {
-            if (from_left) {
-                live += (int64_t)l_sz;
-                peak = live > peak ? live : peak;
+        // ---- the slot's Sends, ascending by source stage.  Send s depends on
+        // Send s-1 only if that went forward (it moved clock s) or this one
+        // goes backward (it reads clock s-1); elsewhere the chain splits into
+        // runs that touch disjoint clocks and proceed in parallel.
+        const uint64_t fs = rdy_mask & ~bwd_mask & ~last_mask, bs = bwd_mask & next_mask;   // sources
+        const uint64_t fl = fs << 1, fr = bs >> 1;                                          // receivers
+        if ((fs | bs) != 0) {
+            const uint64_t linked = fl | bs;
+            const bool l_mc = __builtin_amdgcn_inverse_ballot_w64(mc_mask << 1);
+            const bool r_mc = __builtin_amdgcn_inverse_ballot_w64(mc_mask >> 1);
+            const double own = bwd ? (mc ? cl1 : cl0) : (mc ? cr1 : cr0);
+            const double c_left = l_mc ? cl1 : cl0, c_right = r_mc ? cr1 : cr0;
+            const bool from_left = __builtin_amdgcn_inverse_ballot_w64(fl);
+            const bool from_right = __builtin_amdgcn_inverse_ballot_w64(fr);
+            const bool sends = __builtin_amdgcn_inverse_ballot_w64(fs | bs);
+            // runs of 12 and more Sends after the first (pipeline fill and
+            // drain) take the scans, shorter ones the steps: from there on
+            // the scans never lost
+            uint64_t run = linked & (linked << 1);
+            run &= run << 2;
+            run &= run << 4;
+            run &= run << 4;
+            if (run == 0 || !send_scan(clk, bwd, own, fs | bs, fl, fr, lane, W, segmask)) {
+                for (uint64_t at = ~linked; at != 0; at = (at << 1) & linked) {
+                    const uint64_t af = at & fs, ab = at & bs;
+                    if ((af | ab) == 0) continue;
+                    // a Send's two stages both end at the later clock plus
+                    // its cost (clocks are never NaN or -0.0)
+                    const bool src = __builtin_amdgcn_inverse_ballot_w64(af | ab);
+                    const bool left = __builtin_amdgcn_inverse_ballot_w64((af << 1) | ab);   // partner on the left
+                    const double lc = shr1(clk), rc_ = shl1(clk);
+                    const double e = max_nn(left ? lc : rc_, clk) + (src ? own : (left ? c_left : c_right));
+                    clk = __builtin_amdgcn_inverse_ballot_w64(af | ab | (af << 1) | (ab >> 1)) ? e : clk;
+                }
             }
-            if (sdir != 0) live -= (int64_t)sfre;
+            if (from_left) {
+                live += l_mc ? sz1 : sz0;
+                peak = max_bytes(live, peak);
+            }
+            // (an MLP's training stage keeps the activation it sends)
+            if (sends && (TF || bwd || !train)) live -= mc ? sz1 : sz0;
             if (from_right) {
-                live += (int64_t)r_sz;
-                peak = live > peak ? live : peak;
+                live += r_mc ? sz1 : sz0;
+                peak = max_bytes(live, peak);
             }
         }
 
-        // every second slot: whole periods ahead (see above)
+        // ---- every second slot: whole periods ahead (see above)
         if (odd) {
             const uint64_t both = rdy_prev & rdy_mask, pairs = bwd_prev ^ bwd_mask;
             // a stage that did not run twice, not the pattern of its
             // schedule, or another direction than the stage before
-            const uint64_t off = (~both | (f1b ? ~pairs : pairs)) & stage_mask;
-            const uint64_t turn = f1b ? 0 : (bwd_mask ^ (bwd_mask << 1)) & next_mask;
-            const int64_t cb = __double_as_longlong(clk);
-            if ((off | turn) != stage_mask) {
-                const int64_t c0 = s_snap[0][lane], dl = live - s_snap[1][lane];
-                const int64_t d = cb - c0;
-                const int ex = (int)(cb >> 52);
+            const uint64_t off = ((~both | (f1b ? ~pairs : pairs)) & stage_mask) |
+                                 (f1b ? 0 : (bwd_mask ^ (bwd_mask << 1)) & next_mask);
+            const int64_t now = __double_as_longlong(clk);
+            bool whole = off == 0;   // some segment's stages all ran
+            for (int i = 0; !whole && i < kLanes; i += W) {
+                const uint64_t sm = W == 64 ? ~0ull : ((1ull << W) - 1) << i;
+                whole = (off & sm) == 0 && (stage_mask & sm) != 0;
+            }
+            const int64_t d = now - c0;
+            if (whole) {
+                const int64_t dl = live - live0;
+                const int ec = (int)(now >> 52);
                 const int back = (int)(d & 1);
-                bool bad = ((off | turn) >> lane & 1) != 0 || ex == 0 || ex == 0x7ff || ex != (int)(c0 >> 52) ||
-                           (dl > 0 && peak <= s_snap[2][lane]);
                 const int64_t dn = (int64_t)shr1((uint64_t)d);
-                const int en = shr1(ex);
-                bad = live_stage && (bad || (s > 0 && (d != dn || ex != en)));
+                const int en = shr1(ec);
+                const bool bad = live_stage &&
+                                 (__builtin_amdgcn_inverse_ballot_w64(off) || ec == 0 || ec == kInfExp ||
+                                  ec != (int)(c0 >> 52) || (dl > 0 && peak <= peak0) ||
+                                  (!first && (d != dn || ec != en)));
                 const bool seg_ok = live_stage && (ballot(bad) & segmask) == 0;
                 if (ballot(seg_ok) != 0) {
                     int q = INT_MAX;
                     if (seg_ok) {
-                        q = repeats(f1b, bwd, pos, P, s, K, mr, back, ov_c);
-                        if (back && s_prev[lane] != d) q = 0;
+                        q = repeats(f1b, bwd, nf, nb, K, mr, back, ov_c);
+                        if (back && d_prev != d) q = 0;
                         if (q > 0 && d > 0) {
-                            const int64_t room = (((int64_t)ex + 1) << 52) - 1 - cb;
+                            const int64_t room = (((int64_t)ec + 1) << 52) - 1 - now;
                             const double est = (double)room / (double)d;
                             if (est < (double)q) {
                                 q = (int)est;
@@ -1613,72 +1617,72 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
                     q = seg_reduce(q, W, [](int a, int b) { return a < b ? a : b; });
                     if (back) q &= ~1;
                     if (seg_ok && q > 0) {
-                        clk = __longlong_as_double(cb + (int64_t)q * d);
+                        clk = __longlong_as_double(now + (int64_t)q * d);
                         live += (int64_t)q * dl;
                         if (dl > 0) peak += (int64_t)q * dl;
-                        pos += 2 * q;
                         nf += f1b ? q : (bwd ? 0 : 2 * q);
                         nb += f1b ? q : (bwd ? 2 * q : 0);
                     }
                 }
-                s_prev[lane] = seg_ok ? d : -1;
+                d_prev = seg_ok ? d : -1;
             } else {
-                s_prev[lane] = -1;
+                d_prev = -1;
             }
-            s_snap[0][lane] = __double_as_longlong(clk);
-            s_snap[1][lane] = live;
-            s_snap[2][lane] = peak;
+            c0 = __double_as_longlong(clk);
+            live0 = live;
+            peak0 = peak;
         }
         odd = !odd;
         rdy_prev = rdy_mask;
         bwd_prev = bwd_mask;
     }
-    if (live_stage && status == 0) {
-        Ctx x = {};
-        // (the narrow kernels and the wide ZeRO one keep these values live
-        // across the loop instead: reading the argument block again here
-        // makes the register allocator reserve a private frame in them that
-        // no instruction uses)
-        if constexpr (WIDE && !(ZR && !RC))
-            make_ctx(kernel_args<ParArgs>()->m, kernel_args<ParArgs>()->c, st, x);
-        else
-            make_ctx(M, g.c, st, x);
-        x.mlp = !TF;
-        ZStage zs;
-        if (ZR && x.zero) z_stage(x, s, zs);
-        Walk w{x, clk, live, peak, walked, nops, &zs};
-        w.tm = clkm;
-        if (train) weight_update(x, w, s);
-        // the stage's latest device (under overlap the computation stream
-        // ends last: its final op is an optimizer step after a hand-back)
-        clk = w.clk > w.tm ? w.clk : w.tm;
-        live = w.live;
-        peak = w.peak;
-        walked = w.walked;
-        nops = w.nops;
-        count_blocks(x, s, walked, nops);
+    // (blocks left over that no stage can run: impossible for these schedules)
+    if (nf + nb < len) status |= DSIM_ST_BAD_STRATEGY;
+    if (live_stage && train) {
+        // the weight update: each parameter's collective, then its optimizer
+        // op (no memory above what the blocks reached, but ZeRO's reduced
+        // gradients).  Under overlap the reduced gradients come back from the
+        // communication stream, which is behind after the first hand-back.
+        if (OV && ov_c) clk = max_nn(clk, clkm);
+        auto param = [&](const double2 v) {
+            clk = clk + v.x;
+            clk = clk + v.y;
+        };
+        if (TF && first) param(prog.wu[4]);
+        constexpr int kPar = TF ? 4 : 1;
+        double2 r[kPar];
+#pragma unroll
+        for (int j = 0; j < kPar; ++j) r[j] = prog.wu[j];
+        if (nl >= kFastUnits) {
+            clk = units_exact(r, clk, nl);
+        } else {
+            for (int i = 0; i < nl; ++i) clk = units_seq(r, clk);
+        }
+        if (TF && last) param(prog.wu[4]);
+        if (ZR && zero_c) {
+            const int64_t hi = live + wu_top;
+            peak = hi > peak ? hi : peak;
+        }
     }
 
     // per-candidate results: reductions over the segment
-    const bool contributes = s < P && status == 0;
-    const double mk = seg_reduce(contributes ? clk : 0.0, W, [](double a, double b) { return a > b ? a : b; });
-    const uint64_t cp = seg_reduce(contributes ? (uint64_t)peak : 0ull, W,
-                                   [](uint64_t a, uint64_t b) { return a > b ? a : b; });
-    const uint64_t tops = seg_reduce(contributes ? nops : 0ull, W, [](uint64_t a, uint64_t b) { return a + b; });
-    const uint64_t twalk = seg_reduce(contributes ? walked : 0ull, W, [](uint64_t a, uint64_t b) { return a + b; });
     status = seg_reduce(status, W, [](int32_t a, int32_t b) { return a | b; });
-    if (c < 0) return;
     const bool valid = status == 0;
-    if (s == 0) {
+    const bool mine = valid && live_stage;
+    const double mk = seg_reduce(mine ? clk : 0.0, W, [](double a, double b) { return a > b ? a : b; });
+    const uint64_t cp = seg_reduce(mine ? (uint64_t)peak : 0ull, W, [](uint64_t a, uint64_t b) { return a > b ? a : b; });
+    if (c < 0) return;
+    if (first) {
         int32_t stt = status;
         if (valid && g.c.cap != 0 && cp > g.c.cap) stt |= DSIM_ST_OVER_CAP;
-        g.makespan[c] = valid ? mk : 0.0;
-        g.cand_peak[c] = valid ? cp : 0;
+        g.makespan[c] = mk;
+        g.cand_peak[c] = cp;
         g.status[c] = stt;
-        if (g.n_ops) g.n_ops[c] = valid ? tops : 0;
-        if (g.walked) g.walked[c] = valid ? twalk : 0;
+        if (!valid) {
+            if (g.n_ops) g.n_ops[c] = 0;
+            if (g.walked) g.walked[c] = 0;
+        }
     }
-    const bool mine = valid && s < P;
     if (g.finish) {
         double *row = g.finish + (size_t)c * g.row_width;
         for (int j = s; j < g.row_width; j += W) row[j] = (mine && j == s) ? clk : 0.0;
@@ -1692,37 +1696,28 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
 template <bool TF, bool RC, bool ZR, bool OV>
 __global__ __launch_bounds__(kLanes) void k_parametric(const ParArgs g)
 {
-    parametric_body<TF, false, RC, ZR, OV>(g);
+    parametric_body<TF, RC, ZR, OV>(g);
 }
 
-// wide segments of a transformer: two wavefronts per SIMD
+// the kernel of a launch, by family and model options
 template <bool RC, bool ZR, bool OV>
-__global__ __launch_bounds__(kLanes) __attribute__((amdgpu_waves_per_eu(2))) void k_parametric_wide(const ParArgs g)
+void launch_variant(bool tf, dim3 grid, hipStream_t s, const ParArgs &g)
 {
-    parametric_body<true, true, RC, ZR, OV>(g);
-}
-
-// the kernel of a launch, by family, width class and model options
-template <bool RC, bool ZR, bool OV>
-void launch_variant(bool tf, bool wide, dim3 grid, dim3 block, hipStream_t s, const ParArgs &g)
-{
-    if (!tf) hipLaunchKernelGGL((k_parametric<false, RC, ZR, OV>), grid, block, 0, s, g);
-    else if (!wide) hipLaunchKernelGGL((k_parametric<true, RC, ZR, OV>), grid, block, 0, s, g);
-    else hipLaunchKernelGGL((k_parametric_wide<RC, ZR, OV>), grid, block, 0, s, g);
+    if (tf) hipLaunchKernelGGL((k_parametric<true, RC, ZR, OV>), grid, dim3(kLanes), 0, s, g);
+    else hipLaunchKernelGGL((k_parametric<false, RC, ZR, OV>), grid, dim3(kLanes), 0, s, g);
 }
 
 // (ZeRO and overlap exclude one another)
-void launch_kernel(bool rc, bool zr, bool ov, bool tf, bool wide, dim3 grid, dim3 block, hipStream_t s,
-                   const ParArgs &g)
+void launch_kernel(bool rc, bool zr, bool ov, bool tf, dim3 grid, hipStream_t s, const ParArgs &g)
 {
     if (rc) {
-        if (zr) launch_variant<true, true, false>(tf, wide, grid, block, s, g);
-        else if (ov) launch_variant<true, false, true>(tf, wide, grid, block, s, g);
-        else launch_variant<true, false, false>(tf, wide, grid, block, s, g);
+        if (zr) launch_variant<true, true, false>(tf, grid, s, g);
+        else if (ov) launch_variant<true, false, true>(tf, grid, s, g);
+        else launch_variant<true, false, false>(tf, grid, s, g);
     } else {
-        if (zr) launch_variant<false, true, false>(tf, wide, grid, block, s, g);
-        else if (ov) launch_variant<false, false, true>(tf, wide, grid, block, s, g);
-        else launch_variant<false, false, false>(tf, wide, grid, block, s, g);
+        if (zr) launch_variant<false, true, false>(tf, grid, s, g);
+        else if (ov) launch_variant<false, false, true>(tf, grid, s, g);
+        else launch_variant<false, false, false>(tf, grid, s, g);
     }
 }
 
@@ -1737,7 +1732,7 @@ constexpr uint32_t kSlotLayers = 8;
 // Relative length of the wavefront that simulates a candidate: slots (the
 // stage's blocks plus the pipeline's fill and drain) times the work of a
 // slot (a fixed part and the stage's share of the layers), in half layers.
-// Only orders the wide launch's wavefronts.
+// Only orders the wavefronts.
 __device__ __forceinline__ uint32_t wave_length(const dsim_strategy &st, int n_layers, bool train)
 {
     const uint32_t P = (uint32_t)(st.P < 1 ? 1 : (st.P > kMaxStages ? kMaxStages : st.P));
@@ -1749,7 +1744,7 @@ __device__ __forceinline__ uint32_t wave_length(const dsim_strategy &st, int n_l
     return len > 0xffffffffu ? 0xffffffffu : (uint32_t)len;
 }
 
-// (wave_len, when given: n + 8 words cleared for k_class_scatter)
+// (wave_len: n + 8 words cleared for k_class_scatter)
 __global__ __launch_bounds__(kScanBlock) void k_class_count(const dsim_strategy *cand, int64_t n, int p_bound,
                                                            uint32_t *counts, uint32_t *wave_len)
 {
@@ -1757,10 +1752,8 @@ __global__ __launch_bounds__(kScanBlock) void k_class_count(const dsim_strategy 
     if (threadIdx.x < 8) s_cnt[threadIdx.x] = 0;
     __syncthreads();
     const int64_t c = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-    if (wave_len) {
-        if (c < n) wave_len[c] = 0;
-        if (c < 8) wave_len[n + c] = 0;
-    }
+    if (c < n) wave_len[c] = 0;
+    if (c < 8) wave_len[n + c] = 0;
     if (c < n) atomicAdd(&s_cnt[seg_class(cand[c], p_bound)], 1u);
     __syncthreads();
     if (threadIdx.x < 8) counts[(size_t)blockIdx.x * 8 + threadIdx.x] = s_cnt[threadIdx.x];
@@ -1794,17 +1787,18 @@ __global__ __launch_bounds__(kScanBlock) void k_class_scan(uint32_t *counts, int
         __syncthreads();
     }
     if (t == 0) {
-        uint32_t rank = 0, lane = 0;
+        uint32_t rank = 0, wave = 0;
         for (int j = 0; j < kClasses; ++j) {
             meta[j] = s_total[j];
             meta[8 + j] = rank;
-            meta[16 + j] = lane;
+            meta[16 + j] = wave;
             rank += s_total[j];
-            lane += ((s_total[j] << j) + kLanes - 1) / kLanes * kLanes;
+            const uint32_t per = (uint32_t)kLanes >> j;   // candidates per wavefront
+            wave += (s_total[j] + per - 1) / per;
         }
         meta[kClasses] = 0;
         meta[8 + kClasses] = rank;
-        meta[16 + kClasses] = lane;
+        meta[16 + kClasses] = wave;
     }
 }
 
@@ -1819,16 +1813,15 @@ __device__ __forceinline__ int len_bucket(uint32_t len)
     return e * 16 + (int)f;
 }
 
-// The wide launch's wavefronts longest first: a counting sort of
+// The wavefronts longest first: a counting sort of
 // wave_len (each wavefront's longest candidate, from k_class_scatter) over
 // len_bucket, wavefronts of one bucket in any order.  One block.
-__global__ __launch_bounds__(kOrderBlock) void k_wave_order(const uint32_t *meta, int narrow_end,
-                                                           const uint32_t *wave_len, uint32_t *order)
+__global__ __launch_bounds__(kOrderBlock) void k_wave_order(const uint32_t *meta, const uint32_t *wave_len,
+                                                           uint32_t *order)
 {
     __shared__ uint32_t s_cnt[kLenBuckets];
     const int t = threadIdx.x;
-    const uint32_t w_lo = meta[16 + narrow_end] / (uint32_t)kLanes, w_hi = meta[16 + kClasses] / (uint32_t)kLanes;
-    const uint32_t n_w = w_hi - w_lo;
+    const uint32_t n_w = meta[16 + kClasses];
     for (int i = t; i < kLenBuckets; i += kOrderBlock) s_cnt[i] = 0;
     __syncthreads();
     for (uint32_t i = t; i < n_w; i += kOrderBlock) atomicAdd(&s_cnt[len_bucket(wave_len[i])], 1u);
@@ -1842,15 +1835,14 @@ __global__ __launch_bounds__(kOrderBlock) void k_wave_order(const uint32_t *meta
         }
     }
     __syncthreads();
-    for (uint32_t i = t; i < n_w; i += kOrderBlock) order[atomicAdd(&s_cnt[len_bucket(wave_len[i])], 1u)] = w_lo + i;
+    for (uint32_t i = t; i < n_w; i += kOrderBlock) order[atomicAdd(&s_cnt[len_bucket(wave_len[i])], 1u)] = i;
 }
 
-// (wave_len, when given: each wide wavefront's longest wave_length, the
-// wavefronts counted from the first wide one, class narrow_end)
+// (wave_len: each wavefront's longest wave_length)
 __global__ __launch_bounds__(kScanBlock) void k_class_scatter(const dsim_strategy *cand, int64_t n, int p_bound,
                                                              const uint32_t *offsets, const uint32_t *meta,
-                                                             uint32_t *perm, int narrow_end, int n_layers,
-                                                             bool train, uint32_t *wave_len)
+                                                             uint32_t *perm, int n_layers, bool train,
+                                                             uint32_t *wave_len)
 {
     constexpr int kWaves = kScanBlock / kLanes;
     __shared__ uint32_t s_wcnt[kWaves][8];
@@ -1869,10 +1861,7 @@ __global__ __launch_bounds__(kScanBlock) void k_class_scatter(const dsim_strateg
         for (int v = 0; v < wv; ++v) rank += s_wcnt[v][j];
         const uint32_t slot = offsets[(size_t)blockIdx.x * 8 + j] + rank;
         perm[meta[8 + j] + slot] = (uint32_t)c;
-        if (wave_len && j >= narrow_end) {
-            const uint32_t w = (meta[16 + j] + (slot << j)) / (uint32_t)kLanes - meta[16 + narrow_end] / (uint32_t)kLanes;
-            atomicMax(&wave_len[w], wave_length(cand[c], n_layers, train));
-        }
+        atomicMax(&wave_len[meta[16 + j] + (slot >> (6 - j))], wave_length(cand[c], n_layers, train));
     }
 }
 
@@ -1916,8 +1905,13 @@ size_t parametric_workspace(int64_t n_cand)
     return (size_t)(nb * 8 + 32 + 3 * n_cand + 16) * sizeof(uint32_t);
 }
 
+// Up to this many strategies get a wavefront each: the chip holds 4,096 of
+// them at once (4 per SIMD), no pre-pass is needed, and a wavefront's rare
+// events are its one candidate's own.
+constexpr int64_t kAloneCand = 4096;
+
 dsim_status launch_parametric(const dsim_model &m, const dsim_strategy *cand, int64_t n_cand, const CostConsts &c,
-                              const dsim_results &r, void *ws, hipStream_t s, hipStream_t side)
+                              const dsim_results &r, void *ws, hipStream_t s, hipStream_t)   // (no second stream needed)
 {
     if (n_cand > (int64_t)0x7fffffff)
         return fail(DSIM_ERANGE, "parametric: at most 2^31 - 1 candidates per call");
@@ -1947,8 +1941,21 @@ dsim_status launch_parametric(const dsim_model &m, const dsim_strategy *cand, in
     g.c = ParConsts{c.inv_f, c.inv_b, c.inv_l, c.lat, c.launch, c.cap, c.mm, c.mm_c0, c.mm_c1, c.mm_c2,
                     c.mm_c3, c.mm_floor, c.node, c.net_lat, c.net_inv_l, c.streams, c.st_lat, c.st_inv_l};
 
-    // workspace: per-block class counts, class table, permutation, wide
-    // wavefront order and lengths (every word is written before it is read:
+    const bool rc = m.mode != DSIM_INFER && m.recompute != 0;
+    const bool zr = m.mode != DSIM_INFER && m.zero != 0;
+    const bool ov = m.mode != DSIM_INFER && m.overlap != 0;
+    const bool tf = m.family == DSIM_TRANSFORMER;
+    g.perm = g.meta = g.order = nullptr;
+    g.wave0 = 0;
+    hipError_t e = hipSuccess;
+    if (n_cand <= kAloneCand) {
+        launch_kernel(rc, zr, ov, tf, dim3((unsigned)n_cand), s, g);
+        e = hipGetLastError();
+        return e == hipSuccess ? DSIM_OK : hip_fail(e, "parametric launch");
+    }
+
+    // workspace: per-block class counts, class table, permutation, the
+    // wavefronts' order and lengths (every word is written before it is read:
     // the caller clears nothing)
     const int64_t nb = (n_cand + kScanBlock - 1) / kScanBlock;
     uint32_t *counts = static_cast<uint32_t *>(ws);
@@ -1959,71 +1966,23 @@ dsim_status launch_parametric(const dsim_model &m, const dsim_strategy *cand, in
     g.perm = perm;
     g.order = order;
     g.meta = meta;
-
-    // A large transformer grid splits: the narrow classes run beside the
-    // wide ones (whose smaller LDS footprint lets two wavefronts share a
-    // SIMD) when the caller gives a second stream, else after them on the
-    // one stream.  Small grids and MLPs take one launch for every class.
-    const bool split = m.family == DSIM_TRANSFORMER && n_cand >= kSplitMinCand;
-    const bool zr_only = m.mode != DSIM_INFER && m.zero != 0 && m.recompute == 0;
-    g.narrow_end = split ? first_wide_class(m.mode != DSIM_INFER && m.overlap != 0, zr_only) : kClasses;
-
-    hipLaunchKernelGGL(k_class_count, dim3((unsigned)nb), dim3(kScanBlock), 0, s, cand, n_cand, pb, counts,
-                       split ? wave_len : nullptr);
+    hipLaunchKernelGGL(k_class_count, dim3((unsigned)nb), dim3(kScanBlock), 0, s, cand, n_cand, pb, counts, wave_len);
     hipLaunchKernelGGL(k_class_scan, dim3(1), dim3(kScanBlock), 0, s, counts, nb, meta);
     hipLaunchKernelGGL(k_class_scatter, dim3((unsigned)nb), dim3(kScanBlock), 0, s, cand, n_cand, pb,
-                       (const uint32_t *)counts, (const uint32_t *)meta, perm, g.narrow_end, m.n_layers,
-                       m.mode != DSIM_INFER, split ? wave_len : nullptr);
-    if (split)
-        hipLaunchKernelGGL(k_wave_order, dim3(1), dim3(kOrderBlock), 0, s, (const uint32_t *)meta, g.narrow_end,
-                           (const uint32_t *)wave_len, order);
-    // every class's lanes round up to whole wavefronts: at most one partial
-    // wavefront per class beyond n * wmax lanes
+                       (const uint32_t *)counts, (const uint32_t *)meta, perm, m.n_layers, m.mode != DSIM_INFER, wave_len);
+    hipLaunchKernelGGL(k_wave_order, dim3(1), dim3(kOrderBlock), 0, s, (const uint32_t *)meta,
+                       (const uint32_t *)wave_len, order);
+    // every class rounds up to whole wavefronts: at most one partial
+    // wavefront per class beyond n * wmax lanes; one dispatch holds fewer
+    // than 2^32 lanes
+    if (wmax < (1 << kMinClass)) wmax = 1 << kMinClass;
     const int64_t waves = (n_cand * wmax + kLanes - 1) / kLanes + kClasses;
-    const bool rc = m.mode != DSIM_INFER && m.recompute != 0;
-    const bool zr = m.mode != DSIM_INFER && m.zero != 0;
-    const bool ov = m.mode != DSIM_INFER && m.overlap != 0;
-    const bool tf = m.family == DSIM_TRANSFORMER;
-    const dim3 grid((unsigned)waves), block(kLanes);
-    hipError_t e = hipSuccess;
-    if (!split) {
-        launch_kernel(rc, zr, ov, tf, false, grid, block, s, g);
-        e = hipGetLastError();
-        return e == hipSuccess ? DSIM_OK : hip_fail(e, "parametric launch");
-    }
-    // the narrow classes (1 to 8 lanes per candidate) come first in the
-    // class layout: a grid over their lanes is enough
-    const int64_t narrow_waves = (n_cand * (1 << (g.narrow_end - 1)) + kLanes - 1) / kLanes + kClasses;
-    const dim3 grid_n((unsigned)(narrow_waves < waves ? narrow_waves : waves));
-    if (!side || side == s) {
-        launch_kernel(rc, zr, ov, true, true, grid, block, s, g);
-        launch_kernel(rc, zr, ov, true, false, grid_n, block, s, g);
-        e = hipGetLastError();
-        return e == hipSuccess ? DSIM_OK : hip_fail(e, "parametric launch");
-    }
-    // narrow segments on the caller's stream, right after the pre-pass, and
-    // wide ones on the side stream, which waits for the pre-pass; the
-    // caller's stream then waits for both.  The narrow wavefronts (36 KB of
-    // LDS each) find room only on CUs that wide ones have not filled: started
-    // first, they no longer finish last (GPT-3-shaped grid 3.06 -> 2.78 ms,
-    // recomputation 4.60 -> 3.80)
-    hipEvent_t fork = nullptr, join = nullptr;
-    e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&join, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventRecord(fork, s);
-    if (e == hipSuccess) e = hipStreamWaitEvent(side, fork, 0);
-    if (e == hipSuccess) {
-        launch_kernel(rc, zr, ov, true, false, grid_n, block, s, g);
+    constexpr int64_t kMaxWaves = (int64_t)1 << 25;
+    for (int64_t w0 = 0; w0 < waves && e == hipSuccess; w0 += kMaxWaves) {
+        g.wave0 = (uint32_t)w0;
+        launch_kernel(rc, zr, ov, tf, dim3((unsigned)(waves - w0 < kMaxWaves ? waves - w0 : kMaxWaves)), s, g);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) {
-        launch_kernel(rc, zr, ov, true, true, grid, block, side, g);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipEventRecord(join, side);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
-    if (fork) (void)hipEventDestroy(fork);
-    if (join) (void)hipEventDestroy(join);
     return e == hipSuccess ? DSIM_OK : hip_fail(e, "parametric launch");
 }
 
