@@ -258,7 +258,7 @@ DSIM_API dsim_status dsim_create_grid(const dsim_model *model, const dsim_grid_s
  *   init_live: [n_cand * n_dev] bytes live at t = 0; NULL = zero.  A
  *          device's live bytes (init_live plus its allocations) must stay
  *          below 2^64; candidates starting at 2^62 or more on some device
- *          take a slower exact path (same results).
+ *          may take a slower path (same results).
  *   n_dev: 1..8.
  *   mm_k:  per record, the reduction length of a class-1 record (ignored
  *          on every other record); NULL = 0 for all.
@@ -309,9 +309,10 @@ typedef struct {
 
 /*
  * dsim_simulate_tables -- simulate n_cand explicit programs (Sec. 2.1, 3.3).
- * One GPU lane per candidate walks its ops in order.  n_cand <= 2^32 - 256
- * (DSIM_ERANGE beyond); above 2^28 - 1 candidates every op takes the
- * op-by-op path (same results, slower).
+ * One GPU lane per candidate walks its ops in order, or eight lanes (one per
+ * device) in calls of up to some ten thousand candidates.  n_cand <=
+ * 2^32 - 256 (DSIM_ERANGE beyond); above 2^28 - 1 candidates every op takes
+ * the general path (same results, slower).
  */
 DSIM_API dsim_status dsim_simulate_tables(const dsim_tables *tables, int64_t n_cand,
                                  const dsim_device_model *device,

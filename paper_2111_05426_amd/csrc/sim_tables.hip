@@ -28,14 +28,29 @@
 // over the banks (a 64-lane b128 read still takes several LDS cycles).
 //
 // The kernel runs close to the rate at which HBM returns its op records
-// (about 82 vector instructions per op keep the vector units partly busy
+// (a million 2,048-op programs 7.0 ms, 5.9 TB/s; about 84 vector instructions per op keep the vector units partly busy
 // beside that); it has a fast path for the ops every lane of a wavefront
 // has, which assumes valid compute, send and all-reduce ops of cost class 0
 // (indices clamped, so even an invalid op stays in bounds) and only tests
-// whether each op is one; a lane that meets an op it cannot vouch for (a
+// whether each op is one.  A lane that meets an op it cannot vouch for (a
 // free that would underflow, a broadcast or reduce record, a matrix
-// multiplication record), and every lane's ops past the wavefront's common
-// count, go through the exact per-op path below it.
+// multiplication record), every lane's ops past the wavefront's common count,
+// and every op when the device model has a MatMul regression, nodes or
+// streams take the general path below it: pipelined loads too, each op
+// decoded in full.  (One op at a time with its loads in turn, that path took
+// 1.1 us per op; now 0.65.  40,001 programs of 150 to 600 ops: 960 -> 317 us.)
+//
+// A call of few candidates cannot fill the chip with a lane each, and one
+// lane's chain through an op (LDS counters, an eight-device maximum, the
+// decoding) is long: there k_sim_tables_group gives each candidate eight
+// lanes, one per device, with clocks and counters in registers.  The eight
+// decode eight ops at a time, one each, and take them in turn.  (640 programs
+// of 256 ops 73 -> 36 us; 400 lowered GPT-2-shaped programs of up to 271
+// records, MatMul regression and nodes, 300 -> 39 us.)
+#include <limits.h>
+
+#include <type_traits>
+
 #include "internal.h"
 
 namespace dsim {
@@ -65,8 +80,32 @@ struct TabArgs {
     uint64_t *n_ops_out;
     uint64_t *walked;
     int32_t *status;
+    // device d's GPU and node, four bits each (nodes or streams)
+    uint32_t gpu_of, node_of;
     CostConsts c;
 };
+
+// Cost rows of the general path: compute, then per tier (links, network,
+// streams of one GPU) send, all-reduce over n devices and chain over n
+// devices.  An op costs base + coef * max(flops * g, bytes * w).
+struct CostRow {
+    double base, coef, w, g;
+};
+constexpr int kTierRows = 1 + 2 * (kMaxTableDev + 1);
+constexpr int kCostRows = 1 + 3 * kTierRows;
+__device__ __forceinline__ CostRow cost_row(const CostConsts &c, int i)
+{
+    if (i == 0) return CostRow{c.launch, 1.0, c.inv_b, c.inv_f};
+    const int tier = (i - 1) / kTierRows, k = (i - 1) % kTierRows;
+    const double lat = tier == 2 ? c.st_lat : (tier == 1 ? c.net_lat : c.lat);
+    const double w = tier == 2 ? c.st_inv_l : (tier == 1 ? c.net_inv_l : c.inv_l);
+    if (k == 0) return CostRow{lat, 1.0, w, 0.0};
+    const int n = (k - 1) % (kMaxTableDev + 1);
+    // over one device a collective costs nothing, whatever its bytes
+    if (n <= 1) return CostRow{0.0, 1.0, 0.0, 0.0};
+    if (k > kMaxTableDev + 1) return CostRow{(double)(n - 1) * lat, 1.0, w, 0.0};
+    return CostRow{tier == 2 ? c.ar_lat_st[n] : (tier == 1 ? c.ar_lat_net[n] : c.ar_lat[n]), c.ar_coef[n], w, 0.0};
+}
 
 // Buffer resource covering one workgroup's 64 consecutive 4-byte records of
 // one op row (raw buffer, gfx9 descriptor word 3); the base is wave-uniform,
@@ -123,23 +162,70 @@ __device__ __forceinline__ double bits_double(uint32_t lo, uint32_t hi)
     return __hiloint2double((int)hi, (int)lo);
 }
 
-// Status bits of one op, exactly as the table format defines validity.
+// One op decoded in full: the devices it synchronises, those that allocate
+// and those that free (bit masks; 0 for an op that is skipped), its cost and
+// its status bits, exactly as the table format defines validity.  on: the
+// candidate has the op.  The lanes' op kinds differ, so everything is bit
+// arithmetic on all-ones / all-zeros words, without branches.
+struct TabOp {
+    double cost;
+    uint32_t m, am, fm, flag;
+};
+__device__ __forceinline__ uint32_t ones(bool b) { return b ? ~0u : 0u; }
+
 template <int ND>
-__device__ __forceinline__ uint32_t op_flags(uint32_t code, uint32_t flops_bits, uint32_t bytes_bits)
+__device__ __forceinline__ TabOp decode(const TabArgs &a, const CostRow *rows, uint32_t code, uint32_t fl, uint32_t by,
+                                        uint32_t k, bool on)
 {
-    const uint32_t kind = code & 0xffu, ia = (code >> 8) & 0xffu, ib = (code >> 16) & 0xffu, cls = code >> 24;
+    TabOp o;
+    const uint32_t kind = code & 0xffu, ia = (code >> 8) & 0xffu, ib = (code >> 16) & 0xffu;
+    const uint32_t ma = 1u << (ia & 31u), mb = 1u << (ib & 31u);
+    const uint32_t k0 = ones(kind == 0u), k1 = ones(kind == 1u), k2 = ones(kind == 2u), k3 = ones(kind == 3u),
+                   k4 = ones(kind == 4u);
     // kind, cost class (1 only on compute records), and flops/bytes finite
     // and >= 0 (bit patterns below +inf)
-    if (cls > 1u || (cls == 1u && kind != 0u) || kind > 4u || flops_bits >= 0x7f800000u || bytes_bits >= 0x7f800000u)
-        return DSIM_ST_BAD_OP;
-    if (kind == 0u) return ia < (uint32_t)ND ? 0u : (uint32_t)DSIM_ST_BAD_DEVICE;
-    if (kind == 1u) {
-        if (ia >= (uint32_t)ND || ib >= (uint32_t)ND) return DSIM_ST_BAD_DEVICE;
-        return ia == ib ? (uint32_t)DSIM_ST_SELF_SEND : 0u;
+    const uint32_t bad_op = ~(k0 | k1 | k2 | k3 | k4) | ones((code >> 24) > (k0 & 1u)) | ones(max(fl, by) >= 0x7f800000u);
+    // devices below ND, a mask within them and not empty; the root of a
+    // broadcast or reduce is a member
+    const uint32_t a_out = ones(ia >= (uint32_t)ND), b_out = ones(ib >= (uint32_t)ND), mask_out = ones((ib >> ND) != 0u);
+    const uint32_t bad_dev = (~k2 & a_out) | (k1 & b_out) | (k2 & (mask_out | ones(ib == 0u))) |
+                             ((k3 | k4) & (mask_out | ones((ib & ma) == 0u)));
+    const uint32_t self = k1 & ones(ia == ib);
+    const uint32_t live = ones(on);
+    o.flag = live & ((bad_op & DSIM_ST_BAD_OP) | (~bad_op & ((bad_dev & DSIM_ST_BAD_DEVICE) | (~bad_dev & self & DSIM_ST_SELF_SEND))));
+    const uint32_t ok = live & ~(bad_op | bad_dev | self);   // an invalid op is skipped: no time, no memory
+    const uint32_t m = ok & (((k0 | k1) & ma) | (k1 & mb) | (~(k0 | k1) & ib));
+    o.m = m;
+    // compute allocates and frees on a; send allocates on b and frees on a;
+    // broadcast allocates on the members but a and frees on a; reduce
+    // allocates on a and frees on every member
+    o.am = ok & (((k0 | k4) & ma) | (k1 & mb) | (k3 & ib & ~ma));
+    o.fm = ok & (((k0 | k1 | k3) & ma) | (k4 & ib));
+    // the tier a communication op crosses: the streams of one GPU when all
+    // its devices lie on one GPU (GPUs hold consecutive devices, so its
+    // lowest and highest device decide), the network when its GPUs lie in
+    // more than one node, the node's links otherwise
+    uint32_t tier = 0;
+    if (a.c.node || a.c.streams) {
+        const int lo = 4 * ((__ffs(m) - 1) & 7), hi = 4 * ((31 - __clz(m)) & 7);
+        const uint32_t one_gpu = ones(((a.gpu_of >> lo) & 15u) == ((a.gpu_of >> hi) & 15u)) & ones(a.c.streams != 0);
+        const uint32_t nodes = ones(((a.node_of >> lo) & 15u) != ((a.node_of >> hi) & 15u)) & ones(a.c.node != 0);
+        tier = (one_gpu & 2u) | (~one_gpu & nodes & 1u);
     }
-    if (kind == 2u) return (ib == 0u || (ib >> ND) != 0u) ? (uint32_t)DSIM_ST_BAD_DEVICE : 0u;
-    // broadcast / reduce: the root is a member of the mask
-    return (ia >= (uint32_t)ND || (ib >> ND) != 0u || ((ib >> ia) & 1u) == 0u) ? (uint32_t)DSIM_ST_BAD_DEVICE : 0u;
+    const uint32_t n = (uint32_t)__popc(m);
+    const uint32_t r = ok & ~k0 & (1u + tier * (uint32_t)kTierRows + (k2 & (1u + n)) +
+                                   ((k3 | k4) & ((uint32_t)kMaxTableDev + 2u + n)));
+    const CostRow c = rows[r];
+    const double f = (double)__uint_as_float(fl), b = (double)__uint_as_float(by);
+    o.cost = c.base + c.coef * max_nn(f * c.g, b * c.w);
+    if (a.c.mm) {
+        // a matrix multiplication: the empirical regression of Sec. 4, with
+        // its reduction-length term and floor
+        const double lin = ((a.c.mm_c0 + a.c.mm_c1 * f) + a.c.mm_c2 * b) + a.c.mm_c3 * (double)k;
+        const double mm = a.c.mm_floor > lin ? a.c.mm_floor : lin;
+        o.cost = (code & 0xff0000ffu) == 1u << 24 ? mm : o.cost;
+    }
+    return o;
 }
 
 template <int ND>
@@ -152,12 +238,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWavesPe
     // (one array: the second pair sits at a fixed offset from the first, so
     // one address serves both loads)
     __shared__ double2 s_ct[2][ND + 3][kCopies];
-    __shared__ double2 s_cost[ND + 3];   // (base, coef) for the exact path
+    __shared__ CostRow s_row[kCostRows];   // the general path's costs
 
     const int tid = threadIdx.x;
-    if (tid <= ND) s_cost[tid] = make_double2(a.c.ar_lat[tid], a.c.ar_coef[tid]);
-    if (tid == ND + 1) s_cost[tid] = make_double2(a.c.launch, 1.0);
-    if (tid == ND + 2) s_cost[tid] = make_double2(a.c.lat, 1.0);
     for (int i = tid; i < (ND + 3) * kCopies; i += kBlock) {
         const int e = i / kCopies, k = i % kCopies;
         const bool cmp = e == ND + 1;
@@ -171,7 +254,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWavesPe
     const bool active = c < a.n_cand;
     // the fast path compares live bytes as fp64 bit patterns, which order
     // like the integers below 2^63 - 2^52: a lane starting at 2^62 or more
-    // live bytes on a device (its ops add less than 2^43) takes the exact path
+    // live bytes on a device (its ops add less than 2^43) takes the general path
     bool big_init = false;
 #pragma unroll
     for (int d = 0; d < ND; ++d) {
@@ -183,7 +266,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWavesPe
 
     uint32_t nops = active ? (a.n_ops ? a.n_ops[c] : (uint32_t)a.max_ops) : 0xffffffffu;
     // a lane whose op count exceeds max_ops is flagged and simulates max_ops
-    // ops; the flag survives the exact path's restart (st0)
+    // ops; the flag survives the general path's restart (st0)
     const int32_t st0 = (active && nops > (uint32_t)a.max_ops) ? DSIM_ST_BAD_OP : 0;
     int32_t st = st0;
     if (st0) nops = (uint32_t)a.max_ops;
@@ -196,19 +279,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWavesPe
 #pragma unroll
     for (int d = 0; d < ND; ++d) clk[d] = 0.0;
 
-    const double inv_f = a.c.inv_f, inv_b = a.c.inv_b, inv_l = a.c.inv_l;
-    const double lat = a.c.lat, launch = a.c.launch;
     const size_t N = (size_t)a.n_cand;
 
     // ---- fast path: the ops every lane of the wavefront has ------------------
     // Ops are assumed valid; a cheap test marks any lane that meets an op it
-    // cannot vouch for, and that lane is re-simulated by the exact path below.
+    // cannot vouch for, and that lane is re-simulated by the general path below.
     // Indices are clamped so that even an invalid op stays inside the arrays.
     // (with nodes or streams, communication costs depend on which devices an
-    // op spans: every op takes the exact path; so do tables of more than
-    // kMaxFastCand candidates, whose op rows are too far apart for the 32-bit
-    // offsets of the fast path's loads)
-    const int32_t fast_end = (a.c.node || a.c.streams || a.n_cand > kMaxFastCand)
+    // op spans, and a MatMul regression makes two costs of compute ops: every
+    // op takes the general path; so do tables of more than kMaxFastCand
+    // candidates, whose op rows are too far apart for the 32-bit offsets of
+    // the fast path's loads)
+    const int32_t fast_end = (a.c.mm || a.c.node || a.c.streams || a.n_cand > kMaxFastCand)
                                  ? 0
                                  : (int32_t)(__builtin_amdgcn_readfirstlane(wave_min) / kUnroll) * kUnroll;
 
@@ -350,11 +432,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWavesPe
 
     suspect |= fb_max >= 0x7f800000u;
 
-    // ---- exact path: this lane's remaining ops, or all of them again if the
-    // fast path met an op it could not vouch for -------------------------------
-    int32_t j = fast_end;
+    // ---- general path: this lane's remaining ops, or all of them again if
+    // the fast path met an op it could not vouch for ---------------------------
+    int32_t from = fast_end;
     if (suspect) {
-        j = 0;
+        from = 0;
         st = st0;
 #pragma unroll
         for (int d = 0; d < ND; ++d) {
@@ -364,97 +446,113 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWavesPe
             s_mem[d][tid] = make_ulonglong2(init, init);
         }
     }
-    for (; j < (int32_t)nops; ++j) {
-        const size_t o = (size_t)j * N + (size_t)c;
-        const uint32_t code = a.code[o];
-        const float flf = a.flops[o], byf = a.bytes[o];
-        const uint32_t flag = op_flags<ND>(code, __float_as_uint(flf), __float_as_uint(byf));
-        st |= (int32_t)flag;
-        if (flag) continue;   // an invalid op is skipped: no time, no memory
-        const uint32_t kind = code & 0xffu, ia = (code >> 8) & 0xffu, ib = (code >> 16) & 0xffu;
-        const uint32_t m = kind == 0u ? (1u << ia) : (kind == 1u ? ((1u << ia) | (1u << ib)) : ib);
-        const double f = (double)flf, b = (double)byf;
-        // the tier a communication op crosses: the streams of one GPU when
-        // all its devices lie on one GPU (GPUs hold consecutive devices, so
-        // its lowest and highest device decide), the network when its GPUs
-        // lie in more than one node, the node's links otherwise
-        int tier = 0;
-        if ((a.c.node || a.c.streams) && kind != 0u) {
-            const int lo = __ffs(m) - 1, hi = 31 - __clz(m);
-            const int S = a.c.streams ? a.c.streams : 1;
-            const int glo = lo / S, ghi = hi / S;
-            if (a.c.streams && glo == ghi) tier = 2;
-            else if (a.c.node && glo / a.c.node != ghi / a.c.node) tier = 1;
+    // the wavefront's range: from its earliest lane to its longest program
+    int32_t lo = 0, end = 0;
+    if (__ballot(from < (int32_t)nops) != 0) {
+        lo = from < (int32_t)nops ? from : INT_MAX;
+        end = from < (int32_t)nops ? (int32_t)nops : 0;
+        const uint64_t here = __ballot(true);   // (lanes past n_cand have left)
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const int32_t l2 = __shfl_xor(lo, off), e2 = __shfl_xor(end, off);
+            const bool there = ((here >> ((tid & 63) ^ off)) & 1) != 0;
+            lo = there && l2 < lo ? l2 : lo;
+            end = there && e2 > end ? e2 : end;
         }
-        const double c_lat = tier == 2 ? a.c.st_lat : (tier == 1 ? a.c.net_lat : lat);
-        const double c_inv_l = tier == 2 ? a.c.st_inv_l : (tier == 1 ? a.c.net_inv_l : inv_l);
-        double cost;
-        if (kind == 0u && (code >> 24) == 1u && a.c.mm) {
-            // a matrix multiplication: the empirical regression of Sec. 4,
-            // with its reduction-length term and floor
-            const double k = a.mm_k ? (double)a.mm_k[o] : 0.0;
-            const double lin = ((a.c.mm_c0 + a.c.mm_c1 * f) + a.c.mm_c2 * b) + a.c.mm_c3 * k;
-            cost = a.c.mm_floor > lin ? a.c.mm_floor : lin;
-        } else if (kind == 0u) {
-            const double tf = f * inv_f, tb = b * inv_b;
-            cost = launch + (tf > tb ? tf : tb);
-        } else if (kind == 1u) {
-            cost = c_lat + b * c_inv_l;
-        } else if (kind == 2u) {
-            // over one device it costs nothing (its byte term may overflow)
-            const double2 ar = s_cost[__popc(m)];
-            const int n = __popc(m);
-            cost = n > 1 ? (tier == 2 ? a.c.ar_lat_st[n] : (tier == 1 ? a.c.ar_lat_net[n] : ar.x)) + ar.y * (b * c_inv_l)
-                         : 0.0;
-        } else {
-            // broadcast / reduce: a chain of n - 1 hops (Fig. 9's Send for n = 2)
-            const int n = __popc(m);
-            cost = n > 1 ? (double)(n - 1) * c_lat + b * c_inv_l : 0.0;
+        lo = __builtin_amdgcn_readfirstlane(lo);
+        end = __builtin_amdgcn_readfirstlane(end);
+        // every wavefront that comes here writes the same rows
+        const int rank = __popcll(here & ((1ull << (tid & 63)) - 1ull)), lanes = __popcll(here);
+        for (int i = rank; i < kCostRows; i += lanes) s_row[i] = cost_row(a.c, i);
+        __builtin_amdgcn_wave_barrier();
+    }
+    const bool with_k = a.c.mm && a.mm_k;
+    const uint32_t *k_arr = with_k ? a.mm_k : a.code;   // (its values go unused then)
+    auto load_any = [&](int32_t j0, uint32_t(&cd)[kUnroll], uint32_t(&fl)[kUnroll], uint32_t(&by)[kUnroll],
+                        uint32_t(&al)[kUnroll], uint32_t(&fr)[kUnroll], uint32_t(&mk)[kUnroll]) {
+        // (rows past the tables' last one read it again, so that no load is
+        // conditional; scalar row bases, any n_cand)
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const size_t base = (size_t)min(j0 + u, a.max_ops - 1) * N + blk;
+            cd[u] = __builtin_nontemporal_load(a.code + base + tid);
+            fl[u] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(a.flops) + base + tid);
+            by[u] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(a.bytes) + base + tid);
+            al[u] = __builtin_nontemporal_load(a.alloc + base + tid);
+            fr[u] = __builtin_nontemporal_load(a.freeb + base + tid);
+            mk[u] = __builtin_nontemporal_load(k_arr + base + tid);
         }
-        double start = 0.0;
+    };
+    auto run_any = [&](int32_t j0, const uint32_t(&cd)[kUnroll], const uint32_t(&fl)[kUnroll],
+                       const uint32_t(&by)[kUnroll], const uint32_t(&al)[kUnroll], const uint32_t(&fr)[kUnroll],
+                       const uint32_t(&mk)[kUnroll]) {
+        // all ops decoded first (they do not depend on one another), then
+        // the clocks, then the counters
+        TabOp o[kUnroll];
+        bool many = false;
 #pragma unroll
-        for (int d = 0; d < ND; ++d)
-            if (((m >> d) & 1u) && clk[d] > start) start = clk[d];
-        const double end = start + cost;
+        for (int u = 0; u < kUnroll; ++u) {
+            const int32_t j = j0 + u;
+            o[u] = decode<ND>(a, s_row, cd[u], fl[u], by[u], with_k ? mk[u] : 0u, (j >= from) & (j < (int32_t)nops));
+            st |= (int32_t)o[u].flag;
+            many |= ((o[u].am & (o[u].am - 1u)) | (o[u].fm & (o[u].fm - 1u))) != 0u;
+        }
 #pragma unroll
-        for (int d = 0; d < ND; ++d)
-            if ((m >> d) & 1u) clk[d] = end;
-        if (kind >= 3u) {
-            // the receivers (broadcast) or the root (reduce) allocate, every
-            // member samples its peak, then the root (broadcast) or every
-            // member (reduce) frees
-            const uint64_t al = a.alloc[o], fr = a.freeb[o];
+        for (int u = 0; u < kUnroll; ++u) {
+            // the fast path's update (an op that is skipped has no members:
+            // every clock stays)
+            const uint32_t nm = ~o[u].m;
+            uint32_t xs[ND];
 #pragma unroll
-            for (int d = 0; d < ND; ++d) {
-                if (((m >> d) & 1u) == 0u) continue;
-                const bool gets = kind == 3u ? (uint32_t)d != ia : (uint32_t)d == ia;
-                const uint64_t lt = s_mem[d][tid].x + (gets ? al : 0u);
-                s_mem[d][tid].x = lt;
-                if (lt > s_mem[d][tid].y) s_mem[d][tid].y = lt;
+            for (int d = 0; d < ND; ++d) xs[d] = nm << (31 - d);
+            double v[ND];
+#pragma unroll
+            for (int d = 0; d < ND; ++d) v[d] = clk[d] = with_sign(clk[d], xs[d]);
+#pragma unroll
+            for (int w = 1; w < ND; w *= 2)
+#pragma unroll
+                for (int d = 0; d + w < ND; d += 2 * w) v[d] = max_nn(v[d], v[d + w]);
+            const double e = v[0] + o[u].cost;
+#pragma unroll
+            for (int d = 0; d < ND; ++d) clk[d] = max_abs(clk[d], with_sign(e, xs[d]));
+        }
+        // every allocation is sampled (a member that allocates nothing is at
+        // or below its peak already), then the frees
+        auto alloc_on = [&](int d, uint64_t by) {
+            ulonglong2 t = s_mem[d][tid];
+            t.x += by;
+            t.y = t.x > t.y ? t.x : t.y;
+            s_mem[d][tid] = t;
+        };
+        auto free_on = [&](int d, uint64_t by) {
+            const uint64_t lf = s_mem[d][tid].x;
+            st |= by > lf ? DSIM_ST_MEM_UNDERFLOW : 0;
+            s_mem[d][tid].x = by > lf ? 0 : lf - by;
+        };
+        if (__ballot(many) == 0) {
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                alloc_on(o[u].am ? __ffs(o[u].am) - 1 : 0, o[u].am ? al[u] : 0u);
+                free_on(o[u].fm ? __ffs(o[u].fm) - 1 : 0, o[u].fm ? fr[u] : 0u);
             }
+        } else {   // a broadcast or reduce record among the lanes
 #pragma unroll
-            for (int d = 0; d < ND; ++d) {
-                if (((m >> d) & 1u) == 0u || (kind == 3u && (uint32_t)d != ia)) continue;
-                const uint64_t lf = s_mem[d][tid].x;
-                if (fr > lf) {
-                    st |= DSIM_ST_MEM_UNDERFLOW;
-                    s_mem[d][tid].x = 0;
-                } else {
-                    s_mem[d][tid].x = lf - fr;
-                }
+            for (int u = 0; u < kUnroll; ++u) {
+                for (uint32_t q = o[u].am; q != 0u; q &= q - 1u) alloc_on(__ffs(q) - 1, al[u]);
+                for (uint32_t q = o[u].fm; q != 0u; q &= q - 1u) free_on(__ffs(q) - 1, fr[u]);
             }
-        } else if (kind != 2u) {
-            const uint32_t tdev = kind == 1u ? ib : ia;
-            const uint64_t lt = s_mem[tdev][tid].x + (uint64_t)a.alloc[o];
-            s_mem[tdev][tid].x = lt;
-            if (lt > s_mem[tdev][tid].y) s_mem[tdev][tid].y = lt;
-            const uint64_t lf = s_mem[ia][tid].x, fre = (uint64_t)a.freeb[o];
-            if (fre > lf) {
-                st |= DSIM_ST_MEM_UNDERFLOW;
-                s_mem[ia][tid].x = 0;
-            } else {
-                s_mem[ia][tid].x = lf - fre;
-            }
+        }
+    };
+    if (lo < end) {
+        uint32_t cd0[kUnroll], fl0[kUnroll], by0[kUnroll], al0[kUnroll], fr0[kUnroll], mk0[kUnroll];
+        uint32_t cd1[kUnroll], fl1[kUnroll], by1[kUnroll], al1[kUnroll], fr1[kUnroll], mk1[kUnroll];
+        load_any(lo, cd0, fl0, by0, al0, fr0, mk0);
+        for (int32_t j0 = lo; j0 < end; j0 += 2 * kUnroll) {
+            load_any(j0 + kUnroll, cd1, fl1, by1, al1, fr1, mk1);
+            run_any(j0, cd0, fl0, by0, al0, fr0, mk0);
+            if (j0 + kUnroll >= end) break;
+            load_any(j0 + 2 * kUnroll, cd0, fl0, by0, al0, fr0, mk0);
+            run_any(j0 + kUnroll, cd1, fl1, by1, al1, fr1, mk1);
         }
     }
 
@@ -486,9 +584,156 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWavesPe
     }
 }
 
+// max / or over the eight lanes of a candidate, in every one of them: lanes 1
+// and 2 apart, then the other half of the eight (mirrored)
+template <int CTRL> __device__ __forceinline__ uint32_t dpp8(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL> __device__ __forceinline__ uint64_t dpp8(uint64_t v)
+{
+    return ((uint64_t)dpp8<CTRL>((uint32_t)(v >> 32)) << 32) | dpp8<CTRL>((uint32_t)v);
+}
+template <int CTRL> __device__ __forceinline__ double dpp8(double v)
+{
+    return __longlong_as_double((long long)dpp8<CTRL>((uint64_t)__double_as_longlong(v)));
+}
+template <class T, class Op> __device__ __forceinline__ T over8(T v, Op op)
+{
+    v = op(v, dpp8<0xb1>(v));
+    v = op(v, dpp8<0x4e>(v));
+    return op(v, dpp8<0x141>(v));
+}
+// lane U's value of each eight: broadcast within each four lanes, then the
+// other four take it mirrored (vector moves; ds_swizzle does it in one, but
+// through the LDS pipe)
+template <int U> __device__ __forceinline__ uint32_t from8(uint32_t v)
+{
+    constexpr int q = U & 3;
+    const int t = __builtin_amdgcn_update_dpp(0, (int)v, q | (q << 2) | (q << 4) | (q << 6), 0xf, 0xf, true);
+    return (uint32_t)__builtin_amdgcn_update_dpp(t, t, 0x141, 0xf, U < 4 ? 0xa : 0x5, false);
+}
+
+constexpr int kGroup = 8;
+
+// One candidate per eight lanes, lane d its device d.  Each round the eight
+// lanes load and decode one op each (two rounds ahead in flight) and then
+// take the eight ops in order: the op's masks, cost and sizes from the lane
+// that decoded it, the start as a maximum over the lanes, clock and counters
+// in registers.
+template <int ND> __global__ __launch_bounds__(64) void k_sim_tables_group(const TabArgs a)
+{
+    __shared__ CostRow s_row[kCostRows];
+    const int lane = threadIdx.x, d = lane & (kGroup - 1);
+    if (lane < kCostRows) s_row[lane] = cost_row(a.c, lane);
+    __syncthreads();
+    const int64_t c = (int64_t)blockIdx.x * (64 / kGroup) + lane / kGroup;
+    const bool active = c < a.n_cand;
+    const size_t N = (size_t)a.n_cand;
+    uint32_t nops = active ? (a.n_ops ? a.n_ops[c] : (uint32_t)a.max_ops) : 0u;
+    uint32_t st = 0;
+    if (nops > (uint32_t)a.max_ops) {   // flagged, and max_ops ops are simulated
+        st = DSIM_ST_BAD_OP;
+        nops = (uint32_t)a.max_ops;
+    }
+    uint32_t end = nops;
+#pragma unroll
+    for (int off = 32; off >= kGroup; off >>= 1) end = max(end, (uint32_t)__shfl_xor((int)end, off));
+    end = (uint32_t)__builtin_amdgcn_readfirstlane((int)end);
+    const bool with_k = a.c.mm && a.mm_k;
+
+    double clk = 0.0;
+    uint64_t live = (active && d < ND && a.init_live) ? a.init_live[c * ND + d] : 0;
+    uint64_t peak = live;
+
+    struct Rec {
+        uint32_t cd, fl, by, al, fr, mk;
+    };
+    // (loads are unconditional: past the end they read the last row or
+    // candidate again, and decode ignores them)
+    const uint32_t *k_arr = with_k ? a.mm_k : a.code;
+    const size_t cl = active ? (size_t)c : N - 1;
+    auto load = [&](uint32_t j) {
+        const size_t o = (size_t)min(j, (uint32_t)a.max_ops - 1u) * N + cl;
+        return Rec{a.code[o], __float_as_uint(a.flops[o]), __float_as_uint(a.bytes[o]), a.alloc[o], a.freeb[o], k_arr[o]};
+    };
+    auto run = [&](uint32_t j0, const Rec &r) {
+        const TabOp o = decode<ND>(a, s_row, r.cd, r.fl, r.by, with_k ? r.mk : 0u, j0 + d < nops);
+        st |= o.flag;
+        const uint32_t masks = o.m | (o.am << 8) | (o.fm << 16);
+        const uint64_t cb = (uint64_t)__double_as_longlong(o.cost);
+        auto take = [&](auto u) {
+            constexpr int U = decltype(u)::value;
+            const uint32_t mm = from8<U>(masks);
+            const double cost = bits_double(from8<U>((uint32_t)cb), from8<U>((uint32_t)(cb >> 32)));
+            const uint32_t al = from8<U>(r.al), fr = from8<U>(r.fr);
+            const uint32_t me = mm >> d;
+            const bool in = (me & 1u) != 0u;
+            const double start = over8(in ? clk : 0.0, [](double x, double y) { return max_nn(x, y); });
+            const double e = start + cost;
+            clk = in ? e : clk;
+            live += (uint64_t)((me & 0x100u) ? al : 0u);
+            peak = live > peak ? live : peak;
+            const uint64_t f = (uint64_t)((me & 0x10000u) ? fr : 0u);
+            const bool under = f > live;
+            st |= under ? (uint32_t)DSIM_ST_MEM_UNDERFLOW : 0u;
+            live = under ? 0 : live - f;
+        };
+        take(std::integral_constant<int, 0>());
+        take(std::integral_constant<int, 1>());
+        take(std::integral_constant<int, 2>());
+        take(std::integral_constant<int, 3>());
+        take(std::integral_constant<int, 4>());
+        take(std::integral_constant<int, 5>());
+        take(std::integral_constant<int, 6>());
+        take(std::integral_constant<int, 7>());
+    };
+    // (each set is loaded again right after its use: copying a set whose
+    // loads are in flight would wait for them)
+    if (end > 0) {
+        Rec r0 = load(d), r1 = load(kGroup + d);
+        for (uint32_t j0 = 0; j0 < end; j0 += 2 * kGroup) {
+            run(j0, r0);
+            r0 = load(j0 + 2 * kGroup + d);
+            run(j0 + kGroup, r1);
+            r1 = load(j0 + 3 * kGroup + d);
+        }
+    }
+
+    const double mk = over8(clk, [](double x, double y) { return max_nn(x, y); });
+    const uint64_t cp = over8(peak, [](uint64_t x, uint64_t y) { return x > y ? x : y; });
+    st = over8(st, [](uint32_t x, uint32_t y) { return x | y; });
+    if (!active) return;
+    if (d == 0) {
+        if (a.c.cap != 0 && cp > a.c.cap) st |= DSIM_ST_OVER_CAP;
+        a.makespan[c] = mk;
+        a.cand_peak[c] = cp;
+        a.status[c] = (int32_t)st;
+        if (a.n_ops_out) a.n_ops_out[c] = nops;
+        if (a.walked) a.walked[c] = nops;
+    }
+    if (a.finish)
+        for (int i = d; i < a.row_width; i += kGroup) a.finish[(size_t)c * a.row_width + i] = i < ND ? clk : 0.0;
+    if (a.peak)
+        for (int i = d; i < a.row_width; i += kGroup) a.peak[(size_t)c * a.row_width + i] = i < ND ? peak : 0;
+}
+
+// Calls of at most this many candidates take eight lanes each.  256 random
+// ops over 8 devices, eight lanes against one: 36 / 76 us at 640 candidates,
+// 37 / 86 at 8,192 (one wavefront per SIMD), 59 / 88 at 16,384, 124 / 89 at
+// 32,768; where every op takes the general path 39 / 175, 39 / 172, 62 / 173,
+// 121 / 173, and 224 / 176 at 65,536.
+constexpr int64_t kGroupCand = 20480, kGroupCandGeneral = 45056;
+
 template <int ND>
 hipError_t launch_nd(const TabArgs &a, hipStream_t s)
 {
+    const bool general = a.c.mm || a.c.node || a.c.streams;
+    if (a.n_cand <= (general ? kGroupCandGeneral : kGroupCand)) {
+        const int64_t blocks = (a.n_cand * kGroup + 63) / 64;
+        hipLaunchKernelGGL(k_sim_tables_group<ND>, dim3((unsigned)blocks), dim3(64), 0, s, a);
+        return hipGetLastError();
+    }
     const int64_t blocks = (a.n_cand + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_sim_tables<ND>, dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
     return hipGetLastError();
@@ -520,6 +765,12 @@ dsim_status launch_sim_tables(const dsim_tables &t, int64_t n_cand, const CostCo
     a.walked = r.walked_ops;
     a.status = r.status;
     a.c = c;
+    a.gpu_of = a.node_of = 0;
+    for (int d = 0; d < kMaxTableDev; ++d) {
+        const uint32_t gpu = (uint32_t)(c.streams ? d / c.streams : d);
+        a.gpu_of |= gpu << (4 * d);
+        a.node_of |= (c.node ? gpu / (uint32_t)c.node : 0u) << (4 * d);
+    }
     hipError_t e;
     switch (t.n_dev) {
     case 1: e = launch_nd<1>(a, s); break;

@@ -405,3 +405,42 @@ def test_empty_inputs(torch_gpu):
     dsim.dsim_simulate_tables(g, 5, 8, DeviceSpec(), r)
     torch.cuda.synchronize()
     assert np.all(r["makespan"].cpu().numpy() == 0) and np.all(r["status"].cpu().numpy() == 0)
+
+
+@pytest.mark.parametrize("kinds", ["plain", "bcast_reduce", "matmul", "network", "streams"])
+@pytest.mark.parametrize("n_dev", [1, 3, 8])
+def test_eight_lanes_and_one_lane_per_candidate(torch_gpu, n_dev, kinds):
+    """Small calls take eight lanes per candidate (compared with the oracle
+    above), larger ones one: the same programs repeated past either bound
+    (20,480 candidates, 45,056 where the device model has a MatMul regression,
+    nodes or streams) give the same results, ragged lengths (0 ops, and counts
+    above max_ops), invalid ops, underflows and resident bytes of 2^62 and
+    more included."""
+    from paper_2111_05426_amd import dsim
+    from paper_2111_05426_amd.workloads import DeviceSpec
+    torch = torch_gpu
+    rng = np.random.default_rng(4000 + n_dev)
+    n, max_ops = 263, 75
+    t = random_tables(rng, n, max_ops, n_dev, True, kinds != "plain" and kinds != "matmul", kinds == "matmul")
+    t["n_ops"][5:9] = [max_ops + 1, 2 ** 31, 3, max_ops]
+    t["init"][11, 0] = 2 ** 62 + 12345
+    dev = DeviceSpec(mem_cap_bytes=2 * 10 ** 5,
+                     matmul=(4.5e-6, 9.1e-15, 1.3e-12, 3.7e-14, 4.0e-5) if kinds == "matmul" else None,
+                     network=(2, 3.3e9, 2.1e-5) if kinds == "network" else None,
+                     streams=(2, 4.4e11, 1.3e-6) if kinds == "streams" else None)
+
+    def run(total):
+        at = np.arange(total) % n
+        g = to_gpu(torch, {k: np.ascontiguousarray(v[..., at]) for k, v in t.items() if k != "init"})
+        init = torch.from_numpy(np.ascontiguousarray(t["init"][at]).view(np.int64)).cuda()
+        r = dsim.alloc_results(total, n_dev + 1)
+        dsim.dsim_simulate_tables(g, total, n_dev, dev, r, init_live=init)
+        torch.cuda.synchronize()
+        return results_np(r), at
+
+    small, _ = run(n)
+    assert np.any(small["status"] != 0) and np.any(small["status"] == 0)
+    for total in (20480, 20481, 45057):
+        big, at = run(total)
+        for k in small:
+            assert np.array_equal(big[k], small[k][at]), (total, k)
