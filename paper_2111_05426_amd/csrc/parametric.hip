@@ -937,7 +937,14 @@ __device__ __forceinline__ int repeats(bool pair, bool bwd, int nf, int nb, int 
 // (units_exact), else layer by layer: below it the dependent adds cost less
 // than the binade arithmetic
 constexpr int kFastUnits = 12;
-constexpr int kKeys = 6;    // forward: 2 row classes; backward: 2 row classes x accumulation
+// kinds of blocks: forward of a short and of a long microbatch; backward of
+// microbatch 0 (no accumulation), of a short and of a long other one
+constexpr int kKeys = 5;
+__device__ __forceinline__ bool key_bwd(int key) { return key >= 2; }
+__device__ __forceinline__ bool key_acc(int key) { return key >= 3; }
+// the long microbatches (one row more) come first: microbatch 0 is one if
+// there is any
+__device__ __forceinline__ int key_long(int key, bool any) { return key == 2 ? (any ? 1 : 0) : (key >= 3 ? key - 3 : key); }
 constexpr int kRoles = 4;   // stage 0; a middle stage of q + 1 or of q layers; the last stage (P > 1)
 // binade tables are built for clocks of at least this biased exponent (below,
 // a cost over the ulp could overflow) and below that of infinity
@@ -976,15 +983,15 @@ template <int NF, int NB> __device__ __forceinline__ double walk(const double *a
 // stage's first unit costs what its others do).
 template <bool TF, bool ZR, bool OV> struct Prog {
     using Sh = Shape<TF, ZR>;
-    double2 uf[2][Sh::F_U2], ub[4][Sh::U2];
-    double2 pf[2][Sh::F_PRE2 > 0 ? Sh::F_PRE2 : 1], pb[4][Sh::PRE2];
-    double2 sf[2][Sh::F_SUF2], sb[4][Sh::SUF2];
+    double2 uf[2][Sh::F_U2], ub[3][Sh::U2];
+    double2 pf[2][Sh::F_PRE2 > 0 ? Sh::F_PRE2 : 1], pb[3][Sh::PRE2];
+    double2 sf[2][Sh::F_SUF2], sb[3][Sh::SUF2];
     double2 wu[5];                        // weight update: a layer's parameters, [4] the embedding / head
     int64_t mem[kKeys][kRoles][2];        // a block's net bytes, highest point above its start
     int64_t blk[2][kKeys][kRoles];        // a block's whole ulps in the binade held for each exponent parity, or kWalk
     double2 unit_ulps[2][kKeys];          // one unit's, and their reciprocal; negative: walk it
     int nu[2][kRoles], nrep[kRoles];      // units walked [backward], replayed
-    int npart, single;                    // entries of the replay's partial unit; P == 1
+    int npart, single, any_long;          // entries of the replay's partial unit; P == 1; uneven microbatches
     typename std::conditional<OV, OvUnit<TF>, int>::type ov;   // the last backward block's unit
     Mark mark[OV ? 2 : 1];                // and its hand-overs in pre and suf (transformer)
 
@@ -1039,17 +1046,17 @@ __device__ void block_mem(const Ctx &x, int s, bool bwd, uint64_t m, bool acc, i
     }
 }
 
-// Records one of a candidate's programs: jobs 0-5 a unit, 6-11 a kind's
-// edges, 12 the weight update's parameters, 13 an overlapped last backward
+// Records one of a candidate's programs: jobs 0-4 a unit, 5-9 a kind's
+// edges, 10 the weight update's parameters, 11 an overlapped last backward
 // block.
-constexpr int kJobs = 14;
+constexpr int kJobs = 2 * kKeys + 2;
 template <bool TF, bool ZR, bool OV>
 __device__ __forceinline__ void record_job(const Ctx &x, Prog<TF, ZR, OV> &q, int job)
 {
     using Pr = Prog<TF, ZR, OV>;
     const int key = job < kKeys ? job : job - kKeys;
-    const bool bwd = key >= 2, acc = key >= 4;
-    const uint64_t m = x.mq + (uint64_t)(key & 1);
+    const bool bwd = key_bwd(key), acc = key_acc(key);
+    const uint64_t m = x.mq + (uint64_t)key_long(key, x.mr > 0);
     if (job < kKeys) {
         Record r{x, const_cast<double *>(q.unit(key)), 0};
         record_unit<TF>(x, bwd, m, acc, r);
@@ -1071,7 +1078,7 @@ __device__ __forceinline__ void record_job(const Ctx &x, Prog<TF, ZR, OV> &q, in
         }
         p.pad(Pr::n_pre(bwd));
         f.pad(Pr::n_suf(bwd));
-    } else if (job == 12) {
+    } else if (job == 2 * kKeys) {
         // (collective or hand-back, optimizer) of each parameter
         auto param = [&](uint64_t N) {
             uint64_t fl, by;
@@ -1230,7 +1237,8 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
         for (int job = s; job < kKeys * kRoles; job += W) {
             const int key = job / kRoles, ss = role_stage(x, job % kRoles);
             int64_t d = 0, t = 0;
-            if (ss >= 0) block_mem<TF, RC>(x, ss, key >= 2, x.mq + (uint64_t)(key & 1), key >= 4, d, t);
+            if (ss >= 0)
+                block_mem<TF, RC>(x, ss, key_bwd(key), x.mq + (uint64_t)key_long(key, x.mr > 0), key_acc(key), d, t);
             q.mem[key][job % kRoles][0] = d;
             q.mem[key][job % kRoles][1] = t;
         }
@@ -1245,6 +1253,7 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
                 if (RC) record_partial<TF>(x, 1, n);
                 q.npart = (int)n.walked;
                 q.single = P == 1;
+                q.any_long = x.mr > 0;
             }
         }
         if (live_stage) {
@@ -1255,8 +1264,8 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
                 res0 = resident_inputs(x, s) + zs.rmax;
 #pragma unroll 1
                 for (int key = 0; key < kKeys; ++key) {
-                    const bool bwd = key >= 2;
-                    s_ztop[key][lane] = zero_top<TF>(x, s, zs, bwd, x.mq + (uint64_t)(key & 1), key >= 4,
+                    const bool bwd = key_bwd(key);
+                    s_ztop[key][lane] = zero_top<TF>(x, s, zs, bwd, x.mq + (uint64_t)key_long(key, x.mr > 0), key_acc(key),
                                                      block_units(x, s, bwd, TF),
                                                      TF ? stage_nl(x, s) - 1 : stage_nl(x, s) / (x.H > 1 ? 2 : 1) - 1);
                 }
@@ -1312,7 +1321,7 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
         Pr &q = L[sg];
         const double sc = ldexp(1.0, 1075 - e);   // 1 / ulp
         const int key = lane >> 3, part = lane & 7;
-        const bool bwd = key >= 2;
+        const bool bwd = key_bwd(key);
         double u = 0.0, p = 0.0, f = 0.0, up = 0.0;
         bool tie = false;
         // entry j = part, part + 8, ... of n (at most 8 * MAX); *head: the
@@ -1350,9 +1359,10 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
         if (RC) {
             // backward blocks replay the forward units of their row class
             up = sum8(up);
-            rep = __shfl(u, 8 * (key & 1), kLanes);
-            repp = __shfl(up, 8 * (key & 1), kLanes);
-            bad = bad || (bwd && ((ties >> (8 * (key & 1))) & 0xff) != 0);
+            const int fwd = 8 * (key_long(key, q.any_long != 0) & 1);   // (lanes past the keys: any lane)
+            rep = __shfl(u, fwd, kLanes);
+            repp = __shfl(up, fwd, kLanes);
+            bad = bad || (bwd && ((ties >> fwd) & 0xff) != 0);
         }
         // (whole numbers: exact below 2^53; a block of 2^52 ulps or more
         // leaves the binade anyway)
@@ -1410,7 +1420,7 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
                 // some lane's unit is a backward one)
                 const double *a = prog.unit(key);
                 clk = walk<Pr::Sh::F_U2, Pr::Sh::F_U2>(a, false, clk);
-                if (key >= 2) {
+                if (key_bwd(key)) {
                     constexpr int kRest = Pr::Sh::U2 - Pr::Sh::F_U2;
                     clk = walk<kRest, kRest>(a + 2 * Pr::Sh::F_U2, false, clk);
                 }
@@ -1479,7 +1489,7 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
         const uint64_t bwd_mask = ballot(ready && bwd);
         const bool mc = k < mr;
         const uint64_t mc_mask = ballot(mc);
-        const int key = (mc ? 1 : 0) + (bwd ? (nb > 0 ? 4 : 2) : 0);
+        const int key = bwd ? (nb > 0 ? (mc ? 4 : 3) : 2) : (mc ? 1 : 0);
 
         // ---- the blocks
         const int ex = exponent(clk);
@@ -1693,8 +1703,11 @@ __device__ __forceinline__ void parametric_body(const ParArgs &g)
     }
 }
 
+// (three wavefronts per SIMD for the ZeRO kernels, at the price of 19
+// registers spilled in their set-up, whose per-block maxima over the replicas
+// otherwise take 187 and leave two: GPT-3-shaped ZeRO grid 1.83 -> 1.41 ms)
 template <bool TF, bool RC, bool ZR, bool OV>
-__global__ __launch_bounds__(kLanes) void k_parametric(const ParArgs g)
+__global__ __launch_bounds__(kLanes) __attribute__((amdgpu_waves_per_eu(ZR ? 3 : 1))) void k_parametric(const ParArgs g)
 {
     parametric_body<TF, RC, ZR, OV>(g);
 }
@@ -1732,7 +1745,9 @@ constexpr uint32_t kSlotLayers = 8;
 // Relative length of the wavefront that simulates a candidate: slots (the
 // stage's blocks plus the pipeline's fill and drain) times the work of a
 // slot (a fixed part and the stage's share of the layers), in half layers.
-// Only orders the wavefronts.
+// Only orders the wavefronts.  (An estimate of the slots left after whole
+// periods are skipped, weighted by the class, ran the two-stream and ZeRO
+// grids 1 to 10% slower and GPipe 4% faster.)
 __device__ __forceinline__ uint32_t wave_length(const dsim_strategy &st, int n_layers, bool train)
 {
     const uint32_t P = (uint32_t)(st.P < 1 ? 1 : (st.P > kMaxStages ? kMaxStages : st.P));
