@@ -4,15 +4,24 @@
 // memory cap (or whose status is non-zero), rank the rest by predicted time
 // (makespan ascending, ties to the lower index), keep the first k.
 //
-// Two passes.  Pass 1: block b owns a contiguous chunk and extracts its k
-// smallest (makespan, index) keys in order, round r selecting the smallest
-// key strictly greater than round r-1's with a block-wide min reduction
-// (the chunk is re-read per round; k <= 64 and chunks are small, so the
-// passes stay within L2; chunks shrink to 256 keys while fewer than 256
-// blocks would run).  Pass 2: one block merges the blocks' ascending
-// k-lists, round r taking the least of the lists' heads.  The order is a
-// total order on (makespan, index), so the result does not depend on the
-// launch shape.
+// Small sets are ranked by counting: with all keys in LDS, a key's place is
+// the number of smaller ones, which takes one pass of broadcast reads and no
+// rounds.  Calls of at most 1,024 keys are one block of that.  Larger ones
+// take two passes.  Pass 1: block b owns a contiguous chunk and writes its k
+// smallest (makespan, index) keys in order; chunks have 256 keys (ranked by
+// counting) while fewer than 256 blocks would run, and at most 512 blocks
+// run; in larger chunks each wavefront takes its least remaining key round by
+// round, the winning lane then looking for its next one, and the block's four
+// lists are merged by rank.  Pass 2: one block bounds the k-th smallest key
+// -- by the k-th smallest of the lists' heads and by the least of the lists'
+// k-th keys -- gathers the keys up to the bound (at most k from k lists) and
+// ranks them by counting.  The order is a total order on (makespan, index),
+// so the result does not depend on the launch shape.
+//
+// (With a block-wide minimum and a new scan of the chunk in each of k rounds,
+// and a merge of k rounds over the lists' heads: top-16 of 39,965 keys 21 +
+// 27 us, top-8 of 40,001 11 + 14, top-1 of a million 8.6 + 4.8, of 400 4.7 +
+// 4.6; now 10 + 14, 9 + 10, 7.9 + 4.9, and 3.9 in one.)
 #include "internal.h"
 
 #include <math.h>
@@ -21,143 +30,326 @@ namespace dsim {
 namespace {
 
 constexpr int kSelBlock = 256;
+constexpr int kSelWaves = kSelBlock / 64;
+constexpr int kMergeBlock = 1024;
+constexpr int kMergeWaves = kMergeBlock / 64;
+constexpr int kMaxK = 64;
 constexpr int64_t kChunk = 4096;
 constexpr int64_t kMinChunk = 256;
-constexpr int kMaxBlocks = 2048;
+constexpr int kMaxBlocks = 512;
 constexpr int kFillBlocks = 256;   // one chunk per CU at least, while chunks stay >= kMinChunk
+constexpr int64_t kOneBlock = kMergeBlock;   // keys of a call without a second pass
 
 struct Key {
     double mk;
     int64_t idx;
 };
 
+constexpr int64_t kNone = INT64_MAX;
+
 __device__ __forceinline__ bool key_less(double am, int64_t ai, double bm, int64_t bi)
 {
     return am < bm || (am == bm && ai < bi);
 }
 
-// block-wide argmin of (m, i); returns the winner in every thread: a
-// butterfly over each wavefront's lanes, then the wavefronts' winners
-__device__ Key block_min(double m, int64_t i, double *s_m, int64_t *s_i)
+template <int CTRL, int ROWS> __device__ __forceinline__ double min_dpp(double v)
 {
-    constexpr int kWaves = kSelBlock / 64;
-    for (int o = 32; o > 0; o >>= 1) {
-        const double om = __shfl_xor(m, o, 64);
-        const int64_t oi = __shfl_xor(i, o, 64);
-        if (key_less(om, oi, m, i)) {
-            m = om;
-            i = oi;
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    // (lanes without a source keep their own value)
+    const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return fmin(v, __hiloint2double(hi, lo));
+}
+
+// The least key of the wavefront: its lane (keys are not NaN; lanes without a
+// key hold (+inf, kNone)).
+__device__ __forceinline__ int wave_least(double m, int64_t i)
+{
+    double v = m;
+    v = min_dpp<0x111, 0xf>(v);
+    v = min_dpp<0x112, 0xf>(v);
+    v = min_dpp<0x114, 0xf>(v);
+    v = min_dpp<0x118, 0xf>(v);
+    v = min_dpp<0x142, 0xa>(v);
+    v = min_dpp<0x143, 0xc>(v);
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63), hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+    const double least = __hiloint2double(hi, lo);
+    uint64_t at = __builtin_amdgcn_ballot_w64(m == least);
+    if ((at & (at - 1)) != 0) {   // equal makespans: the lowest index
+        int64_t b = m == least ? i : kNone;
+        for (int o = 32; o > 0; o >>= 1) {
+            const int64_t x = __shfl_xor(b, o, 64);
+            b = x < b ? x : b;
         }
+        at = __builtin_amdgcn_ballot_w64(m == least && i == b);
     }
-    if ((threadIdx.x & 63) == 0) {
-        s_m[threadIdx.x / 64] = m;
-        s_i[threadIdx.x / 64] = i;
+    return __builtin_ctzll(at);
+}
+
+__device__ __forceinline__ double from_lane(double v, int l)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ __forceinline__ int64_t from_lane(int64_t v, int l)
+{
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
+                     (uint32_t)__builtin_amdgcn_readlane((int)v, l));
+}
+
+// Merge of W ascending lists of k keys by rank: thread t's key and its place
+// among all of them (-1: no key).  n: keys there are in all.
+template <int W> __device__ __forceinline__ int rank_of(const double (&m)[W][kMaxK], const int64_t (&i)[W][kMaxK], int k,
+                                                        int t, Key &key, int &n)
+{
+    n = 0;
+    int place = -1;
+    const int a = t / k, r = t % k;
+    const bool has = t < W * k && i[a < W ? a : 0][r] != kNone;
+    if (has) {
+        key = Key{m[a][r], i[a][r]};
+        place = r;
+    }
+    for (int b = 0; b < W; ++b) {
+        // keys of list b below this one, and in all
+        int lo = 0, hi = k, all = 0, end = k;
+        while (lo < hi || all < end) {
+            if (lo < hi) {
+                const int mid = (lo + hi) / 2;
+                if (has && key_less(m[b][mid], i[b][mid], key.mk, key.idx)) lo = mid + 1;
+                else hi = mid;
+            }
+            if (all < end) {
+                const int mid = (all + end) / 2;
+                if (i[b][mid] != kNone) all = mid + 1;
+                else end = mid;
+            }
+        }
+        if (has && b != a) place += lo;
+        n += all;
+    }
+    return place;
+}
+
+// The feasible makespan of entry i, NaN for an infeasible one (NaN compares
+// false with everything, so it is never counted).
+__device__ __forceinline__ double feasible(const double *mk, const uint64_t *pk, const int32_t *st, uint64_t cap,
+                                           int64_t i)
+{
+    const bool ok = st[i] == 0 && (cap == 0 || pk[i] <= cap);
+    return ok ? mk[i] : __longlong_as_double(-1);
+}
+
+// how many of the n keys (m[j], j) are less than (v, t)
+__device__ __forceinline__ int count_less(const double *m, int n, double v, int t)
+{
+    int less = 0;
+#pragma unroll 8
+    for (int j = 0; j < n; ++j) less += (m[j] < v) | ((m[j] == v) & (j < t)) ? 1 : 0;
+    return less;
+}
+
+// The least (m, i) of a block of W wavefronts, in its thread 0's return value.
+template <int W> __device__ __forceinline__ Key block_least(double m, int64_t i, double *s_m, int64_t *s_i)
+{
+    const int t = threadIdx.x;
+    const int l = wave_least(m, i);
+    const double wm = from_lane(m, l);
+    const int64_t wi = from_lane(i, l);
+    if ((t & 63) == 0) {
+        s_m[t / 64] = wm;
+        s_i[t / 64] = wi;
     }
     __syncthreads();
     Key k{s_m[0], s_i[0]};
-    for (int v = 1; v < kWaves; ++v)
+    for (int v = 1; v < W; ++v)
         if (key_less(s_m[v], s_i[v], k.mk, k.idx)) k = Key{s_m[v], s_i[v]};
-    __syncthreads();
     return k;
 }
 
-constexpr int64_t kNone = INT64_MAX;
+// at most 1,024 keys
+__global__ __launch_bounds__(kMergeBlock) void k_select_one(const double *mk, const uint64_t *pk, const int32_t *st,
+                                                            int n, uint64_t cap, int k, int64_t *out_idx,
+                                                            double *out_mk, int32_t *out_found)
+{
+    __shared__ double s_m[kMergeBlock];
+    __shared__ int64_t s_i[kMergeWaves];
+    __shared__ int s_n;
+    const int t = threadIdx.x;
+    const double v = t < n ? feasible(mk, pk, st, cap, t) : __longlong_as_double(-1);
+    const bool has = v == v;
+    if (k == 1) {
+        const Key b = block_least<kMergeWaves>(has ? v : HUGE_VAL, has ? t : kNone, s_m, s_i);
+        if (t == 0) {
+            out_idx[0] = b.idx == kNone ? -1 : b.idx;
+            out_mk[0] = b.mk;
+            *out_found = b.idx == kNone ? 0 : 1;
+        }
+        return;
+    }
+    if (t == 0) s_n = 0;
+    s_m[t] = v;
+    __syncthreads();
+    if (has) {
+        const int r = count_less(s_m, n, v, t);
+        if (r < k) {
+            out_idx[r] = t;
+            out_mk[r] = v;
+        }
+    }
+    const int mine = __popcll(__builtin_amdgcn_ballot_w64(has));
+    if ((t & 63) == 0) atomicAdd(&s_n, mine);
+    __syncthreads();
+    const int found = s_n < k ? s_n : k;
+    if (t >= found && t < k) {
+        out_idx[t] = -1;
+        out_mk[t] = HUGE_VAL;
+    }
+    if (t == 0) *out_found = found;
+}
 
 __global__ __launch_bounds__(kSelBlock) void k_select_chunks(const double *mk, const uint64_t *pk,
                                                              const int32_t *st, int64_t n, uint64_t cap,
                                                              int k, int64_t chunk, Key *ws)
 {
-    __shared__ double s_m[kSelBlock];
-    __shared__ int64_t s_i[kSelBlock];
+    __shared__ double s_m[kSelWaves][kMaxK];
+    __shared__ int64_t s_i[kSelWaves][kMaxK];
+    const int t = threadIdx.x, wave = t / 64, lane = t % 64;
     const int64_t lo = (int64_t)blockIdx.x * chunk;
     const int64_t hi = lo + chunk < n ? lo + chunk : n;
-    double pm = -HUGE_VAL;
-    int64_t pi = -1;
-    for (int r = 0; r < k; ++r) {
-        double bm = HUGE_VAL;
-        int64_t bi = kNone;
-        for (int64_t i = lo + threadIdx.x; i < hi; i += kSelBlock) {
-            if (st[i] != 0) continue;
-            if (cap != 0 && pk[i] > cap) continue;
-            const double m = mk[i];
-            if (!key_less(pm, pi, m, i)) continue;
-            if (key_less(m, i, bm, bi)) {
+    Key *list = ws + (int64_t)blockIdx.x * k;
+    // this thread's least key above (pm, pi)
+    auto next = [&](double pm, int64_t pi, double &bm, int64_t &bi) {
+        bm = HUGE_VAL;
+        bi = kNone;
+        for (int64_t i = lo + t; i < hi; i += kSelBlock) {
+            const double m = feasible(mk, pk, st, cap, i);
+            if (key_less(pm, pi, m, i) && key_less(m, i, bm, bi)) {
                 bm = m;
                 bi = i;
             }
         }
-        const Key best = block_min(bm, bi, s_m, s_i);
-        if (threadIdx.x == 0) {
-            ws[(int64_t)blockIdx.x * k + r].mk = best.mk;
-            ws[(int64_t)blockIdx.x * k + r].idx = best.idx == kNone ? -1 : best.idx;
+    };
+    double bm;
+    int64_t bi;
+    if (k == 1) {
+        next(-HUGE_VAL, -1, bm, bi);
+        const Key b = block_least<kSelWaves>(bm, bi, &s_m[0][0], &s_i[0][0]);
+        if (t == 0) list[0] = Key{b.mk, b.idx == kNone ? -1 : b.idx};
+        return;
+    }
+    if (chunk == kSelBlock) {   // one key a thread
+        static_assert(kSelWaves * kMaxK == kSelBlock, "a place for every thread's key");
+        double *all = &s_m[0][0];
+        const double v = lo + t < hi ? feasible(mk, pk, st, cap, lo + t) : __longlong_as_double(-1);
+        const bool has = v == v;
+        all[t] = v;
+        if (t < kSelWaves) s_i[0][t] = 0;
+        __syncthreads();
+        if (has) {
+            const int r = count_less(all, kSelBlock, v, t);
+            if (r < k) list[r] = Key{v, lo + t};
         }
-        pm = best.mk;
-        pi = best.idx;
-        if (best.idx == kNone) {
-            for (int q = r + 1; q < k && threadIdx.x == 0; ++q) {
-                ws[(int64_t)blockIdx.x * k + q].mk = HUGE_VAL;
-                ws[(int64_t)blockIdx.x * k + q].idx = -1;
+        const int mine = __popcll(__builtin_amdgcn_ballot_w64(has));
+        if (lane == 0) s_i[0][wave] = mine;
+        __syncthreads();
+        int have = 0;
+        for (int w = 0; w < kSelWaves; ++w) have += (int)s_i[0][w];
+        if (t >= have && t < k) list[t] = Key{HUGE_VAL, -1};
+        return;
+    }
+    next(-HUGE_VAL, -1, bm, bi);
+    for (int r = 0; r < k; ++r) {
+        const int l = wave_least(bm, bi);
+        const double wm = from_lane(bm, l);
+        const int64_t wi = from_lane(bi, l);
+        if (lane == 0) {
+            s_m[wave][r] = wm;
+            s_i[wave][r] = wi;
+        }
+        if (wi == kNone) {
+            for (int q = r + 1 + lane; q < k; q += 64) {
+                s_m[wave][q] = HUGE_VAL;
+                s_i[wave][q] = kNone;
             }
             break;
         }
+        if (lane == l && r + 1 < k) next(wm, wi, bm, bi);
     }
+    __syncthreads();
+    Key key{HUGE_VAL, -1};
+    int have;
+    const int place = rank_of(s_m, s_i, k, t, key, have);
+    if (place >= 0 && place < k) list[place] = key;
+    if (t >= have && t < k) list[t] = Key{HUGE_VAL, -1};
 }
 
-// Pass 2: the blocks' lists are ascending, so round r's key is the least
-// of the lists' heads; each thread holds the heads of its lists (list q
-// at thread q mod kSelBlock) and the owner of the winning head advances it.
-constexpr int kListsPerThread = kMaxBlocks / kSelBlock;
-__global__ __launch_bounds__(kSelBlock) void k_select_merge(const Key *ws, int64_t nl, int k,
+__global__ __launch_bounds__(kMergeBlock) void k_select_merge(const Key *ws, int64_t nl, int k,
                                                             int64_t *out_idx, double *out_mk,
                                                             int32_t *out_found)
 {
-    __shared__ double s_m[kSelBlock];
-    __shared__ int64_t s_i[kSelBlock];
-    int head[kListsPerThread];
-    double hm[kListsPerThread];
-    int64_t hi[kListsPerThread];
-#pragma unroll
-    for (int j = 0; j < kListsPerThread; ++j) {
-        const int64_t q = threadIdx.x + (int64_t)j * kSelBlock;
-        head[j] = 0;
-        hm[j] = HUGE_VAL;
-        hi[j] = kNone;
-        if (q < nl && ws[q * k].idx >= 0) {
-            hm[j] = ws[q * k].mk;
-            hi[j] = ws[q * k].idx;
+    static_assert(kMaxBlocks <= kMergeBlock, "a thread for every list");
+    __shared__ double s_m[kMaxK * kMaxK];
+    __shared__ int64_t s_i[kMaxK * kMaxK];
+    __shared__ double s_wm[kMergeWaves];
+    __shared__ int64_t s_wi[kMergeWaves];
+    __shared__ Key s_bound;
+    __shared__ int s_n;
+    const int t = threadIdx.x;
+    const Key none{HUGE_VAL, kNone};
+    Key head = t < nl ? ws[(int64_t)t * k] : none;
+    if (head.idx < 0) head = none;
+    if (k == 1) {
+        const Key b = block_least<kMergeWaves>(head.mk, head.idx, s_wm, s_wi);
+        if (t == 0) {
+            out_idx[0] = b.idx == kNone ? -1 : b.idx;
+            out_mk[0] = b.mk;
+            *out_found = b.idx == kNone ? 0 : 1;
+        }
+        return;
+    }
+    Key tail = t < nl ? ws[(int64_t)t * k + k - 1] : none;
+    if (tail.idx < 0) tail = none;
+    const bool has = head.idx != kNone;
+    if (t < nl) s_m[t] = has ? head.mk : __longlong_as_double(-1);
+    if (t == 0) {
+        s_bound = none;
+        s_n = 0;
+    }
+    const Key last = block_least<kMergeWaves>(tail.mk, tail.idx, s_wm, s_wi);   // (its barrier covers the stores above)
+    // lists hold ascending indices, so equal heads rank by their list
+    if (has && count_less(s_m, (int)nl, head.mk, t) == k - 1) s_bound = head;
+    __syncthreads();
+    Key bound = s_bound;
+    if (key_less(last.mk, last.idx, bound.mk, bound.idx)) bound = last;
+    // the keys up to the bound: of at most k lists (or of all, if fewer than
+    // k have any), at most k each
+    for (int64_t q = t; q < nl * k; q += kMergeBlock) {
+        const Key x = ws[q];
+        if (x.idx >= 0 && !key_less(bound.mk, bound.idx, x.mk, x.idx)) {
+            const int at = atomicAdd(&s_n, 1);
+            s_m[at] = x.mk;
+            s_i[at] = x.idx;
         }
     }
-    int found = 0;
-    for (int r = 0; r < k; ++r) {
-        double bm = HUGE_VAL;
-        int64_t bi = kNone;
-#pragma unroll
-        for (int j = 0; j < kListsPerThread; ++j)
-            if (key_less(hm[j], hi[j], bm, bi)) {
-                bm = hm[j];
-                bi = hi[j];
-            }
-        const Key best = block_min(bm, bi, s_m, s_i);
-        if (threadIdx.x == 0) {
-            out_idx[r] = best.idx == kNone ? -1 : best.idx;
-            out_mk[r] = best.idx == kNone ? HUGE_VAL : best.mk;
+    __syncthreads();
+    const int n = s_n;
+    for (int q = t; q < n; q += kMergeBlock) {
+        const double m = s_m[q];
+        const int64_t i = s_i[q];
+        int r = 0;
+#pragma unroll 4
+        for (int j = 0; j < n; ++j) r += key_less(s_m[j], s_i[j], m, i) ? 1 : 0;
+        if (r < k) {
+            out_idx[r] = i;
+            out_mk[r] = m;
         }
-        if (best.idx == kNone) continue;
-        found = r + 1;
-#pragma unroll
-        for (int j = 0; j < kListsPerThread; ++j)
-            if (hi[j] == best.idx) {   // indices are unique: this thread's list holds the winner
-                const int64_t q = threadIdx.x + (int64_t)j * kSelBlock;
-                ++head[j];
-                hm[j] = HUGE_VAL;
-                hi[j] = kNone;
-                if (head[j] < k && ws[q * k + head[j]].idx >= 0) {
-                    hm[j] = ws[q * k + head[j]].mk;
-                    hi[j] = ws[q * k + head[j]].idx;
-                }
-            }
     }
-    if (threadIdx.x == 0) *out_found = found;
+    const int found = n < k ? n : k;
+    if (t >= found && t < k) {
+        out_idx[t] = -1;
+        out_mk[t] = HUGE_VAL;
+    }
+    if (t == 0) *out_found = found;
 }
 
 int64_t n_chunks(int64_t n, int64_t *chunk)
@@ -182,6 +374,12 @@ dsim_status launch_argmin(const double *mk, const uint64_t *pk, const int32_t *s
                           uint64_t cap, int32_t k, void *ws, int64_t *out_idx, double *out_mk,
                           int32_t *out_found, hipStream_t s)
 {
+    if (n <= kOneBlock) {
+        hipLaunchKernelGGL(k_select_one, dim3(1), dim3(kMergeBlock), 0, s, mk, pk, st, (int)n, cap, k, out_idx, out_mk,
+                           out_found);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? DSIM_OK : hip_fail(e, "select launch");
+    }
     int64_t chunk;
     const int64_t blocks = n_chunks(n, &chunk);
     Key *w = static_cast<Key *>(ws);
@@ -189,7 +387,7 @@ dsim_status launch_argmin(const double *mk, const uint64_t *pk, const int32_t *s
                        cap, k, chunk, w);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "select_chunks launch");
-    hipLaunchKernelGGL(k_select_merge, dim3(1), dim3(kSelBlock), 0, s, w, blocks, k, out_idx, out_mk, out_found);
+    hipLaunchKernelGGL(k_select_merge, dim3(1), dim3(kMergeBlock), 0, s, w, blocks, k, out_idx, out_mk, out_found);
     e = hipGetLastError();
     return e == hipSuccess ? DSIM_OK : hip_fail(e, "select_merge launch");
 }

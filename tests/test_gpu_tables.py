@@ -444,3 +444,31 @@ def test_eight_lanes_and_one_lane_per_candidate(torch_gpu, n_dev, kinds):
         big, at = run(total)
         for k in small:
             assert np.array_equal(big[k], small[k][at]), (total, k)
+
+
+@pytest.mark.parametrize("n", [2, 64, 1023, 1024, 1025, 65_536, 131_072, 131_073, 300_001])
+@pytest.mark.parametrize("k", [1, 2, 63, 64])
+@pytest.mark.parametrize("order", ["ascending", "descending", "equal", "sparse"])
+def test_argmin_orders_and_block_edges(torch_gpu, n, k, order):
+    """Selection at the edges of its passes (1,024 keys in one block, 256-key
+    chunks up to 131,072 keys) on keys that crowd into few chunks (sorted
+    either way), on equal ones, and where few are feasible, +inf and -0.0
+    among them; against a sort."""
+    from paper_2111_05426_amd import dsim
+    torch = torch_gpu
+    rng = np.random.default_rng(n + 31 * k)
+    mk = {"ascending": np.arange(n) * 0.5, "descending": np.arange(n)[::-1] * 0.5, "equal": np.full(n, 3.0),
+          "sparse": rng.uniform(0, 9, n)}[order]
+    st = (rng.random(n) > (40.0 / n if order == "sparse" else 2.0)).astype(np.int32)
+    mk[n // 2] = np.inf
+    mk[n // 3] = -0.0
+    st[[n // 2, n // 3]] = 0
+    pk = np.zeros(n, np.int64)
+    idx, mo, found = dsim.select_topk(*(torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (mk, pk, st)), 7, k)
+    torch.cuda.synchronize()
+    ok = np.nonzero(st == 0)[0]
+    best = ok[np.lexsort((ok, mk[ok]))][:k]
+    f = int(found.item())
+    assert f == len(best)
+    assert np.array_equal(idx.cpu().numpy()[:f], best) and np.array_equal(mo.cpu().numpy()[:f], mk[best])
+    assert np.all(idx.cpu().numpy()[f:] == -1) and np.all(mo.cpu().numpy()[f:] == np.inf)
