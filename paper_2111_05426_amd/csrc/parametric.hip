@@ -1775,41 +1775,36 @@ __global__ __launch_bounds__(kScanBlock) void k_class_count(const dsim_strategy 
 }
 
 // counts[b][j] -> exclusive prefix over blocks b, per class j; meta as in
-// ParArgs.  One block.
-__global__ __launch_bounds__(kScanBlock) void k_class_scan(uint32_t *counts, int64_t nb, uint32_t *meta)
+// ParArgs.  One block; a wavefront per class.
+__global__ __launch_bounds__(kLanes * kClasses) void k_class_scan(uint32_t *counts, int64_t nb, uint32_t *meta)
 {
-    __shared__ uint32_t s_v[kScanBlock];
-    __shared__ uint32_t s_total[8];
-    const int t = threadIdx.x;
-    for (int j = 0; j < kClasses; ++j) {
-        uint32_t carry = 0;
-        for (int64_t b0 = 0; b0 < nb; b0 += kScanBlock) {
-            const int64_t b = b0 + t;
+    __shared__ uint32_t s_total[kClasses];
+    const int j = threadIdx.x / kLanes, lane = threadIdx.x % kLanes;
+    uint32_t carry = 0;
+    if (j >= kMinClass) {   // (no candidate is in a narrower class)
+        for (int64_t b0 = 0; b0 < nb; b0 += kLanes) {
+            const int64_t b = b0 + lane;
             const uint32_t v = b < nb ? counts[(size_t)b * 8 + j] : 0;
-            s_v[t] = v;
-            __syncthreads();
-            for (int o = 1; o < kScanBlock; o <<= 1) {
-                const uint32_t add = t >= o ? s_v[t - o] : 0;
-                __syncthreads();
-                s_v[t] += add;
-                __syncthreads();
+            uint32_t sum = v;
+            for (int o = 1; o < kLanes; o <<= 1) {
+                const uint32_t up = (uint32_t)__shfl_up((int)sum, o, kLanes);
+                sum += lane >= o ? up : 0;
             }
-            if (b < nb) counts[(size_t)b * 8 + j] = carry + s_v[t] - v;
-            carry += s_v[kScanBlock - 1];
-            __syncthreads();
+            if (b < nb) counts[(size_t)b * 8 + j] = carry + sum - v;
+            carry += (uint32_t)__shfl((int)sum, kLanes - 1, kLanes);
         }
-        if (t == 0) s_total[j] = carry;
-        __syncthreads();
     }
-    if (t == 0) {
+    if (lane == 0) s_total[j] = carry;
+    __syncthreads();
+    if (threadIdx.x == 0) {
         uint32_t rank = 0, wave = 0;
-        for (int j = 0; j < kClasses; ++j) {
-            meta[j] = s_total[j];
-            meta[8 + j] = rank;
-            meta[16 + j] = wave;
-            rank += s_total[j];
-            const uint32_t per = (uint32_t)kLanes >> j;   // candidates per wavefront
-            wave += (s_total[j] + per - 1) / per;
+        for (int i = 0; i < kClasses; ++i) {
+            meta[i] = s_total[i];
+            meta[8 + i] = rank;
+            meta[16 + i] = wave;
+            rank += s_total[i];
+            const uint32_t per = (uint32_t)kLanes >> i;   // candidates per wavefront
+            wave += (s_total[i] + per - 1) / per;
         }
         meta[kClasses] = 0;
         meta[8 + kClasses] = rank;
@@ -1834,20 +1829,30 @@ __device__ __forceinline__ int len_bucket(uint32_t len)
 __global__ __launch_bounds__(kOrderBlock) void k_wave_order(const uint32_t *meta, const uint32_t *wave_len,
                                                            uint32_t *order)
 {
-    __shared__ uint32_t s_cnt[kLenBuckets];
+    __shared__ uint32_t s_cnt[kLenBuckets], s_part[kLenBuckets / kLanes];
     const int t = threadIdx.x;
     const uint32_t n_w = meta[16 + kClasses];
     for (int i = t; i < kLenBuckets; i += kOrderBlock) s_cnt[i] = 0;
     __syncthreads();
+    // (neighbouring wavefronts have nearly the same length, and a wavefront's
+    // atomics on one bucket run one by one; a contiguous part of the list per
+    // thread took 13 instead of 20 us here, but mixed the wavefronts of a
+    // bucket and cost the simulation 20)
     for (uint32_t i = t; i < n_w; i += kOrderBlock) atomicAdd(&s_cnt[len_bucket(wave_len[i])], 1u);
     __syncthreads();
-    if (t == 0) {   // bucket starts, longest bucket first
-        uint32_t pos = 0;
-        for (int i = kLenBuckets - 1; i >= 0; --i) {
-            const uint32_t k = s_cnt[i];
-            s_cnt[i] = pos;
-            pos += k;
-        }
+    // bucket starts, longest bucket first: a prefix sum from the last bucket
+    const int b = kLenBuckets - 1 - t;
+    uint32_t sum = t < kLenBuckets ? s_cnt[b] : 0;
+    const uint32_t own = sum;
+    for (int o = 1; o < kLanes; o <<= 1) {
+        const uint32_t up = (uint32_t)__shfl_up((int)sum, o, kLanes);
+        sum += t % kLanes >= o ? up : 0;
+    }
+    if (t < kLenBuckets && t % kLanes == kLanes - 1) s_part[t / kLanes] = sum;
+    __syncthreads();
+    if (t < kLenBuckets) {
+        for (int w = 0; w < t / kLanes; ++w) sum += s_part[w];
+        s_cnt[b] = sum - own;
     }
     __syncthreads();
     for (uint32_t i = t; i < n_w; i += kOrderBlock) order[atomicAdd(&s_cnt[len_bucket(wave_len[i])], 1u)] = i;
@@ -1982,7 +1987,7 @@ dsim_status launch_parametric(const dsim_model &m, const dsim_strategy *cand, in
     g.order = order;
     g.meta = meta;
     hipLaunchKernelGGL(k_class_count, dim3((unsigned)nb), dim3(kScanBlock), 0, s, cand, n_cand, pb, counts, wave_len);
-    hipLaunchKernelGGL(k_class_scan, dim3(1), dim3(kScanBlock), 0, s, counts, nb, meta);
+    hipLaunchKernelGGL(k_class_scan, dim3(1), dim3(kLanes * kClasses), 0, s, counts, nb, meta);
     hipLaunchKernelGGL(k_class_scatter, dim3((unsigned)nb), dim3(kScanBlock), 0, s, cand, n_cand, pb,
                        (const uint32_t *)counts, (const uint32_t *)meta, perm, m.n_layers, m.mode != DSIM_INFER, wave_len);
     hipLaunchKernelGGL(k_wave_order, dim3(1), dim3(kOrderBlock), 0, s, (const uint32_t *)meta,
