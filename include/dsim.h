@@ -406,7 +406,7 @@ DSIM_API dsim_status dsim_simulate_parametric_static(const dsim_model *model, co
  *     DSIM_ST_NOT_TABLE (more than max_ops ops, a FLOP or byte count not
  *     exact in fp32, or an alloc / free size or a reduction length above
  *     2^32 - 1).
- * 1 <= n_dev <= 8, max_ops >= 0, n_cand <= 2^32 - 256.  One GPU lane per
+ * 1 <= n_dev <= 8, max_ops >= 0, n_cand <= 2^32 - 256.  One wavefront per
  * candidate.
  */
 DSIM_API dsim_status dsim_materialize_tables(const dsim_model *model, const dsim_strategy *cand, int64_t n_cand,

@@ -1,7 +1,7 @@
 // materialize.hip -- write the whole distributed program of a strategy as an
 // explicit op table.
 //
-// One lane per candidate expands the transform of Sec. 4 for every device
+// One wavefront per candidate expands the transform of Sec. 4 for every device
 // (device p*(D*H) + d*H + h runs stage p of data replica d, tensor rank h)
 // in a program order whose per-device projections are those of the
 // transform (Sec. 2.1 semantics depend on nothing else): the splits, then
@@ -20,14 +20,20 @@
 // rank), and the weight update hands each one back before its optimizer op.
 // The records go to the op-major, candidate-fastest table layout that
 // dsim_simulate_tables reads.
+//
+// A block's records depend on its stage, direction and microbatch alone, and
+// their number on even less, so the wavefront first walks the schedule (a
+// lane per stage) to find where each block and Send starts, and then its
+// lanes write 64 of them at a time, one each.  What bounds it is one block's
+// chain of records in a lane: the 30 strategies of the tiny MLP, up to 440
+// records each, took 444 us with a lane writing a whole program, 40 now; 888
+// MLP strategies of up to 25,552 records 11.8 -> 0.75 ms.
 #include "model.h"
 
 namespace dsim {
 namespace {
 
 constexpr int kLanes = 64;
-constexpr uint16_t kNoBlock = 0xffffu;
-
 struct MatArgs {
     dsim_model m;
     const dsim_strategy *cand;
@@ -43,6 +49,23 @@ struct MatArgs {
     uint32_t *n_ops;
     uint64_t *init_live;
     int32_t *status;
+    int64_t c0;         // the launch's first candidate
+};
+
+// How many records a stage's ops make.
+struct RecordCount {
+    const Ctx &x;
+    int64_t n;
+
+    __device__ __forceinline__ void local(uint64_t, uint64_t, uint64_t, uint64_t) { n += x.D * x.H; }
+    __device__ __forceinline__ void mm(uint64_t, uint64_t, uint64_t, uint64_t, uint64_t) { n += x.D * x.H; }
+    __device__ __forceinline__ void ar_tp(uint64_t) { n += x.H > 1 ? x.D : 0; }
+    __device__ __forceinline__ void ar_dp(uint64_t) { n += x.D > 1 ? x.H : 0; }
+    __device__ __forceinline__ void bcast(uint64_t, int) { n += x.zero ? x.H : 0; }
+    __device__ __forceinline__ void reduce(uint64_t, int) { n += x.H; }
+    __device__ __forceinline__ void owner_local(uint64_t, uint64_t, uint64_t, uint64_t, int) { n += x.H; }
+    __device__ __forceinline__ void handover(uint64_t) { n += x.D * x.H + x.H; }
+    __device__ __forceinline__ void handback(uint64_t) { n += x.D * x.H; }
 };
 
 // Appends records for one stage's ops on every replica device.
@@ -79,7 +102,7 @@ struct Emit {
         }
         ++j;
     }
-    __device__ void compute(uint32_t cls, uint64_t fl, uint64_t by, uint64_t al, uint64_t fr, uint64_t k)
+    __device__ __forceinline__ void compute(uint32_t cls, uint64_t fl, uint64_t by, uint64_t al, uint64_t fr, uint64_t k)
     {
         for (int r = 0; r < x.D * x.H; ++r) {
             const uint64_t copy = (pend != 0 && r / x.H != pend_owner) ? pend : 0;
@@ -87,16 +110,16 @@ struct Emit {
         }
         pend = 0;
     }
-    __device__ void local(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr) { compute(0u, fl, by, al, fr, 0); }
+    __device__ __forceinline__ void local(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr) { compute(0u, fl, by, al, fr, 0); }
     // a matrix multiplication of reduction length k: cost class 1 of the
     // table format
-    __device__ void mm(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr, uint64_t k)
+    __device__ __forceinline__ void mm(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr, uint64_t k)
     {
         compute(1u, fl, by, al, fr, k);
     }
     // ZeRO: the owner's broadcast over the D replicas of each tensor rank
     // (kind 3, root = the owner: the others allocate their copy)
-    __device__ void bcast(uint64_t by, int grp)
+    __device__ __forceinline__ void bcast(uint64_t by, int grp)
     {
         if (!x.zero) return;
         const int o = grp % x.D;
@@ -107,26 +130,26 @@ struct Emit {
     }
     // ZeRO: reduce onto the owner (kind 4: the owner allocates the reduced
     // gradient, every member frees its own)
-    __device__ void reduce(uint64_t by, int grp)
+    __device__ __forceinline__ void reduce(uint64_t by, int grp)
     {
         const int o = grp % x.D;
         for (int h = 0; h < x.H; ++h)
             put(4u | (dv(base + o * x.H + h) << 8) | (dp_mask(h) << 16), 0, by, by, by);
     }
-    __device__ void owner_local(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr, int grp)
+    __device__ __forceinline__ void owner_local(uint64_t fl, uint64_t by, uint64_t al, uint64_t fr, int grp)
     {
         const int o = grp % x.D;
         for (int h = 0; h < x.H; ++h) put(dv(base + o * x.H + h) << 8, fl, by, al, fr);
     }
     // the D replicas of tensor rank h on this stage (stream 0: computation,
     // 1: communication)
-    __device__ uint32_t dp_mask(int h, int stream = 0) const
+    __device__ __forceinline__ uint32_t dp_mask(int h, int stream = 0) const
     {
         uint32_t mask = 0;
         for (int d = 0; d < x.D; ++d) mask |= 1u << (dv(base + d * x.H + h) + (uint32_t)stream);
         return mask;
     }
-    __device__ void ar_tp(uint64_t by)
+    __device__ __forceinline__ void ar_tp(uint64_t by)
     {
         if (x.H <= 1) return;
         for (int d = 0; d < x.D; ++d) {
@@ -135,12 +158,12 @@ struct Emit {
             put(2u | (mask << 16), 0, by, 0, 0);
         }
     }
-    __device__ void ar_dp(uint64_t by)
+    __device__ __forceinline__ void ar_dp(uint64_t by)
     {
         if (x.D <= 1) return;
         for (int h = 0; h < x.H; ++h) put(2u | (dp_mask(h) << 16), 0, by, 0, 0);
     }
-    __device__ void send(int t, uint64_t sz, uint64_t fre)
+    __device__ __forceinline__ void send(int t, uint64_t sz, uint64_t fre)
     {
         const int tbase = t * x.D * x.H;
         for (int r = 0; r < x.D * x.H; ++r)
@@ -148,123 +171,190 @@ struct Emit {
     }
     // overlap: each replica hands the finished gradient to its communication
     // stream (nothing allocated or freed), whose D replicas all-reduce it
-    __device__ void handover(uint64_t by)
+    __device__ __forceinline__ void handover(uint64_t by)
     {
         for (int r = 0; r < x.D * x.H; ++r) put(1u | (dv(base + r) << 8) | ((dv(base + r) + 1u) << 16), 0, by, 0, 0);
         for (int h = 0; h < x.H; ++h) put(2u | (dp_mask(h, 1) << 16), 0, by, 0, 0);
     }
     // overlap: the reduced gradient comes back to the computation stream
-    __device__ void handback(uint64_t by)
+    __device__ __forceinline__ void handback(uint64_t by)
     {
         for (int r = 0; r < x.D * x.H; ++r) put(1u | ((dv(base + r) + 1u) << 8) | (dv(base + r) << 16), 0, by, 0, 0);
     }
 };
 
+// A block or Send of the schedule and its first record.
+struct Item {
+    int64_t at;
+    int32_t k;
+    uint16_t s;
+    uint8_t bwd, send;
+};
+constexpr int kItems = kLanes + 2 * kMaxTableDev;   // a slot adds at most two per stage
+
 __global__ __launch_bounds__(kLanes) void k_materialize(const MatArgs g)
 {
-    __shared__ uint16_t s_pos[kMaxTableDev][kLanes], s_nf[kMaxTableDev][kLanes], s_nb[kMaxTableDev][kLanes],
-        s_em[kMaxTableDev][kLanes];
+    __shared__ Item s_item[kItems];
     const int lane = threadIdx.x;
-    const int64_t c = (int64_t)blockIdx.x * kLanes + lane;
-    if (c >= g.n_cand) return;
+    const int64_t c = g.c0 + (int64_t)blockIdx.x;
     const dsim_strategy st = g.cand[c];
-    for (int dev = 0; dev < g.n_dev; ++dev) g.init_live[c * g.n_dev + dev] = 0;
     const int S = g.m.overlap ? 2 : 1;
     const bool ok = strategy_ok(g.m, st.D, st.H, st.P, st.K) && st.K <= kMaxK &&
                     (int64_t)S * st.D * st.H * st.P <= (int64_t)g.n_dev;
     if (!ok) {
-        g.n_ops[c] = 0;
-        g.status[c] = DSIM_ST_BAD_STRATEGY;
+        if (lane < g.n_dev) g.init_live[c * g.n_dev + lane] = 0;
+        if (lane == 0) {
+            g.n_ops[c] = 0;
+            g.status[c] = DSIM_ST_BAD_STRATEGY;
+        }
         return;
     }
     CostConsts none = {};
     Ctx x = {};
     make_ctx(g.m, none, st, x);
     const int DH = x.D * x.H;
-    Emit e{x, g, c, 0, false, 0, 0, 0, S};
-    for (int s = 0; s < x.P; ++s) {
-        if (x.zero) {
-            // each data replica holds the groups it owns
-            ZStage zs;
-            z_stage(x, s, zs);
-            const uint64_t in = resident_inputs(x, s);
-            for (int r = 0; r < DH; ++r) g.init_live[c * g.n_dev + s * DH + r] = in + z_owned(x, zs, r / x.H);
-        } else {
-            // (a communication stream holds nothing)
-            const uint64_t r0 = resident(x, s);
-            for (int r = 0; r < DH; ++r) g.init_live[c * g.n_dev + e.dv(s * DH + r)] = r0;
+    if (lane < g.n_dev) {
+        // a communication stream, and a device beyond the program's, holds nothing
+        const int gpu = lane / S, s = gpu / DH;
+        uint64_t r0 = 0;
+        if (lane % S == 0 && s < x.P) {
+            if (x.zero) {
+                // each data replica holds the groups it owns
+                ZStage zs;
+                z_stage(x, s, zs);
+                r0 = resident_inputs(x, s) + z_owned(x, zs, (gpu % DH) / x.H);
+            } else {
+                r0 = resident(x, s);
+            }
         }
-        s_pos[s][lane] = 0;
-        s_nf[s][lane] = 0;
-        s_nb[s][lane] = 0;
+        g.init_live[c * g.n_dev + lane] = r0;
     }
-    // microbatch splits before the pipeline
-    if (x.K > 1) {
-        e.base = 0;
-        split(x, e);
+
+    // records of this lane's stage: a forward block, the backward blocks of
+    // microbatch 0, of the last one and of the others, the weight update
+    const int s = lane;
+    const bool stage = s < x.P;
+    int64_t n_f = 0, n_b0 = 0, n_b1 = 0, n_bl = 0, n_wu = 0;
+    if (stage) {
+        RecordCount f{x, 0}, b0{x, 0}, b1{x, 0}, bl{x, 0}, w{x, 0};
+        block_fwd(x, f, s, 0);
+        n_f = f.n;
         if (x.train) {
+            block_bwd(x, b0, s, 0);
+            if (x.K > 1) block_bwd(x, bl, s, x.K - 1);
+            if (x.K > 2) block_bwd(x, b1, s, 1);
+            weight_update(x, w, s);
+            n_b0 = b0.n;
+            n_b1 = b1.n;
+            n_bl = bl.n;
+            n_wu = w.n;
+        }
+    }
+    // exclusive prefix sum over the stages' lanes, and their total
+    auto before = [&](int64_t v, int64_t &total) {
+        int64_t sum = v;
+        for (int o = 1; o < kMaxTableDev; o <<= 1) {
+            const int64_t up = __shfl_up(sum, o, kLanes);
+            sum += lane >= o ? up : 0;
+        }
+        total = __shfl(sum, kMaxTableDev - 1, kLanes);
+        return sum - v;
+    };
+
+    Emit e{x, g, c, 0, false, 0, 0, 0, S};
+    // microbatch splits before the pipeline: one lane each
+    int64_t at = 0;
+    if (x.K > 1) {
+        if (lane == 0) {
+            split(x, e);
+        } else if (lane == 1 && x.train) {
+            e.j = DH;
             e.base = (x.P - 1) * DH;
             split(x, e);
         }
+        at = x.train ? 2 * DH : DH;
     }
-    const int len = x.train ? 2 * x.K : x.K;
-    for (;;) {
-        bool left = false, any = false;
-        int prev_nf0 = 0;
-        for (int s = 0; s < x.P; ++s) {
-            int pos = s_pos[s][lane], nf = s_nf[s][lane], nb = s_nb[s][lane];
-            const int nf0 = nf;
-            uint16_t em = kNoBlock;
-            if (pos < len) {
-                left = true;
-                bool bwd;
-                int k;
-                block_at(x, s, pos, bwd, k);
-                const bool ready = !bwd ? (s == 0 || prev_nf0 > k) : (s == x.P - 1 ? nf0 > k : s_nb[s + 1][lane] > k);
-                if (ready) {
-                    e.base = s * DH;
-                    if (bwd) block_bwd(x, e, s, k);
-                    else block_fwd(x, e, s, k);
-                    ++pos;
-                    if (bwd) ++nb;
-                    else ++nf;
-                    em = (uint16_t)((k << 1) | (bwd ? 1 : 0));
-                    any = true;
+
+    const int len = stage ? (x.train ? 2 * x.K : x.K) : 0;
+    // forwards before the first backward (synchronous 1F1B; all otherwise)
+    const int warm = (x.train && x.schedule != DSIM_SCHED_GPIPE && x.P - 1 - s < x.K) ? x.P - 1 - s : x.K;
+    int nf = 0, nb = 0, n = 0;
+    bool stuck = false;
+    for (bool more = true; more;) {
+        // one slot of the schedule
+        const bool bwd = nf == x.K || nf - nb > warm;
+        const int k = bwd ? nb : nf;
+        const int left = __shfl_up(nf, 1, kLanes), right = __shfl_down(nb, 1, kLanes);
+        const int avail = bwd ? (s == x.P - 1 ? nf : right) : (s == 0 ? INT32_MAX : left);
+        const bool ready = nf + nb < len && avail > k;
+        const uint64_t run = __ballot(ready);
+        const bool sends = ready && (bwd ? s > 0 : s < x.P - 1);
+        const uint64_t out = __ballot(sends), below = (1ull << lane) - 1ull;
+        int64_t total;
+        const int64_t mine = !ready ? 0 : (!bwd ? n_f : (k == 0 ? n_b0 : (k == x.K - 1 ? n_bl : n_b1)));
+        const int64_t ahead = before(mine, total);
+        if (ready) s_item[n + __popcll(run & below)] = Item{at + ahead, k, (uint16_t)s, (uint8_t)bwd, 0};
+        n += __popcll(run);
+        at += total;
+        if (sends) {
+            const int p = __popcll(out & below);
+            s_item[n + p] = Item{at + (int64_t)p * DH, k, (uint16_t)s, (uint8_t)bwd, 1};
+        }
+        n += __popcll(out);
+        at += (int64_t)__popcll(out) * DH;
+        if (ready) {
+            if (bwd) ++nb;
+            else ++nf;
+        }
+        more = __ballot(nf + nb < len) != 0;
+        stuck = more && run == 0;   // no stage can proceed: impossible for these schedules
+        more = more && !stuck;
+        if (n < kLanes && more) continue;
+        // write up to 64 of them
+        do {
+            __syncthreads();
+            const int now = n < kLanes ? n : kLanes;
+            if (lane < now) {
+                const Item it = s_item[lane];
+                if (it.at < (int64_t)g.max_ops) {   // (beyond, the program does not fit anyway)
+                    e.j = it.at;
+                    e.base = it.s * DH;
+                    e.pend = 0;
+                    if (it.send) {
+                        uint64_t sz, fre;
+                        send_size(x, it.s, mb_rows(x, it.k), it.bwd != 0, sz, fre);
+                        e.send(it.bwd ? it.s - 1 : it.s + 1, sz, fre);
+                    } else if (it.bwd) {
+                        block_bwd(x, e, it.s, it.k);
+                    } else {
+                        block_fwd(x, e, it.s, it.k);
+                    }
                 }
             }
-            s_pos[s][lane] = (uint16_t)pos;
-            s_nf[s][lane] = (uint16_t)nf;
-            s_nb[s][lane] = (uint16_t)nb;
-            s_em[s][lane] = em;
-            prev_nf0 = nf0;
-        }
-        if (!left) break;
-        if (!any) {   // no stage can proceed: impossible for 1F1B
-            g.n_ops[c] = 0;
-            g.status[c] = DSIM_ST_BAD_STRATEGY;
-            return;
-        }
-        for (int s = 0; s < x.P; ++s) {
-            const uint16_t em = s_em[s][lane];
-            if (em == kNoBlock) continue;
-            const bool bwd = em & 1;
-            const int k = em >> 1;
-            if ((!bwd && s == x.P - 1) || (bwd && s == 0)) continue;
-            uint64_t sz, fre;
-            send_size(x, s, mb_rows(x, k), bwd, sz, fre);
-            e.base = s * DH;
-            e.send(bwd ? s - 1 : s + 1, sz, fre);
-        }
+            __syncthreads();
+            Item rest;
+            const bool moves = lane < n - now;
+            if (moves) rest = s_item[now + lane];
+            __syncthreads();
+            if (moves) s_item[lane] = rest;
+            n -= now;
+        } while (!more && n > 0);
     }
-    if (x.train) {
-        for (int s = 0; s < x.P; ++s) {
-            e.base = s * DH;
-            weight_update(x, e, s);
-        }
+    int64_t total;
+    const int64_t ahead = before(n_wu, total);
+    if (stage && x.train) {
+        e.j = at + ahead;
+        e.base = s * DH;
+        e.pend = 0;
+        weight_update(x, e, s);
     }
-    const bool fits = e.j <= (int64_t)g.max_ops && !e.inexact;
-    g.n_ops[c] = fits ? (uint32_t)e.j : 0u;
-    g.status[c] = fits ? 0 : DSIM_ST_NOT_TABLE;
+    at += total;
+    const bool inexact = __ballot(e.inexact) != 0;
+    if (lane == 0) {
+        const bool fits = at <= (int64_t)g.max_ops && !inexact;
+        g.n_ops[c] = fits && !stuck ? (uint32_t)at : 0u;
+        g.status[c] = stuck ? DSIM_ST_BAD_STRATEGY : (fits ? 0 : DSIM_ST_NOT_TABLE);
+    }
 }
 
 }  // namespace
@@ -289,9 +379,14 @@ dsim_status launch_materialize(const dsim_model &m, const dsim_strategy *cand, i
     g.n_ops = n_ops;
     g.init_live = init_live;
     g.status = status;
-    const int64_t blocks = (n_cand + kLanes - 1) / kLanes;
-    hipLaunchKernelGGL(k_materialize, dim3((unsigned)blocks), dim3(kLanes), 0, s, g);
-    const hipError_t e = hipGetLastError();
+    // (one dispatch holds fewer than 2^32 lanes)
+    constexpr int64_t kMaxBlocks = (int64_t)1 << 25;
+    hipError_t e = hipSuccess;
+    for (g.c0 = 0; g.c0 < n_cand && e == hipSuccess; g.c0 += kMaxBlocks) {
+        const int64_t blocks = n_cand - g.c0 < kMaxBlocks ? n_cand - g.c0 : kMaxBlocks;
+        hipLaunchKernelGGL(k_materialize, dim3((unsigned)blocks), dim3(kLanes), 0, s, g);
+        e = hipGetLastError();
+    }
     return e == hipSuccess ? DSIM_OK : hip_fail(e, "materialize launch");
 }
 

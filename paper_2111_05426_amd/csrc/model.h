@@ -702,36 +702,6 @@ __device__ __forceinline__ void split(const Ctx &x, S &o)
     o.local(0, 2 * whole, whole, whole);
 }
 
-// ---------------------------------------------------------------------------
-// Block order of a stage: forward-only (inference); synchronous 1F1B; GPipe
-// ---------------------------------------------------------------------------
-// position `pos` of stage s's block sequence -> (is_backward, microbatch)
-__device__ __forceinline__ void block_at(const Ctx &x, int s, int pos, bool &bwd, int &k)
-{
-    if (!x.train) {
-        bwd = false;
-        k = pos;
-        return;
-    }
-    if (x.schedule == DSIM_SCHED_GPIPE) {   // all forwards, then all backwards
-        bwd = pos >= x.K;
-        k = bwd ? pos - x.K : pos;
-        return;
-    }
-    const int w = (x.P - 1 - s) < x.K ? (x.P - 1 - s) : x.K;
-    if (pos < w) {
-        bwd = false;
-        k = pos;
-    } else if (pos < w + 2 * (x.K - w)) {
-        const int j = pos - w;
-        bwd = (j & 1) != 0;
-        k = bwd ? (j - 1) / 2 : w + j / 2;
-    } else {
-        bwd = true;
-        k = pos - w - (x.K - w);
-    }
-}
-
 // bytes sent after a block of m rows, and the bytes the sender frees
 __device__ __forceinline__ void send_size(const Ctx &x, int s, uint64_t m, bool bwd, uint64_t &sz, uint64_t &fre)
 {

@@ -234,3 +234,29 @@ def test_materialize_errors(torch_gpu, orc):
     odd = mlp(2, 4097, 8, 4, INFER)
     g = materialize_and_simulate(torch_gpu, odd, np.array([(1, 1, 1, 1)], np.int32), dev, 8, 64)
     assert list(g["mat_status"]) == [ST_NOT_TABLE] and g["table_ops"][0] == 0
+
+
+# A wavefront lists a schedule's blocks and Sends and writes 64 of them at a
+# time: programs of fewer and of many more than 64, one and eight stages, and
+# tables too short for them.
+@pytest.mark.parametrize("option", ["plain", "gpipe", "recompute", "zero", "overlap"])
+@pytest.mark.parametrize("family", ["mlp", "tf"])
+def test_long_schedules(torch_gpu, orc, family, option):
+    kw = {"gpipe": dict(schedule=SCHED_GPIPE), "plain": {}}.get(option, {option: 1})
+    model = mlp(8, 64, 96, 2, TRAIN_ADAM, **kw) if family == "mlp" else transformer(8, 32, 4, 8, 64, 96, 2, TRAIN_ADAM, **kw)
+    n_dev = 8
+    strat = all_strats([1, 2], [1, 2], [1, 2, 4, 8], [1, 2, 31, 32, 48], 4 if option == "overlap" else 8)
+    dev = DeviceSpec(streams=(2, float("inf"), 0.0)) if option == "overlap" else DeviceSpec()
+    o = orc.run_strategies(model, strat, dev, slice=False, row_width=8, threads=8)
+    ok = o["status"] == 0
+    assert np.any(ok)
+    strat, o = strat[ok], {k: v[ok] for k, v in o.items()}
+    max_ops = int(o["n_ops"].max())
+    g = materialize_and_simulate(torch_gpu, model, strat, dev, n_dev, max_ops)
+    assert np.array_equal(g["mat_status"], np.zeros(len(strat), np.int32))
+    assert np.array_equal(g["table_ops"], o["n_ops"].astype(np.int64))
+    assert np.array_equal(g["makespan"], o["makespan"])
+    assert np.array_equal(g["cand_peak"].view(np.uint64), o["cand_peak"])
+    # one record too few for the longest program: that one does not fit, the others do
+    g = materialize_and_simulate(torch_gpu, model, strat, dev, n_dev, max_ops - 1)
+    assert np.array_equal(g["mat_status"] == ST_NOT_TABLE, o["n_ops"] == max_ops)
