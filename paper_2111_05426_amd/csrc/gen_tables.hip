@@ -32,6 +32,12 @@ namespace {
 
 constexpr int kGenBlock = 64;
 constexpr int kSlots = 16;
+// Unused slots that make a block's share of the LDS 40 KB: a CU then holds
+// four wavefronts, one per SIMD.  With 32 KB it holds five, one SIMD runs two
+// of them at half speed and the others wait for it (1.48 against 1.95 ms at
+// 250,000 x 512 records; 16-bit buffers, the size drawn again when one is
+// freed, and two wavefronts per SIMD: 1% less, but for 65,536 ops at most).
+constexpr int kPad = 4;
 
 struct GenArgs {
     uint64_t seed;
@@ -45,9 +51,10 @@ struct GenArgs {
     uint32_t *n_ops_out;
 };
 
-__device__ __forceinline__ uint64_t splitmix_at(uint64_t seed, uint64_t n)
+constexpr uint64_t kGamma = 0x9E3779B97F4A7C15ull;
+// SplitMix64's output for the state z
+__device__ __forceinline__ uint64_t mix(uint64_t z)
 {
-    uint64_t z = seed + n * 0x9E3779B97F4A7C15ull;
     z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
     return z ^ (z >> 31);
@@ -79,81 +86,102 @@ __device__ __forceinline__ float log_uniform(uint64_t r, double log2_lo, double 
     return (float)ldexp(e, (int)n);
 }
 
+// The k-th number (k = 0, 1, ...) with two bits set or more: m is number
+// m - 2 - floor(log2 m) of them, so m = k + 2 + floor(log2 m), and the
+// logarithm of k + 2 is that of m or one less.
+__device__ __forceinline__ uint32_t nth_mask(uint32_t k)
+{
+    const uint32_t m = k + 33u - (uint32_t)__clz((int)(k + 2u));
+    return k + 33u - (uint32_t)__clz((int)m);
+}
+
+// Bound by vector issue: the draws' 64-bit products and the three powers of
+// two per op are about 1,700 cycles of a SIMD for 64 records.  So every op
+// kind shares one straight sequence -- the draws that only one kind needs
+// take each other's places (flops / destination / mask; bytes / message), a
+// draw's state is the op's plus a constant -- where three divergent branches
+// ran eleven draws and five powers; the buffer counts are bytes of one
+// register pair.  250,000 x 512 records over 8 devices: 2.29 -> 1.48 ms
+// (2.6 GB of records: a fill of that size takes 0.37 ms).
 __global__ __launch_bounds__(kGenBlock) void k_gen_tables(const GenArgs g)
 {
-    __shared__ uint32_t s_buf[8][kSlots][kGenBlock];
-    __shared__ uint32_t s_cnt[8][kGenBlock];
-    __shared__ uint32_t s_masks[256];
-    __shared__ uint32_t s_nmasks;
-
+    __shared__ uint32_t s_buf[8][kSlots + kPad][kGenBlock];
     const int tid = threadIdx.x;
-    if (tid == 0) {
-        uint32_t n = 0;
-        for (uint32_t mask = 0; mask < (1u << g.n_dev); ++mask)
-            if (__popc(mask) >= 2) s_masks[n++] = mask;
-        s_nmasks = n;
-    }
-    for (int d = 0; d < 8; ++d) s_cnt[d][tid] = 0;
-    __syncthreads();
     const int64_t cand = (int64_t)blockIdx.x * kGenBlock + tid;
     if (cand >= g.n_cand) return;
 
-    const uint64_t c = (uint64_t)cand;
-    const uint64_t seed = g.seed;
     const uint32_t nd = (uint32_t)g.n_dev;
-    const uint32_t n_masks = s_nmasks;
+    const uint32_t n_masks = (1u << nd) - 1u - nd;   // masks of two devices or more
     const size_t N = (size_t)g.n_cand;
+    // the state of draw 0 of op j is that of op 0 plus 32 j kGamma
+    uint64_t z = g.seed + (((uint64_t)cand << 32) + 1u) * kGamma;
+    uint64_t counts = 0;   // live buffers, a byte per device
 
-    for (int32_t j = 0; j < g.n_ops; ++j) {
-        const uint64_t base = (c << 32) + ((uint64_t)j << 5) + 1u;
-        const uint32_t kd = pick(splitmix_at(seed, base + 0), 10u);
-        const uint32_t a = pick(splitmix_at(seed, base + 1), nd);
-        uint32_t al = 0, fr = 0, code;
-        float fl = 0.f, by;
-        if (kd < 9u) {
-            const uint64_t r5 = splitmix_at(seed, base + 5);
-            const uint32_t na = s_cnt[a][tid];
-            if ((r5 >> 63) && na > 0u) {
-                const uint32_t i = (uint32_t)(((r5 & 0xffffffffull) * (uint64_t)na) >> 32);
-                fr = s_buf[a][i][tid];
-                s_buf[a][i][tid] = s_buf[a][na - 1u][tid];
-                s_cnt[a][tid] = na - 1u;
-            }
+    // an op's draws: everything that does not depend on the live buffers
+    struct Op {
+        uint32_t code, a, b, size, which;
+        float fl, by;
+        bool frees, allocs, is_s;
+    };
+    auto draw = [&](uint64_t zj) {
+        Op o;
+        const uint32_t kd = pick(mix(zj), 10u);
+        const bool is_c = kd < 7u;
+        o.is_s = kd == 7u || kd == 8u;
+        const uint32_t a = pick(mix(zj + kGamma), nd);
+        const uint64_t r_a = mix(zj + (is_c ? 3u * kGamma : 2u * kGamma));     // flops; destination; mask
+        const uint64_t r_b = mix(zj + (o.is_s ? 7u * kGamma : 4u * kGamma));   // bytes; message
+        const uint64_t r5 = mix(zj + 5u * kGamma), r6 = mix(zj + 6u * kGamma), r7 = mix(zj + 7u * kGamma);
+        const float fl = log_uniform(r_a, kLog2_1e6, kLog2_1e12);
+        const float v = log_uniform(r_b, kLog2_1e3, kLog2_1e9);
+        const float size = log_uniform(r7, kLog2_1e3, kLog2_1e9);
+        const uint32_t msg = (uint32_t)v;
+        uint32_t b = a + 1u + pick(r_a, nd - 1u);
+        b = b >= nd ? b - nd : b;
+        const uint32_t mask = nth_mask(pick(r_a, n_masks));
+        o.code = is_c ? a << 8 : (o.is_s ? 1u | (a << 8) | (b << 16) : 2u | (mask << 16));
+        o.fl = is_c ? fl : 0.f;
+        o.by = o.is_s ? (float)msg : v;
+        o.a = a;
+        o.b = o.is_s ? b : a;   // the device that allocates
+        o.size = o.is_s ? msg : (uint32_t)size;
+        o.frees = (is_c || o.is_s) && (r5 >> 63) != 0;
+        o.which = (uint32_t)r5;
+        o.allocs = o.is_s || (is_c && (r6 >> 63) != 0);
+        return o;
+    };
+    // free a live buffer of a, then allocate one on a (compute) or b (send)
+    auto apply = [&](const Op &p, int32_t j) {
+        uint32_t fr = 0, al = 0;
+        const uint32_t na = (uint32_t)(counts >> (8u * p.a)) & 0xffu;
+        if (p.frees && na > 0u) {
+            const uint32_t i = (uint32_t)(((uint64_t)p.which * (uint64_t)na) >> 32);
+            fr = s_buf[p.a][i][tid];
+            s_buf[p.a][i][tid] = s_buf[p.a][na - 1u][tid];
+            counts -= 1ull << (8u * p.a);
         }
-        if (kd < 7u) {
-            const uint64_t r6 = splitmix_at(seed, base + 6);
-            code = a << 8;
-            fl = log_uniform(splitmix_at(seed, base + 3), kLog2_1e6, kLog2_1e12);
-            by = log_uniform(splitmix_at(seed, base + 4), kLog2_1e3, kLog2_1e9);
-            const uint32_t na = s_cnt[a][tid];
-            if ((r6 >> 63) && na < (uint32_t)kSlots) {
-                al = (uint32_t)log_uniform(splitmix_at(seed, base + 7), kLog2_1e3, kLog2_1e9);
-                s_buf[a][na][tid] = al;
-                s_cnt[a][tid] = na + 1u;
-            }
-        } else if (kd < 9u) {
-            const uint32_t b = (a + 1u + pick(splitmix_at(seed, base + 2), nd - 1u)) % nd;
-            const uint32_t msg = (uint32_t)log_uniform(splitmix_at(seed, base + 7), kLog2_1e3, kLog2_1e9);
-            code = 1u | (a << 8) | (b << 16);
-            by = (float)msg;
-            const uint32_t nb = s_cnt[b][tid];
-            if (nb < (uint32_t)kSlots) {
-                al = msg;
-                s_buf[b][nb][tid] = msg;
-                s_cnt[b][tid] = nb + 1u;
-            }
-        } else {
-            const uint32_t mask = s_masks[pick(splitmix_at(seed, base + 2), n_masks)];
-            code = 2u | (mask << 16);
-            by = log_uniform(splitmix_at(seed, base + 4), kLog2_1e3, kLog2_1e9);
+        const uint32_t nt = (uint32_t)(counts >> (8u * p.b)) & 0xffu;
+        if (p.allocs && nt < (uint32_t)kSlots) {
+            al = p.size;
+            s_buf[p.b][nt][tid] = al;
+            counts += 1ull << (8u * p.b);
         }
         const size_t o = (size_t)j * N + (size_t)cand;
-        __builtin_nontemporal_store(code, g.code + o);
-        __builtin_nontemporal_store(fl, g.flops + o);
-        __builtin_nontemporal_store(by, g.bytes + o);
+        __builtin_nontemporal_store(p.code, g.code + o);
+        __builtin_nontemporal_store(p.fl, g.flops + o);
+        __builtin_nontemporal_store(p.by, g.bytes + o);
         __builtin_nontemporal_store(al, g.alloc + o);
         __builtin_nontemporal_store(fr, g.freeb + o);
+    };
+    // (two ops' draws together: about one wavefront runs per SIMD, and their
+    // products and polynomials fill one another's latencies)
+    int32_t j = 0;
+    for (; j + 1 < g.n_ops; j += 2, z += 64u * kGamma) {
+        const Op p0 = draw(z), p1 = draw(z + 32u * kGamma);
+        apply(p0, j);
+        apply(p1, j + 1);
     }
+    if (j < g.n_ops) apply(draw(z), j);
     if (g.n_ops_out) g.n_ops_out[cand] = (uint32_t)g.n_ops;
 }
 

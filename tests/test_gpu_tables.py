@@ -287,6 +287,19 @@ def test_generator_bit_exact(torch_gpu, orc, n_dev):
     assert np.all(G["n_ops"] == n_ops)
 
 
+@pytest.mark.parametrize("n_dev,n_cand,n_ops", [(2, 1, 1), (3, 63, 2), (4, 64, 3), (6, 65, 200), (7, 129, 130)])
+def test_generator_edges(torch_gpu, orc, n_dev, n_cand, n_ops):
+    """Odd and even op counts (draws go two ops at a time), partial
+    wavefronts, every other device count (the all-reduce's masks)."""
+    G = {k: v.cpu().numpy() for k, v in gen_gpu(torch_gpu, 5, n_cand, n_ops, n_dev).items() if v is not None}
+    for c in {0, n_cand // 2, n_cand - 1}:
+        o = orc.gen_table(5, c, n_ops, n_dev)
+        for k in ("code", "alloc", "free"):
+            assert np.array_equal(G[k][:, c].view(np.uint32), o[k]), (c, k)
+        for k in ("flops", "bytes"):
+            assert np.array_equal(G[k][:, c], o[k]), (c, k)
+
+
 def test_generated_tables_simulate_vs_oracle(torch_gpu, orc):
     from paper_2111_05426_amd import dsim
     from paper_2111_05426_amd.workloads import DeviceSpec
