@@ -162,8 +162,8 @@ _SIDE = []
 
 
 def side_stream(torch):
-    """The second stream of the split transform launch, created once (default
-    priority) so that every grid runs on the same pair of streams."""
+    """The second stream that dsim_simulate_parametric accepts (and leaves
+    unused), created once at the default priority."""
     if not _SIDE:
         _SIDE.append(torch.cuda.Stream())
     return _SIDE[0]
@@ -171,10 +171,10 @@ def side_stream(torch):
 
 # Vector issue rate of the chip: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane
 # instructions per second (a wave64 vector instruction occupies a 16-lane
-# SIMD for 4 cycles).  The transform's kernels are bound by dependent fp64
-# adds, Send-chain steps and wave-wide votes, i.e. by vector issue and its
-# latency, so their roofline is this rate and their achieved figure is the
-# vector instructions they execute (rocprofv3 SQ_INSTS_VALU, 64 lanes each)
+# SIMD for 4 cycles).  The transform's kernel is bound by the slots' schedule,
+# the Send-chain scans and steps and the block sums, i.e. by vector issue and
+# its latency, so its roofline is this rate and its achieved figure is the
+# vector instructions it executes (rocprofv3 SQ_INSTS_VALU, 64 lanes each)
 # per second of the live launch time.
 VALU_PEAK_T = 256 * 4 * 16 * 2.4e9 / 1e12
 PARAMETRIC_SRC = [os.path.join(ROOT, "paper_2111_05426_amd", "csrc", f) for f in ("parametric.hip", "model.h")]
@@ -212,7 +212,7 @@ def bench_parametric(torch, dsim, W, reps, warmup=1, cpu_budget_s=0.0):
     out_mk = torch.empty(k, dtype=torch.float64, device="cuda")
     found = torch.empty(1, dtype=torch.int32, device="cuda")
     pws = dsim.alloc_parametric_workspace(n)
-    side = side_stream(torch)   # the split launch of large transformer grids runs on two streams
+    side = side_stream(torch)
     dev = W.device
     ev = []
 
@@ -256,7 +256,7 @@ def bench_parametric(torch, dsim, W, reps, warmup=1, cpu_budget_s=0.0):
     achieved = rec["valu_insts_per_call"] * 64 / (kern_ms * 1e-3) / 1e12 if rec else None
     out["roofline"] = {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_T,
                        "unit": "T vector lane-instructions/s", "frac": achieved / VALU_PEAK_T if rec else None,
-                       "traffic": None, "kernel": "k_parametric + k_parametric_wide",
+                       "traffic": None, "kernel": "k_parametric",
                        "valu_insts_per_call": rec["valu_insts_per_call"] if rec else None,
                        "counters": rec["summary"] if rec else "not current for this source"}
     if cpu_budget_s > 0:

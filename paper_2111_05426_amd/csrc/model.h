@@ -185,10 +185,6 @@ __device__ __forceinline__ double cost_ar_dp(const Ctx &x, uint64_t bytes)
 {
     return x.arl_d + x.arc_d * ((double)bytes * x.inv_l_d);
 }
-__device__ __forceinline__ double cost_send(const Ctx &x, uint64_t bytes)
-{
-    return x.lat + (double)bytes * x.inv_l;
-}
 // a matrix multiplication of reduction length k: the empirical regression of
 // Sec. 4 when the device model carries one, the roofline otherwise
 __device__ __forceinline__ double cost_mm(const Ctx &x, uint64_t flops, uint64_t bytes, uint64_t k)

@@ -1,8 +1,9 @@
 // parametric.hip -- simulate the D/H/P/K transform without building op lists.
 //
-// Each candidate gets a segment of W = 2^ceil(log2 P) lanes of a wavefront,
-// one lane per pipeline stage; segments of equal width share wavefronts
-// (64 / W candidates each).  A lane expands, on the fly and in program order,
+// Each candidate gets a segment of W = 16, 32 or 64 lanes of a wavefront (the
+// least that holds its P stages), one lane per pipeline stage; segments of
+// equal width share wavefronts (64 / W candidates each), and in a small call
+// every candidate has a wavefront of its own.  A lane expands, on the fly and in program order,
 // the ops of its stage of the distributed program the transform of Sec. 4
 // produces (ops in model.h) and simulates them with the semantics of Sec. 2.1
 // and the cost model of Sec. 3.3:
@@ -1173,9 +1174,9 @@ __device__ __forceinline__ int64_t update_top(const Ctx &x, int s, const ZStage 
 // block adds are tabulated per candidate, and whole periods are skipped.
 // Against two launches (1-8 and 16-64 lanes) that walked every block's costs
 // and re-recorded a program whenever a lane's block kind changed: 39,965
-// GPT-3-shaped strategies 2.03 -> 1.09 ms, with ZeRO 3.10 -> 1.83, two-stream
-// 3.59 -> 1.42, 2,240 MLP ones 350 -> 152 us, 398 GPT-2-small-shaped training
-// ones 195 -> 110 us; vector instructions per GPT-3-shaped call 929M (before
+// GPT-3-shaped strategies 2.03 -> 1.06 ms, with ZeRO 3.10 -> 1.37, two-stream
+// 3.59 -> 1.31, 2,240 MLP ones 350 -> 149 us, 398 GPT-2-small-shaped training
+// ones 195 -> 105 us (selection and pre-pass included); vector instructions per GPT-3-shaped call 929M (before
 // either change) -> 527M, which keep the SIMDs' issue about 85% busy.
 template <bool TF, bool RC, bool ZR, bool OV>
 __device__ __forceinline__ void parametric_body(const ParArgs &g)
@@ -1920,7 +1921,7 @@ size_t parametric_workspace(int64_t n_cand)
 {
     const int64_t nb = (n_cand + kScanBlock - 1) / kScanBlock;
     // per-block class counts, the class table (32 words), the permutation,
-    // the wide launch's wavefront order and lengths (at most n_cand +
+    // the wavefronts' order and lengths (at most n_cand +
     // kClasses wavefronts each)
     return (size_t)(nb * 8 + 32 + 3 * n_cand + 16) * sizeof(uint32_t);
 }
