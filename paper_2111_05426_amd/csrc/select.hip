@@ -8,20 +8,23 @@
 // the number of smaller ones, which takes one pass of broadcast reads and no
 // rounds.  Calls of at most 1,024 keys are one block of that.  Larger ones
 // take two passes.  Pass 1: block b owns a contiguous chunk and writes its k
-// smallest (makespan, index) keys in order; chunks have 256 keys (ranked by
-// counting) while fewer than 256 blocks would run, and at most 512 blocks
-// run; in larger chunks each wavefront takes its least remaining key round by
-// round, the winning lane then looking for its next one, and the block's four
-// lists are merged by rank.  Pass 2: one block bounds the k-th smallest key
-// -- by the k-th smallest of the lists' heads and by the least of the lists'
-// k-th keys -- gathers the keys up to the bound (at most k from k lists) and
-// ranks them by counting.  The order is a total order on (makespan, index),
-// so the result does not depend on the launch shape.
+// smallest (makespan, index) keys in order; chunks have 256 keys while fewer
+// than 256 blocks would run, and at most 512 blocks run.  A chunk of 256 keys
+// is ranked by counting for k > 8; else each wavefront takes its least
+// remaining key round by round (in larger chunks the winning lane then looks
+// for its next one) and the block's four lists are merged by rank.  Pass 2:
+// one block bounds the k-th smallest key -- by the lists' heads, or by their
+// j-th keys where lists are few, and by the least of the lists' k-th keys --
+// gathers the keys up to the bound and ranks them by counting.  The order is
+// a total order on (makespan, index), so the result does not depend on the
+// launch shape.
 //
-// (With a block-wide minimum and a new scan of the chunk in each of k rounds,
-// and a merge of k rounds over the lists' heads: top-16 of 39,965 keys 21 +
-// 27 us, top-8 of 40,001 11 + 14, top-1 of a million 8.6 + 4.8, of 400 4.7 +
-// 4.6; now 10 + 14, 9 + 10, 7.9 + 4.9, and 3.9 in one.)
+// Bound by the two launches (6 us at k = 1) and by the counts.  Both passes,
+// us, with a block-wide minimum and a new scan of the chunk in each of k
+// rounds and a merge of k rounds -> now: 6,000 keys, k = 4 13.8 -> 11.2, 16
+// 44.8 -> 17.4, 64 167 -> 25; 100,000 keys 14.8 -> 12.9, 46.9 -> 19.4, 174 ->
+// 41; a million 23.8 -> 23.0, 82 -> 59, 316 -> 207.  (Counting every head for
+// small k as well: 100,000 keys, k = 4 26.2.)
 #include "internal.h"
 
 #include <math.h>
@@ -37,6 +40,8 @@ constexpr int kMaxK = 64;
 constexpr int64_t kChunk = 4096;
 constexpr int64_t kMinChunk = 256;
 constexpr int kMaxBlocks = 512;
+constexpr int kRowK = 16;     // 16 lists stand as one in the merge up to this k: 16 k^2 <= kMaxK^2 keys
+constexpr int kRoundK = 8;    // chunks of one key a thread take rounds up to this k
 constexpr int kFillBlocks = 256;   // one chunk per CU at least, while chunks stay >= kMinChunk
 constexpr int64_t kOneBlock = kMergeBlock;   // keys of a call without a second pass
 
@@ -237,7 +242,9 @@ __global__ __launch_bounds__(kSelBlock) void k_select_chunks(const double *mk, c
         if (t == 0) list[0] = Key{b.mk, b.idx == kNone ? -1 : b.idx};
         return;
     }
-    if (chunk == kSelBlock) {   // one key a thread
+    // one key a thread: counting takes one pass over 256 keys, the rounds
+    // below (without a second look at the chunk) a pass over 64 lanes each
+    if (chunk == kSelBlock && k > kRoundK) {
         static_assert(kSelWaves * kMaxK == kSelBlock, "a place for every thread's key");
         double *all = &s_m[0][0];
         const double v = lo + t < hi ? feasible(mk, pk, st, cap, lo + t) : __longlong_as_double(-1);
@@ -273,7 +280,14 @@ __global__ __launch_bounds__(kSelBlock) void k_select_chunks(const double *mk, c
             }
             break;
         }
-        if (lane == l && r + 1 < k) next(wm, wi, bm, bi);
+        if (lane == l && r + 1 < k) {
+            if (chunk == kSelBlock) {
+                bm = HUGE_VAL;
+                bi = kNone;
+            } else {
+                next(wm, wi, bm, bi);
+            }
+        }
     }
     __syncthreads();
     Key key{HUGE_VAL, -1};
@@ -287,7 +301,7 @@ __global__ __launch_bounds__(kMergeBlock) void k_select_merge(const Key *ws, int
                                                             int64_t *out_idx, double *out_mk,
                                                             int32_t *out_found)
 {
-    static_assert(kMaxBlocks <= kMergeBlock, "a thread for every list");
+    static_assert(16 * kRowK * kRowK <= kMaxK * kMaxK && kMaxBlocks <= kMergeBlock, "room for the gathered keys, a thread for every list");
     __shared__ double s_m[kMaxK * kMaxK];
     __shared__ int64_t s_i[kMaxK * kMaxK];
     __shared__ double s_wm[kMergeWaves];
@@ -309,20 +323,48 @@ __global__ __launch_bounds__(kMergeBlock) void k_select_merge(const Key *ws, int
     }
     Key tail = t < nl ? ws[(int64_t)t * k + k - 1] : none;
     if (tail.idx < 0) tail = none;
-    const bool has = head.idx != kNone;
-    if (t < nl) s_m[t] = has ? head.mk : __longlong_as_double(-1);
+    // Every list's j-th key: where p = ceil(k / j) of them lie at or below a
+    // key, so do k keys.  Few lists: a j that leaves about half the lists
+    // above the bound.
+    const int j = nl >= 2 * k ? 1 : (int)((2 * k + nl - 1) / nl);
+    const int p = (k + j - 1) / j;
+    Key mark = head;
+    if (j > 1) {
+        mark = t < nl && j <= k ? ws[(int64_t)t * k + j - 1] : none;
+        if (mark.idx < 0) mark = none;
+    }
+    const bool has = mark.idx != kNone;
+    // Many lists for few keys: the least of 16 lists stands for them (the
+    // gathered keys then come from 16 k lists at most, 16 k^2 keys), and a
+    // sixteenth of the keys is counted.
+    const bool rows = k <= kRowK && nl >= 16 * k;
+    bool lead = has;
+    if (rows) {
+        double v = mark.mk;
+        v = min_dpp<0x111, 0xf>(v);
+        v = min_dpp<0x112, 0xf>(v);
+        v = min_dpp<0x114, 0xf>(v);
+        v = min_dpp<0x118, 0xf>(v);
+        v = __shfl(v, (t & 63) | 15, 64);
+        const uint32_t at = (uint32_t)(__builtin_amdgcn_ballot_w64(has && mark.mk == v) >> (t & 48)) & 0xffffu;
+        lead = at != 0 && (t & 15) == __builtin_ctz(at);
+        if (lead || (at == 0 && (t & 15) == 0)) s_m[t / 16] = lead ? mark.mk : __longlong_as_double(-1);
+    } else if (t < nl) {
+        s_m[t] = has ? mark.mk : __longlong_as_double(-1);
+    }
     if (t == 0) {
         s_bound = none;
         s_n = 0;
     }
     const Key last = block_least<kMergeWaves>(tail.mk, tail.idx, s_wm, s_wi);   // (its barrier covers the stores above)
-    // lists hold ascending indices, so equal heads rank by their list
-    if (has && count_less(s_m, (int)nl, head.mk, t) == k - 1) s_bound = head;
+    // lists hold ascending indices, so equal keys rank by their list
+    const int place = rows ? t / 16 : t;
+    if (lead && count_less(s_m, rows ? (int)((nl + 15) / 16) : (int)nl, mark.mk, place) == p - 1) s_bound = mark;
     __syncthreads();
     Key bound = s_bound;
     if (key_less(last.mk, last.idx, bound.mk, bound.idx)) bound = last;
-    // the keys up to the bound: of at most k lists (or of all, if fewer than
-    // k have any), at most k each
+    // the keys up to the bound: of p lists (16 k at most) all k at most, of
+    // the others fewer than j
     for (int64_t q = t; q < nl * k; q += kMergeBlock) {
         const Key x = ws[q];
         if (x.idx >= 0 && !key_less(bound.mk, bound.idx, x.mk, x.idx)) {

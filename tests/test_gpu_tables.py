@@ -485,3 +485,12 @@ def test_argmin_orders_and_block_edges(torch_gpu, n, k, order):
     assert f == len(best)
     assert np.array_equal(idx.cpu().numpy()[:f], best) and np.array_equal(mo.cpu().numpy()[:f], mk[best])
     assert np.all(idx.cpu().numpy()[f:] == -1) and np.all(mo.cpu().numpy()[f:] == np.inf)
+
+
+@pytest.mark.parametrize("k,n", [(8, 1_500), (8, 32_767), (8, 32_769), (9, 40_000), (16, 65_280), (16, 65_537),
+                                 (16, 1_000_000), (17, 70_000), (40, 12_000)])
+@pytest.mark.parametrize("order", ["ascending", "descending", "equal", "sparse"])
+def test_argmin_bounds_of_the_merge(torch_gpu, k, n, order):
+    """Up to 8 keys by rounds, up to 16 bounded by 16 lists at a time (from
+    16 k lists on), few lists bounded by their second or later keys."""
+    test_argmin_orders_and_block_edges(torch_gpu, n, k, order)
