@@ -6,25 +6,28 @@
 //
 // Small sets are ranked by counting: with all keys in LDS, a key's place is
 // the number of smaller ones, which takes one pass of broadcast reads and no
-// rounds.  Calls of at most 1,024 keys are one block of that.  Larger ones
-// take two passes.  Pass 1: block b owns a contiguous chunk and writes its k
-// smallest (makespan, index) keys in order; chunks have 256 keys while fewer
-// than 256 blocks would run, and at most 512 blocks run.  A chunk of 256 keys
+// rounds.  Calls of at most 512 keys (640 for k > 32, 1,024 at k = 1) are one
+// block of that; beyond, the count costs more than a second launch (k = 4, us,
+// one block against two passes: 400 keys 13.3 / 13.9, 512 16.6 / 13.9, 1,024
+// 43 / 14).  Larger ones take two passes.  Pass 1: block b owns a contiguous
+// chunk and writes its k smallest (makespan, index) keys in order; chunks have
+// 256 keys while fewer than 256 blocks would run, and at most 1,024 blocks
+// run, of 512 threads from chunks of 4,096 keys on (16 million keys, top-16,
+// us: 512 blocks of 256 threads 1,352, 1,024 of 256 747, 1,024 of 512 429,
+// with the loads of four keys in flight 291).  A chunk of 256 keys
 // is ranked by counting for k > 8; else each wavefront takes its least
 // remaining key round by round (in larger chunks the winning lane then looks
-// for its next one) and the block's four lists are merged by rank.  Pass 2:
+// for its next one) and the block's lists are merged by rank.  Pass 2:
 // one block bounds the k-th smallest key -- by the lists' heads, or by their
 // j-th keys where lists are few, and by the least of the lists' k-th keys --
 // gathers the keys up to the bound and ranks them by counting.  The order is
 // a total order on (makespan, index), so the result does not depend on the
 // launch shape.
 //
-// Bound by the two launches (6 us at k = 1) and by the counts.  Both passes,
-// us, with a block-wide minimum and a new scan of the chunk in each of k
-// rounds and a merge of k rounds -> now: 6,000 keys, k = 4 13.8 -> 11.2, 16
-// 44.8 -> 17.4, 64 167 -> 25; 100,000 keys 14.8 -> 12.9, 46.9 -> 19.4, 174 ->
-// 41; a million 23.8 -> 23.0, 82 -> 59, 316 -> 207.  (Counting every head for
-// small k as well: 100,000 keys, k = 4 26.2.)
+// Bound by the two launches and by the counts.  A call, us, k = 4, 16, 64:
+// 3,000 keys 14, 18, 26; 65,536 14, 22, 34; a million 21, 52, 177; 16 million
+// 96, 291, 1,093.  (Counting every head for small k as well: 100,000 keys,
+// k = 4 26.2 against 12.9.)
 #include "internal.h"
 
 #include <math.h>
@@ -33,17 +36,19 @@ namespace dsim {
 namespace {
 
 constexpr int kSelBlock = 256;
-constexpr int kSelWaves = kSelBlock / 64;
+constexpr int kWideBlock = 512;   // for chunks of kChunk keys and more
 constexpr int kMergeBlock = 1024;
 constexpr int kMergeWaves = kMergeBlock / 64;
 constexpr int kMaxK = 64;
 constexpr int64_t kChunk = 4096;
 constexpr int64_t kMinChunk = 256;
-constexpr int kMaxBlocks = 512;
+constexpr int kMaxBlocks = 1024;
 constexpr int kRowK = 16;     // 16 lists stand as one in the merge up to this k: 16 k^2 <= kMaxK^2 keys
 constexpr int kRoundK = 8;    // chunks of one key a thread take rounds up to this k
 constexpr int kFillBlocks = 256;   // one chunk per CU at least, while chunks stay >= kMinChunk
-constexpr int64_t kOneBlock = kMergeBlock;   // keys of a call without a second pass
+// Keys of a call without a second pass: any number the block has threads for
+// at k = 1; else up to where counting costs what the second pass does
+constexpr int64_t one_block(int k) { return k == 1 ? kMergeBlock : (k <= 32 ? 512 : 640); }
 
 struct Key {
     double mk;
@@ -140,8 +145,10 @@ template <int W> __device__ __forceinline__ int rank_of(const double (&m)[W][kMa
 __device__ __forceinline__ double feasible(const double *mk, const uint64_t *pk, const int32_t *st, uint64_t cap,
                                            int64_t i)
 {
-    const bool ok = st[i] == 0 && (cap == 0 || pk[i] <= cap);
-    return ok ? mk[i] : __longlong_as_double(-1);
+    // (the loads do not wait for one another)
+    const double m = mk[i];
+    const uint64_t p = cap != 0 ? pk[i] : 0;
+    return st[i] == 0 && p <= cap ? m : __longlong_as_double(-1);
 }
 
 // how many of the n keys (m[j], j) are less than (v, t)
@@ -212,12 +219,13 @@ __global__ __launch_bounds__(kMergeBlock) void k_select_one(const double *mk, co
     if (t == 0) *out_found = found;
 }
 
-__global__ __launch_bounds__(kSelBlock) void k_select_chunks(const double *mk, const uint64_t *pk,
-                                                             const int32_t *st, int64_t n, uint64_t cap,
-                                                             int k, int64_t chunk, Key *ws)
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_select_chunks(const double *mk, const uint64_t *pk, const int32_t *st,
+                                                         int64_t n, uint64_t cap, int k, int64_t chunk, Key *ws)
 {
-    __shared__ double s_m[kSelWaves][kMaxK];
-    __shared__ int64_t s_i[kSelWaves][kMaxK];
+    constexpr int kWaves = BLOCK / 64;
+    __shared__ double s_m[kWaves][kMaxK];
+    __shared__ int64_t s_i[kWaves][kMaxK];
     const int t = threadIdx.x, wave = t / 64, lane = t % 64;
     const int64_t lo = (int64_t)blockIdx.x * chunk;
     const int64_t hi = lo + chunk < n ? lo + chunk : n;
@@ -226,7 +234,8 @@ __global__ __launch_bounds__(kSelBlock) void k_select_chunks(const double *mk, c
     auto next = [&](double pm, int64_t pi, double &bm, int64_t &bi) {
         bm = HUGE_VAL;
         bi = kNone;
-        for (int64_t i = lo + t; i < hi; i += kSelBlock) {
+#pragma unroll 4
+        for (int64_t i = lo + t; i < hi; i += BLOCK) {
             const double m = feasible(mk, pk, st, cap, i);
             if (key_less(pm, pi, m, i) && key_less(m, i, bm, bi)) {
                 bm = m;
@@ -238,29 +247,29 @@ __global__ __launch_bounds__(kSelBlock) void k_select_chunks(const double *mk, c
     int64_t bi;
     if (k == 1) {
         next(-HUGE_VAL, -1, bm, bi);
-        const Key b = block_least<kSelWaves>(bm, bi, &s_m[0][0], &s_i[0][0]);
+        const Key b = block_least<kWaves>(bm, bi, &s_m[0][0], &s_i[0][0]);
         if (t == 0) list[0] = Key{b.mk, b.idx == kNone ? -1 : b.idx};
         return;
     }
     // one key a thread: counting takes one pass over 256 keys, the rounds
     // below (without a second look at the chunk) a pass over 64 lanes each
-    if (chunk == kSelBlock && k > kRoundK) {
-        static_assert(kSelWaves * kMaxK == kSelBlock, "a place for every thread's key");
+    if (chunk == BLOCK && k > kRoundK) {
+        static_assert(kWaves * kMaxK == BLOCK, "a place for every thread's key");
         double *all = &s_m[0][0];
         const double v = lo + t < hi ? feasible(mk, pk, st, cap, lo + t) : __longlong_as_double(-1);
         const bool has = v == v;
         all[t] = v;
-        if (t < kSelWaves) s_i[0][t] = 0;
+        if (t < kWaves) s_i[0][t] = 0;
         __syncthreads();
         if (has) {
-            const int r = count_less(all, kSelBlock, v, t);
+            const int r = count_less(all, BLOCK, v, t);
             if (r < k) list[r] = Key{v, lo + t};
         }
         const int mine = __popcll(__builtin_amdgcn_ballot_w64(has));
         if (lane == 0) s_i[0][wave] = mine;
         __syncthreads();
         int have = 0;
-        for (int w = 0; w < kSelWaves; ++w) have += (int)s_i[0][w];
+        for (int w = 0; w < kWaves; ++w) have += (int)s_i[0][w];
         if (t >= have && t < k) list[t] = Key{HUGE_VAL, -1};
         return;
     }
@@ -281,7 +290,7 @@ __global__ __launch_bounds__(kSelBlock) void k_select_chunks(const double *mk, c
             break;
         }
         if (lane == l && r + 1 < k) {
-            if (chunk == kSelBlock) {
+            if (chunk == BLOCK) {
                 bm = HUGE_VAL;
                 bi = kNone;
             } else {
@@ -416,7 +425,7 @@ dsim_status launch_argmin(const double *mk, const uint64_t *pk, const int32_t *s
                           uint64_t cap, int32_t k, void *ws, int64_t *out_idx, double *out_mk,
                           int32_t *out_found, hipStream_t s)
 {
-    if (n <= kOneBlock) {
+    if (n <= one_block(k)) {
         hipLaunchKernelGGL(k_select_one, dim3(1), dim3(kMergeBlock), 0, s, mk, pk, st, (int)n, cap, k, out_idx, out_mk,
                            out_found);
         const hipError_t e = hipGetLastError();
@@ -425,8 +434,12 @@ dsim_status launch_argmin(const double *mk, const uint64_t *pk, const int32_t *s
     int64_t chunk;
     const int64_t blocks = n_chunks(n, &chunk);
     Key *w = static_cast<Key *>(ws);
-    hipLaunchKernelGGL(k_select_chunks, dim3((unsigned)blocks), dim3(kSelBlock), 0, s, mk, pk, st, n,
-                       cap, k, chunk, w);
+    if (chunk >= kChunk)
+        hipLaunchKernelGGL(k_select_chunks<kWideBlock>, dim3((unsigned)blocks), dim3(kWideBlock), 0, s, mk, pk, st, n,
+                           cap, k, chunk, w);
+    else
+        hipLaunchKernelGGL(k_select_chunks<kSelBlock>, dim3((unsigned)blocks), dim3(kSelBlock), 0, s, mk, pk, st, n,
+                           cap, k, chunk, w);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "select_chunks launch");
     hipLaunchKernelGGL(k_select_merge, dim3(1), dim3(kMergeBlock), 0, s, w, blocks, k, out_idx, out_mk, out_found);

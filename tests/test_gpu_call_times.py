@@ -1,0 +1,60 @@
+"""Ranges of a call's size in which it must not fall behind: each test compares
+two times of the same library on the same card, with a wide margin on either
+side (the figures in the docstrings are an MI355X's)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    from paper_2111_05426_amd import dsim
+    dsim.lib()
+    return torch
+
+
+def call_us(torch, call, reps=20, runs=7):
+    """The least mean time of a call among `reps` in a row."""
+    call()
+    best = np.inf
+    for _ in range(runs):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(reps):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / reps)
+    return best
+
+
+def selection(torch, n, k):
+    from paper_2111_05426_amd import dsim
+    g = torch.Generator(device="cuda").manual_seed(n)
+    mk = torch.rand(n, generator=g, device="cuda", dtype=torch.float64)
+    pk = torch.zeros(n, dtype=torch.int64, device="cuda")
+    st = torch.zeros(n, dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(dsim.dsim_argmin_workspace(n, k), 16), dtype=torch.uint8, device="cuda")
+    idx = torch.empty(k, dtype=torch.int64, device="cuda")
+    out = torch.empty(k, dtype=torch.float64, device="cuda")
+    found = torch.empty(1, dtype=torch.int32, device="cuda")
+    return lambda: dsim.dsim_argmin(mk, pk, st, 0, k, ws, idx, out, found)
+
+
+def test_selection_around_one_block(torch_gpu):
+    """1,024 keys cost about what 1,025 do (15 us; counted in one block they
+    took 43)."""
+    small, more = (call_us(torch_gpu, selection(torch_gpu, n, 4)) for n in (1024, 1025))
+    print("top-4 of 1,024: %.1f us, of 1,025: %.1f us" % (small, more))
+    assert small < 1.8 * more
+
+
+def test_selection_of_many_keys(torch_gpu):
+    """Sixteen times the keys cost far less than sixteen times as much (52 and
+    291 us; 1,352 with at most 512 blocks of 256 threads)."""
+    few, many = (call_us(torch_gpu, selection(torch_gpu, n, 16), 5) for n in (1_000_000, 16_000_000))
+    print("top-16 of a million: %.1f us, of 16 million: %.1f us" % (few, many))
+    assert many < 12 * few

@@ -459,12 +459,12 @@ def test_eight_lanes_and_one_lane_per_candidate(torch_gpu, n_dev, kinds):
             assert np.array_equal(big[k], small[k][at]), (total, k)
 
 
-@pytest.mark.parametrize("n", [2, 64, 1023, 1024, 1025, 65_536, 131_072, 131_073, 300_001])
+@pytest.mark.parametrize("n", [2, 64, 512, 513, 640, 641, 1023, 1024, 1025, 65_536, 131_072, 131_073, 300_001])
 @pytest.mark.parametrize("k", [1, 2, 63, 64])
 @pytest.mark.parametrize("order", ["ascending", "descending", "equal", "sparse"])
 def test_argmin_orders_and_block_edges(torch_gpu, n, k, order):
-    """Selection at the edges of its passes (1,024 keys in one block, 256-key
-    chunks up to 131,072 keys) on keys that crowd into few chunks (sorted
+    """Selection at the edges of its passes (512, 640 or 1,024 keys in one
+    block, 256-key chunks up to 131,072 keys) on keys that crowd into few chunks (sorted
     either way), on equal ones, and where few are feasible, +inf and -0.0
     among them; against a sort."""
     from paper_2111_05426_amd import dsim
@@ -488,9 +488,12 @@ def test_argmin_orders_and_block_edges(torch_gpu, n, k, order):
 
 
 @pytest.mark.parametrize("k,n", [(8, 1_500), (8, 32_767), (8, 32_769), (9, 40_000), (16, 65_280), (16, 65_537),
-                                 (16, 1_000_000), (17, 70_000), (40, 12_000)])
+                                 (16, 1_000_000), (17, 70_000), (40, 12_000), (32, 513), (33, 640), (3, 1_044_481),
+                                 (64, 2_097_153), (5, 4_194_305), (64, 4_200_001)])
 @pytest.mark.parametrize("order", ["ascending", "descending", "equal", "sparse"])
 def test_argmin_bounds_of_the_merge(torch_gpu, k, n, order):
     """Up to 8 keys by rounds, up to 16 bounded by 16 lists at a time (from
-    16 k lists on), few lists bounded by their second or later keys."""
+    16 k lists on), few lists bounded by their second or later keys; blocks of
+    512 threads (chunks of 4,096 keys and more, from 1,044,481 keys on), more
+    than 512 lists, chunks of 8,192."""
     test_argmin_orders_and_block_edges(torch_gpu, n, k, order)
