@@ -407,7 +407,8 @@ DSIM_API dsim_status dsim_simulate_parametric_static(const dsim_model *model, co
  *     exact in fp32, or an alloc / free size or a reduction length above
  *     2^32 - 1).
  * 1 <= n_dev <= 8, max_ops >= 0, n_cand <= 2^32 - 256.  One wavefront per
- * candidate.
+ * candidate, or eight lanes of one in calls of more than some thousand
+ * candidates and few rows.
  */
 DSIM_API dsim_status dsim_materialize_tables(const dsim_model *model, const dsim_strategy *cand, int64_t n_cand,
                                     int32_t max_ops, int32_t n_dev, uint32_t *code, float *flops,

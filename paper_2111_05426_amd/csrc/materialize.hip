@@ -1,7 +1,8 @@
 // materialize.hip -- write the whole distributed program of a strategy as an
 // explicit op table.
 //
-// One wavefront per candidate expands the transform of Sec. 4 for every device
+// One wavefront per candidate, or eight lanes of one in large calls of short
+// programs, expands the transform of Sec. 4 for every device
 // (device p*(D*H) + d*H + h runs stage p of data replica d, tensor rank h)
 // in a program order whose per-device projections are those of the
 // transform (Sec. 2.1 semantics depend on nothing else): the splits, then
@@ -190,30 +191,43 @@ struct Item {
     uint16_t s;
     uint8_t bwd, send;
 };
-constexpr int kItems = kLanes + 2 * kMaxTableDev;   // a slot adds at most two per stage
 
-__global__ __launch_bounds__(kLanes) void k_materialize(const MatArgs g)
+// G lanes per candidate; kLanes / G neighbouring candidates share a wavefront.
+template <int G> __global__ __launch_bounds__(kLanes) void k_materialize(const MatArgs g)
 {
-    __shared__ Item s_item[kItems];
-    const int lane = threadIdx.x;
-    const int64_t c = g.c0 + (int64_t)blockIdx.x;
-    const dsim_strategy st = g.cand[c];
+    static_assert(G >= kMaxTableDev && kLanes % G == 0, "a lane for every stage");
+    constexpr int kPer = kLanes / G;
+    constexpr int kItems = G + 2 * kMaxTableDev;        // a slot adds at most two per stage
+    __shared__ Item s_item[kPer][kItems];
+    const int lane = threadIdx.x % G, sub = G == kLanes ? 0 : threadIdx.x / G;
+    // Workgroups go round the XCDs in turn: 32 neighbouring candidates, whose
+    // records share cache lines, on one XCD, so that its L2 puts their words
+    // together (64,000 MLP strategies of 465 records on average: 3.7 -> 1.8 ms)
+    constexpr uint32_t kNear = 32 / kPer, kTurn = 8 * kNear;
+    uint32_t b = blockIdx.x;
+    if (b < gridDim.x / kTurn * kTurn) b = b / kTurn * kTurn + b % 8 * kNear + b / 8 % kNear;
+    const int64_t c = g.c0 + (int64_t)b * kPer + sub;
+    dsim_strategy st = {1, 1, 1, 1};
+    if (c < g.n_cand) st = g.cand[c];
     const int S = g.m.overlap ? 2 : 1;
-    const bool ok = strategy_ok(g.m, st.D, st.H, st.P, st.K) && st.K <= kMaxK &&
+    const bool ok = c < g.n_cand && strategy_ok(g.m, st.D, st.H, st.P, st.K) && st.K <= kMaxK &&
                     (int64_t)S * st.D * st.H * st.P <= (int64_t)g.n_dev;
-    if (!ok) {
+    if (c < g.n_cand && !ok) {
         if (lane < g.n_dev) g.init_live[c * g.n_dev + lane] = 0;
         if (lane == 0) {
             g.n_ops[c] = 0;
             g.status[c] = DSIM_ST_BAD_STRATEGY;
         }
-        return;
+    }
+    if (!ok) {
+        if (G == kLanes) return;
+        st = dsim_strategy{1, 1, 1, 1};   // (takes part in the wavefront's loops with no stage)
     }
     CostConsts none = {};
     Ctx x = {};
     make_ctx(g.m, none, st, x);
     const int DH = x.D * x.H;
-    if (lane < g.n_dev) {
+    if (ok && lane < g.n_dev) {
         // a communication stream, and a device beyond the program's, holds nothing
         const int gpu = lane / S, s = gpu / DH;
         uint64_t r0 = 0;
@@ -233,7 +247,7 @@ __global__ __launch_bounds__(kLanes) void k_materialize(const MatArgs g)
     // records of this lane's stage: a forward block, the backward blocks of
     // microbatch 0, of the last one and of the others, the weight update
     const int s = lane;
-    const bool stage = s < x.P;
+    const bool stage = ok && s < x.P;
     int64_t n_f = 0, n_b0 = 0, n_b1 = 0, n_bl = 0, n_wu = 0;
     if (stage) {
         RecordCount f{x, 0}, b0{x, 0}, b1{x, 0}, bl{x, 0}, w{x, 0};
@@ -254,17 +268,21 @@ __global__ __launch_bounds__(kLanes) void k_materialize(const MatArgs g)
     auto before = [&](int64_t v, int64_t &total) {
         int64_t sum = v;
         for (int o = 1; o < kMaxTableDev; o <<= 1) {
-            const int64_t up = __shfl_up(sum, o, kLanes);
+            const int64_t up = __shfl_up(sum, o, G);
             sum += lane >= o ? up : 0;
         }
-        total = __shfl(sum, kMaxTableDev - 1, kLanes);
+        total = __shfl(sum, kMaxTableDev - 1, G);
         return sum - v;
     };
+    // whether any candidate of the wavefront is in p (the same for all lanes
+    // of one), and the candidate's lanes for which p holds
+    auto any = [](bool p) { return G == kLanes ? p : __ballot(p) != 0; };
+    auto lanes = [&](bool p) { return (uint64_t)__ballot(p) >> (sub * G) & (~0ull >> (64 - G)); };
 
     Emit e{x, g, c, 0, false, 0, 0, 0, S};
     // microbatch splits before the pipeline: one lane each
     int64_t at = 0;
-    if (x.K > 1) {
+    if (ok && x.K > 1) {
         if (lane == 0) {
             split(x, e);
         } else if (lane == 1 && x.train) {
@@ -279,26 +297,28 @@ __global__ __launch_bounds__(kLanes) void k_materialize(const MatArgs g)
     // forwards before the first backward (synchronous 1F1B; all otherwise)
     const int warm = (x.train && x.schedule != DSIM_SCHED_GPIPE && x.P - 1 - s < x.K) ? x.P - 1 - s : x.K;
     int nf = 0, nb = 0, n = 0;
-    bool stuck = false;
-    for (bool more = true; more;) {
+    bool stuck = false, more = ok;
+    // (the loops' conditions are the wavefront's: a candidate that has ended
+    // takes part with no stage ready and nothing to write)
+    while (any(more)) {
         // one slot of the schedule
         const bool bwd = nf == x.K || nf - nb > warm;
         const int k = bwd ? nb : nf;
-        const int left = __shfl_up(nf, 1, kLanes), right = __shfl_down(nb, 1, kLanes);
+        const int left = __shfl_up(nf, 1, G), right = __shfl_down(nb, 1, G);
         const int avail = bwd ? (s == x.P - 1 ? nf : right) : (s == 0 ? INT32_MAX : left);
         const bool ready = nf + nb < len && avail > k;
-        const uint64_t run = __ballot(ready);
+        const uint64_t run = lanes(ready);
         const bool sends = ready && (bwd ? s > 0 : s < x.P - 1);
-        const uint64_t out = __ballot(sends), below = (1ull << lane) - 1ull;
+        const uint64_t out = lanes(sends), below = (1ull << lane) - 1ull;
         int64_t total;
         const int64_t mine = !ready ? 0 : (!bwd ? n_f : (k == 0 ? n_b0 : (k == x.K - 1 ? n_bl : n_b1)));
         const int64_t ahead = before(mine, total);
-        if (ready) s_item[n + __popcll(run & below)] = Item{at + ahead, k, (uint16_t)s, (uint8_t)bwd, 0};
+        if (ready) s_item[sub][n + __popcll(run & below)] = Item{at + ahead, k, (uint16_t)s, (uint8_t)bwd, 0};
         n += __popcll(run);
         at += total;
         if (sends) {
             const int p = __popcll(out & below);
-            s_item[n + p] = Item{at + (int64_t)p * DH, k, (uint16_t)s, (uint8_t)bwd, 1};
+            s_item[sub][n + p] = Item{at + (int64_t)p * DH, k, (uint16_t)s, (uint8_t)bwd, 1};
         }
         n += __popcll(out);
         at += (int64_t)__popcll(out) * DH;
@@ -306,16 +326,15 @@ __global__ __launch_bounds__(kLanes) void k_materialize(const MatArgs g)
             if (bwd) ++nb;
             else ++nf;
         }
-        more = __ballot(nf + nb < len) != 0;
-        stuck = more && run == 0;   // no stage can proceed: impossible for these schedules
-        more = more && !stuck;
-        if (n < kLanes && more) continue;
-        // write up to 64 of them
-        do {
+        const bool rest_of_it = more && lanes(nf + nb < len) != 0;
+        stuck = stuck || (rest_of_it && run == 0);   // no stage can proceed: impossible for these schedules
+        more = rest_of_it && !stuck;
+        // write up to G of each candidate's, once one has so many or has ended
+        while (any(n >= G || (!more && n > 0))) {
             __syncthreads();
-            const int now = n < kLanes ? n : kLanes;
+            const int now = n < G ? n : G;
             if (lane < now) {
-                const Item it = s_item[lane];
+                const Item it = s_item[sub][lane];
                 if (it.at < (int64_t)g.max_ops) {   // (beyond, the program does not fit anyway)
                     e.j = it.at;
                     e.base = it.s * DH;
@@ -332,13 +351,17 @@ __global__ __launch_bounds__(kLanes) void k_materialize(const MatArgs g)
                 }
             }
             __syncthreads();
-            Item rest;
-            const bool moves = lane < n - now;
-            if (moves) rest = s_item[now + lane];
-            __syncthreads();
-            if (moves) s_item[lane] = rest;
+            // (what is left moves to the front, up to G at a time)
+            for (int m0 = 0; m0 < kItems - G; m0 += G) {
+                const int m = m0 + lane;
+                Item rest;
+                const bool moves = m < n - now;
+                if (moves) rest = s_item[sub][now + m];
+                __syncthreads();
+                if (moves) s_item[sub][m] = rest;
+            }
             n -= now;
-        } while (!more && n > 0);
+        }
     }
     int64_t total;
     const int64_t ahead = before(n_wu, total);
@@ -349,13 +372,26 @@ __global__ __launch_bounds__(kLanes) void k_materialize(const MatArgs g)
         weight_update(x, e, s);
     }
     at += total;
-    const bool inexact = __ballot(e.inexact) != 0;
-    if (lane == 0) {
+    const bool inexact = lanes(e.inexact) != 0;
+    if (ok && lane == 0) {
         const bool fits = at <= (int64_t)g.max_ops && !inexact;
         g.n_ops[c] = fits && !stuck ? (uint32_t)at : 0u;
         g.status[c] = stuck ? DSIM_ST_BAD_STRATEGY : (fits ? 0 : DSIM_ST_NOT_TABLE);
     }
 }
+
+// Tables of at most kGroupOps rows for more than kGroupCand candidates take
+// eight lanes each: the lanes of a wavefront of its own would mostly idle,
+// there are more than enough wavefronts, and eight neighbours' words of a
+// record are written together.  Programs of 146 records on average (440 rows),
+// us, 64 lanes against eight: 4,000 candidates 95 / 107, 8,000 149 / 108,
+// 16,000 253 / 185, 64,000 920 / 700; 64,000 equal ones of 60 records 739 /
+// 122.  With longer ones an eight-lane chain is too long, and the candidates
+// of a wavefront wait for each other: 290 on average (1,160 rows), 16,000
+// candidates 258 / 330, 64,000 897 / 1,250.
+constexpr int kGroup = 8;
+constexpr int32_t kGroupOps = 512;
+constexpr int64_t kGroupCand = 8192;
 
 }  // namespace
 
@@ -379,12 +415,16 @@ dsim_status launch_materialize(const dsim_model &m, const dsim_strategy *cand, i
     g.n_ops = n_ops;
     g.init_live = init_live;
     g.status = status;
+    const bool group = max_ops <= kGroupOps && n_cand > kGroupCand;
+    const int64_t per = group ? kLanes / kGroup : 1;
     // (one dispatch holds fewer than 2^32 lanes)
     constexpr int64_t kMaxBlocks = (int64_t)1 << 25;
     hipError_t e = hipSuccess;
-    for (g.c0 = 0; g.c0 < n_cand && e == hipSuccess; g.c0 += kMaxBlocks) {
-        const int64_t blocks = n_cand - g.c0 < kMaxBlocks ? n_cand - g.c0 : kMaxBlocks;
-        hipLaunchKernelGGL(k_materialize, dim3((unsigned)blocks), dim3(kLanes), 0, s, g);
+    for (g.c0 = 0; g.c0 < n_cand && e == hipSuccess; g.c0 += kMaxBlocks * per) {
+        const int64_t want = (n_cand - g.c0 + per - 1) / per;
+        const dim3 blocks((unsigned)(want < kMaxBlocks ? want : kMaxBlocks));
+        if (group) hipLaunchKernelGGL(k_materialize<kGroup>, blocks, dim3(kLanes), 0, s, g);
+        else hipLaunchKernelGGL(k_materialize<kLanes>, blocks, dim3(kLanes), 0, s, g);
         e = hipGetLastError();
     }
     return e == hipSuccess ? DSIM_OK : hip_fail(e, "materialize launch");

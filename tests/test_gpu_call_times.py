@@ -58,3 +58,28 @@ def test_selection_of_many_keys(torch_gpu):
     few, many = (call_us(torch_gpu, selection(torch_gpu, n, 16), 5) for n in (1_000_000, 16_000_000))
     print("top-16 of a million: %.1f us, of 16 million: %.1f us" % (few, many))
     assert many < 12 * few
+
+
+@pytest.mark.parametrize("name", ["equal", "grid"])
+def test_materialize_many_programs(torch_gpu, name):
+    """64,000 programs are written in a small multiple of the time of filling
+    their words: equal ones of 108 records 6 times (139 us; 29 times with a
+    wavefront each), a grid of 465 records on average 18 times (1.8 ms; 39
+    times with neighbours on different XCDs)."""
+    from paper_2111_05426_amd import dsim
+    from paper_2111_05426_amd.workloads import GridSpec, TRAIN_SGD, mlp
+    torch = torch_gpu
+    n, model = 64_000, mlp(4, 256, 512, 4, TRAIN_SGD)
+    grid = dsim.dsim_create_grid(model, GridSpec(8, 0, 1, 8))
+    strat = grid[np.arange(n) % len(grid)] if name == "grid" else np.tile(np.array([[2, 1, 1, 2]], np.int32), (n, 1))
+    cand = torch.from_numpy(np.ascontiguousarray(strat)).cuda()
+    rows = 1720 if name == "grid" else 110
+    t, status = dsim.dsim_materialize_tables(model, cand, 8, rows)
+    assert not status.any()
+    words = 6 * int(t["n_ops"].long().sum().item())
+    del t
+    fill = torch.empty(words, dtype=torch.int32, device="cuda")
+    base = call_us(torch, lambda: fill.fill_(1), 10)
+    took = call_us(torch, lambda: dsim.dsim_materialize_tables(model, cand, 8, rows), 3, 5)
+    print("%s: %d words, filled in %.1f us, written in %.1f us" % (name, words, base, took))
+    assert took < (28 if name == "grid" else 14) * base

@@ -260,3 +260,43 @@ def test_long_schedules(torch_gpu, orc, family, option):
     # one record too few for the longest program: that one does not fit, the others do
     g = materialize_and_simulate(torch_gpu, model, strat, dev, n_dev, max_ops - 1)
     assert np.array_equal(g["mat_status"] == ST_NOT_TABLE, o["n_ops"] == max_ops)
+
+
+# Many short programs are written by eight lanes each (tables of at most 512
+# rows for more than 8,192 candidates), the others by a wavefront each, with
+# neighbours kept on one XCD: the same words as a small call writes, which the
+# tests above compare with the oracle.
+@pytest.mark.parametrize("max_ops", [511, 512, 513])
+@pytest.mark.parametrize("option", ["plain", "gpipe", "recompute", "zero", "overlap", "infer"])
+@pytest.mark.parametrize("family", ["mlp", "tf"])
+def test_many_programs(torch_gpu, family, option, max_ops):
+    from paper_2111_05426_amd import dsim
+    torch = torch_gpu
+    kw = {"gpipe": dict(schedule=SCHED_GPIPE), "plain": {}, "infer": {}}.get(option, {option: 1})
+    mode = INFER if option == "infer" else TRAIN_ADAM
+    model = mlp(8, 64, 96, 2, mode, **kw) if family == "mlp" else transformer(4, 32, 4, 8, 64, 96, 2, mode, **kw)
+    n_dev = 8
+    # programs that fit, that do not, and strategies with too many devices,
+    # stages or microbatches
+    strat = np.array([(d, h, p, k) for d in (1, 2, 3, 5, 8) for h in (1, 2, 4) for p in (1, 2, 4, 8)
+                      for k in (1, 2, 5, 12, 97)], np.int32)
+
+    def tables(rows):
+        t, status = dsim.dsim_materialize_tables(model, torch.from_numpy(np.ascontiguousarray(rows)).cuda(), n_dev, max_ops)
+        torch.cuda.synchronize()
+        return t, status
+
+    t0, st0 = tables(strat)
+    seen = set(st0.cpu().numpy().tolist())
+    assert {0, ST_BAD_STRATEGY} <= seen and (ST_NOT_TABLE in seen or option == "infer")
+    at = np.random.default_rng(7).permutation(np.arange(8193 + 70) % len(strat))
+    at[1000:1100] = at[1000]            # equal neighbours too
+    for n in (8193, len(at)):
+        pick = torch.from_numpy(at[:n]).cuda()
+        t, st = tables(strat[at[:n]])
+        assert torch.equal(st, st0[pick])
+        assert torch.equal(t["n_ops"], t0["n_ops"][pick]) and torch.equal(t["init_live"], t0["init_live"][pick])
+        live = torch.arange(max_ops, device="cuda")[:, None] < t["n_ops"][None, :]
+        for k in ("code", "flops", "bytes", "alloc", "free", "mm_k"):
+            a, b = t[k].view(torch.int32), t0[k].view(torch.int32)[:, pick]
+            assert torch.equal(torch.where(live, a, 0), torch.where(live, b, 0)), k
