@@ -348,8 +348,8 @@ DSIM_API dsim_status dsim_simulate_tables(const dsim_tables *tables, int64_t n_c
  * DSIM_ENOSPC if shorter), owned by the caller, in use until hip_stream has
  * passed the call; no word of it needs clearing (calls of at most 4,096
  * candidates check it but do not use it).  Every kernel runs on hip_stream;
- * side_stream is accepted and not used (one kernel simulates every
- * candidate).  n_cand < 2^31, and n_cand * W below
+ * side_stream is accepted and not used (strategies of few stages in large
+ * calls have a kernel of their own, before the others').  n_cand < 2^31, and n_cand * W below
  * 2^32 - 2^9 lanes, W = min(row_width, 64, n_layers) rounded up to a power
  * of two (DSIM_ERANGE otherwise: split the call).
  */

@@ -83,3 +83,24 @@ def test_materialize_many_programs(torch_gpu, name):
     took = call_us(torch, lambda: dsim.dsim_materialize_tables(model, cand, 8, rows), 3, 5)
     print("%s: %d words, filled in %.1f us, written in %.1f us" % (name, words, base, took))
     assert took < (28 if name == "grid" else 14) * base
+
+
+@pytest.mark.parametrize("family,k_max", [("mlp", 4), ("mlp", 64), ("tf", 4), ("tf", 64)])
+def test_many_strategies_of_few_stages(torch_gpu, family, k_max):
+    """100,000 strategies of one stage take far less than as many of sixteen
+    (up to 4 microbatches: MLP 50 us, transformer 63; up to 64: 93 and 138; with
+    sixteen lanes each 389, 480, 583 and 687, as long as of sixteen stages)."""
+    from paper_2111_05426_amd import dsim
+    from paper_2111_05426_amd.workloads import DeviceSpec, TRAIN_ADAM, TRAIN_ADAM_MIXED, mlp, transformer
+    torch = torch_gpu
+    model = mlp(16, 1024, 8192, 2, TRAIN_ADAM) if family == "mlp" else transformer(24, 1024, 16, 1024, 50257, 4096, 2, TRAIN_ADAM_MIXED)
+    n, took = 100_000, {}
+    for P in (1, 16):
+        grid = np.array([(D, H, P, K) for K in range(1, k_max + 1) for H in (1, 2) for D in (1, 2, 4, 8, 16, 32, 64)
+                         if P == 1 or H == 1 or family == "tf"], np.int32)
+        cand = torch.from_numpy(np.ascontiguousarray(grid[(np.arange(n) * len(grid)) // n])).cuda()
+        r, ws = dsim.alloc_results(n, P), dsim.alloc_parametric_workspace(n)
+        took[P] = call_us(torch, lambda: dsim.dsim_simulate_parametric(model, cand, DeviceSpec(), r, workspace=ws), 5, 5)
+        assert not (r["status"] != 0).any()
+    print("%s, K <= %d: one stage %.1f us, sixteen %.1f us" % (family, k_max, took[1], took[16]))
+    assert took[1] < 0.5 * took[16]

@@ -35,7 +35,7 @@ _SIDE = []
 
 
 def side_stream(torch):
-    """One second stream (default priority) for the split launch."""
+    """One second stream (default priority), which the calls accept."""
     if not _SIDE:
         _SIDE.append(torch.cuda.Stream())
     return _SIDE[0]
@@ -342,10 +342,9 @@ def test_gpt3_grid_selection(torch_gpu, gpt3_runs, key):
 
 @pytest.mark.parametrize("w", [GPT3_175B, ALL["gpt3_175b_zero"], ALL["gpt3_175b_overlap"]],
                          ids=["1f1b", "zero", "overlap"])
-def test_split_launch_on_one_stream(torch_gpu, w):
-    """The two kernels of a large transformer grid side by side (a second
-    stream) or one after the other on the caller's stream: the same results,
-    bit for bit, and a workspace reused by a second, smaller call."""
+def test_workspace_reuse_and_side_stream(torch_gpu, w):
+    """A second stream changes nothing (the call accepts and ignores it), and a
+    workspace can be used again by a second, smaller call."""
     from paper_2111_05426_amd import dsim
     strat = dsim.dsim_create_grid(w.model, w.grid)
     a = run_gpu(torch_gpu, w.model, strat, w.device, 64, side=True)
@@ -355,6 +354,7 @@ def test_split_launch_on_one_stream(torch_gpu, w):
     # one workspace for two calls in a row, the second smaller
     ws = dsim.alloc_parametric_workspace(len(strat))
     sub = strat[::3]
+    assert len(sub) > 4096   # (smaller calls do not touch it)
     for part in (strat, sub):
         r = dsim.alloc_results(len(part), 64)
         dsim.dsim_simulate_parametric(w.model, torch_gpu.from_numpy(np.ascontiguousarray(part)).cuda(), w.device,
@@ -528,3 +528,71 @@ def test_repeated_periods(torch_gpu, orc, case, dev):
     o = orc.run_strategies(model, strat, d, slice=True, row_width=g["finish"].shape[1], threads=8)
     assert np.any(o["status"] == 0)
     compare(g, o, strat)
+
+
+# Calls of more than 4,096 strategies share wavefronts: 16, 32 or 64 lanes a
+# strategy, several binades, size classes and skipped periods side by side;
+# and, where strategies of few stages are many, the narrow launch, 1 to 8 lanes
+# each with programs of their own.  One strategy's results do not depend on
+# that: every call below is compared bit for bit with a small call of the same
+# strategies (a wavefront each), and that one with the oracle on a sample.
+SHARED_OPTIONS = {"infer": dict(mode=INFER), "sgd": dict(mode=TRAIN_SGD), "adam": dict(mode=TRAIN_ADAM),
+                  "gpipe": dict(mode=TRAIN_ADAM, schedule=SCHED_GPIPE), "rc": dict(mode=TRAIN_ADAM_MIXED, recompute=1),
+                  "zero": dict(mode=TRAIN_ADAM, zero=1), "overlap": dict(mode=TRAIN_ADAM, overlap=1),
+                  "rc_zero": dict(mode=TRAIN_SGD, recompute=1, zero=1),
+                  "rc_overlap": dict(mode=TRAIN_ADAM, recompute=1, overlap=1),
+                  "gpipe_rc_overlap": dict(mode=TRAIN_SGD, schedule=SCHED_GPIPE, recompute=1, overlap=1)}
+SHARED_DEVICES = EDGE_DEVICES + [("calibrated", ALL["gpt3_175b_mi355x"].device)]
+# (largest P, largest K, strategies, in grid order): the shared 16 to 64 lanes;
+# large ones with many of few stages beside them; the narrow launch alone, few
+# microbatches or many; with segments of 8 lanes
+SHARED_CALLS = [(40, 20_000, 4_099, False), (40, 7, 8_001, True), (40, 8, 41_003, False), (40, 20_000, 150_001, False),
+                (4, 8, 4_097, False), (4, 20_000, 24_577, False), (4, 120, 9_001, True), (8, 8, 12_289, False),
+                (8, 120, 30_001, True), (8, 8, 70_001, False)]
+
+
+@pytest.mark.parametrize("dev", SHARED_DEVICES, ids=[d[0] for d in SHARED_DEVICES])
+@pytest.mark.parametrize("option", list(SHARED_OPTIONS))
+@pytest.mark.parametrize("family", ["mlp", "tf"])
+def test_shared_wavefronts(torch_gpu, orc, family, option, dev):
+    from paper_2111_05426_amd import dsim
+    torch = torch_gpu
+    kw = dict(SHARED_OPTIONS[option])
+    mode = kw.pop("mode")
+    model = mlp(48, 64, 240, 4, mode, **kw) if family == "mlp" else transformer(41, 32, 4, 8, 101, 240, 2, mode, **kw)
+    d = replace(dev[1], **OVERLAP_DEVICE) if model.overlap else dev[1]
+    # in a grid's order (P, K, H, D), with invalid ones of every sort among them
+    strat = np.array([(D, H, P, K) for P in (-1, 1, 2, 3, 4, 5, 8, 16, 17, 24, 40, 70) for K in (0, 1, 2, 3, 7, 8, 41, 80, 119, 120, 20000)
+                      for H in (1, 2, 4) for D in (0, 1, 2, 3, 6)], np.int32)
+    fields = ("makespan", "finish", "peak", "cand_peak", "n_ops", "walked_ops", "status")
+
+    def call(rows, rw):
+        r = dsim.alloc_results(len(rows), rw)
+        ws = dsim.alloc_parametric_workspace(len(rows))
+        ws.fill_(0xCD)
+        for k in fields:
+            r[k].fill_(-7)
+        dsim.dsim_simulate_parametric(model, torch.from_numpy(np.ascontiguousarray(rows)).cuda(), d, r, workspace=ws)
+        return r
+
+    for p_max, k_max, n, ordered in SHARED_CALLS:
+        # strategies beyond the call's P and K stay in as a few invalid ones
+        some = (strat[:, 2] <= p_max) & (strat[:, 3] <= k_max)
+        mine = np.concatenate([strat[some], strat[(strat[:, 2] > p_max) & (strat[:, 3] == 8)][:9]])
+        assert len(mine) <= 4096
+        small = call(mine, p_max)
+        at = (np.arange(n) * len(mine)) // n if ordered else np.random.default_rng(n).permutation(np.arange(n) % len(mine))
+        big = call(mine[at], p_max)
+        pick = torch.from_numpy(at).cuda()
+        for k in fields:
+            # (bits: some times are +inf)
+            a, b = big[k].view(torch.int64 if big[k].dtype == torch.float64 else big[k].dtype), small[k][pick]
+            assert torch.equal(a, b.view(a.dtype)), (p_max, k_max, n, k)
+        if (p_max, k_max) in ((40, 20_000), (8, 120)):
+            status = small["status"].cpu().numpy()
+            assert np.any(status != 0) and np.any(status == 0)
+            ok = np.nonzero(status == 0)[0]
+            ok = ok[::max(1, len(ok) // 12)]
+            o = orc.run_strategies(model, mine[ok], d, slice=True, row_width=p_max, threads=THREADS)
+            g = {k: v.cpu().numpy()[ok] for k, v in small.items() if k != "row_width"}
+            compare(g, o, mine[ok])
