@@ -109,7 +109,7 @@ def test_tables_vs_oracle(torch_gpu, orc, n_dev, bad, kinds):
     rooted, classes, net = kinds in ("bcast_reduce", "network", "streams"), kinds == "matmul", kinds == "network"
     streams = kinds == "streams"
     rng = np.random.default_rng(1000 + n_dev + 17 * bad + 101 * rooted + 211 * classes + 307 * net + 401 * streams)
-    n_cand, max_ops = 777, 301   # several 256-lane blocks and a ragged tail
+    n_cand, max_ops = 777, 301   # eight lanes each: 98 wavefronts, the last one partial
     t = random_tables(rng, n_cand, max_ops, n_dev, bad, rooted, classes)
     # the MatMul regression with its reduction-length term and a floor that
     # binds on part of the records (the floor above c0 + the smallest terms)
@@ -147,11 +147,12 @@ def test_tables_vs_oracle(torch_gpu, orc, n_dev, bad, kinds):
 
 @pytest.mark.parametrize("n_dev", [3, 8])
 def test_tables_long_op_counts_and_large_resident_bytes(torch_gpu, orc, n_dev):
-    """Lanes whose op count exceeds max_ops are flagged (DSIM_ST_BAD_OP) and
-    simulate max_ops ops, also when another op of theirs (a broadcast or
-    reduce record, a free that would underflow) sends them to the exact
-    path; lanes starting with 2^62 or more live bytes on a device keep exact
-    integer peaks.  Against the oracle on the first max_ops ops."""
+    """Candidates whose op count exceeds max_ops are flagged (DSIM_ST_BAD_OP)
+    and simulate max_ops ops, with broadcast and reduce records, invalid ops
+    and frees that would underflow among them; those starting with 2^62 or more
+    live bytes on a device keep exact integer peaks.  Against the oracle on the
+    first max_ops ops (eight lanes per candidate; the larger calls' kernel is
+    compared with this one below)."""
     from paper_2111_05426_amd import dsim
     from paper_2111_05426_amd.workloads import DeviceSpec
     torch = torch_gpu
@@ -186,7 +187,9 @@ def test_tables_long_op_counts_and_large_resident_bytes(torch_gpu, orc, n_dev):
 @pytest.mark.parametrize("n_dev", [3, 8])
 def test_tables_overflowing_costs(torch_gpu, orc, n_dev):
     """Valid rates so slow that op costs and clocks overflow to +inf: both
-    sides reach the same infinite (and finite) times, and no NaN appears."""
+    sides reach the same infinite (and finite) times, and no NaN appears (eight
+    lanes per candidate; the larger calls' kernel is compared with this one
+    below)."""
     from paper_2111_05426_amd import dsim
     from paper_2111_05426_amd.workloads import DeviceSpec
     torch = torch_gpu
@@ -216,7 +219,7 @@ def test_tables_overflowing_costs(torch_gpu, orc, n_dev):
 def test_tables_largest_fast_path_and_beyond(torch_gpu, orc, n_cand):
     """The largest table the fast path takes (its loads reach four op rows,
     16 * n_cand bytes, through 32-bit offsets) and one candidate more, which
-    the op-by-op path takes: sampled candidates, first and last included,
+    the general path takes: sampled candidates, first and last included,
     against the oracle.  About 40 GB of tables, built on the GPU."""
     from paper_2111_05426_amd import dsim
     from paper_2111_05426_amd.workloads import DeviceSpec
@@ -420,27 +423,40 @@ def test_empty_inputs(torch_gpu):
     assert np.all(r["makespan"].cpu().numpy() == 0) and np.all(r["status"].cpu().numpy() == 0)
 
 
-@pytest.mark.parametrize("kinds", ["plain", "bcast_reduce", "matmul", "network", "streams"])
-@pytest.mark.parametrize("n_dev", [1, 3, 8])
-def test_eight_lanes_and_one_lane_per_candidate(torch_gpu, n_dev, kinds):
-    """Small calls take eight lanes per candidate (compared with the oracle
-    above), larger ones one: the same programs repeated past either bound
-    (20,480 candidates, 45,056 where the device model has a MatMul regression,
-    nodes or streams) give the same results, ragged lengths (0 ops, and counts
-    above max_ops), invalid ops, underflows and resident bytes of 2^62 and
-    more included."""
+@pytest.mark.parametrize("kinds", ["plain", "bcast_reduce", "matmul", "network", "streams", "overflow"])
+@pytest.mark.parametrize("n_dev", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_eight_lanes_and_one_lane_per_candidate(torch_gpu, orc, n_dev, kinds):
+    """Small calls take eight lanes per candidate, larger ones one (more than
+    20,480 candidates, 45,056 where the device model has a MatMul regression,
+    nodes or streams), whose fast path takes the ops all lanes of a wavefront
+    have and whose general path the others, from the start where the fast one
+    met an op it cannot vouch for: the same programs repeated past either bound
+    give the same results, ragged lengths (0 ops, and counts above max_ops),
+    invalid ops, underflows, costs and clocks of +inf and resident bytes of
+    2^62 and more (a fifth of the devices, one candidate near 2^64) included.
+    The small call is compared with the oracle on every fifth program."""
     from paper_2111_05426_amd import dsim
     from paper_2111_05426_amd.workloads import DeviceSpec
     torch = torch_gpu
     rng = np.random.default_rng(4000 + n_dev)
     n, max_ops = 263, 75
-    t = random_tables(rng, n, max_ops, n_dev, True, kinds != "plain" and kinds != "matmul", kinds == "matmul")
+    t = random_tables(rng, n, max_ops, n_dev, kinds != "overflow", kinds in ("bcast_reduce", "network", "streams"),
+                      kinds == "matmul")
+    over = rng.random(n) < 0.2
+    t["n_ops"] = np.where(over, max_ops + rng.integers(1, 1000, n), t["n_ops"]).astype(np.uint32)
     t["n_ops"][5:9] = [max_ops + 1, 2 ** 31, 3, max_ops]
+    if kinds != "plain":   # (plain: the fast path's lanes as they mostly are)
+        big = rng.random((n, n_dev)) < 0.2
+        t["init"] = np.where(big, (np.uint64(1) << np.uint64(62)) + rng.integers(0, 1 << 40, (n, n_dev)).astype(np.uint64),
+                             t["init"]).astype(np.uint64)
+        t["init"][0] = np.uint64((1 << 64) - (1 << 20))
     t["init"][11, 0] = 2 ** 62 + 12345
     dev = DeviceSpec(mem_cap_bytes=2 * 10 ** 5,
                      matmul=(4.5e-6, 9.1e-15, 1.3e-12, 3.7e-14, 4.0e-5) if kinds == "matmul" else None,
                      network=(2, 3.3e9, 2.1e-5) if kinds == "network" else None,
                      streams=(2, 4.4e11, 1.3e-6) if kinds == "streams" else None)
+    if kinds == "overflow":
+        dev = replace(dev, flops_per_s=1e-290, link_bytes_per_s=1e-300, launch_s=0.0)
 
     def run(total):
         at = np.arange(total) % n
@@ -452,11 +468,23 @@ def test_eight_lanes_and_one_lane_per_candidate(torch_gpu, n_dev, kinds):
         return results_np(r), at
 
     small, _ = run(n)
-    assert np.any(small["status"] != 0) and np.any(small["status"] == 0)
+    if kinds != "overflow":
+        assert np.any(small["status"] != 0) and np.any(small["status"] & 8)
+    else:
+        assert n_dev == 1 or np.isinf(small["makespan"]).sum() > n // 4
+    assert not np.isnan(small["finish"]).any()
+    for c in range(0, n, 5):
+        m = min(int(t["n_ops"][c]), max_ops)
+        o = orc.sim_table({k: t[k][:m, c] for k in ("code", "flops", "bytes", "alloc", "free", "mm_k") if k in t}, n_dev, dev,
+                          init_live=t["init"][c])
+        assert small["status"][c] == (o["status"] | (dsim.ST_BAD_OP if t["n_ops"][c] > max_ops else 0)), c
+        assert_times(small["finish"][c, :n_dev], o["finish"])
+        assert np.array_equal(small["peak"][c, :n_dev].view(np.uint64), np.asarray(o["peak"], np.uint64)), c
     for total in (20480, 20481, 45057):
-        big, at = run(total)
+        large, at = run(total)
         for k in small:
-            assert np.array_equal(big[k], small[k][at]), (total, k)
+            assert np.array_equal(large[k].view(np.int64) if large[k].dtype == np.float64 else large[k],
+                                  (small[k].view(np.int64) if small[k].dtype == np.float64 else small[k])[at]), (total, k)
 
 
 @pytest.mark.parametrize("n", [2, 64, 512, 513, 640, 641, 1023, 1024, 1025, 65_536, 131_072, 131_073, 300_001])
