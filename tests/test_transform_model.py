@@ -1,86 +1,16 @@
-"""CPU models of two shortcuts of the transform kernel (csrc/parametric.hip),
-each against the plain evaluation it stands for, bit for bit:
+"""A CPU model of two shortcuts of the transform kernel (csrc/parametric.h)
+against the plain evaluation they stand for, bit for bit: whole periods of a
+schedule taken at once (`repeats` and the shift of all clocks), and blocks as
+one addition of whole ulps -- against a slot-by-slot walk that adds every cost.
+(tests/test_send_scan_model.py: a slot's Sends as scans.)
 
-* a slot's Sends as scans over the whole wavefront (`send_scan`): one prefix
-  sum of whole ulps whatever the segments, a segmented maximum, one binade
-  per candidate -- against the step walk of tests/test_send_scan_model.py;
-* whole periods of a schedule taken at once (`repeats` and the shift of all
-  clocks), and blocks as one addition of whole ulps -- against a slot-by-slot
-  walk that adds every cost.
-
-Neither calls the library or the oracle; the GPU parity tests check the
+It calls neither the library nor the oracle; the GPU parity tests check the
 kernel itself."""
 import math
 import random
 import struct
 
 import pytest
-
-from test_send_scan_model import _flags, _positions, _random_slot, _shl, _shr, steps
-
-
-def scan(W, P, live, sdir, cost, clk):
-    """None where the kernel declines (then it walks the steps)."""
-    s, _, left, right = _flags(W, P, live, sdir)
-    cl, cr = _shr(clk, 0.0), _shl(clk, 0.0)
-    src = [d != 0 for d in sdir]
-    z = [max(clk[i], cl[i] if sdir[i] < 0 else cr[i]) if src[i] else clk[i] for i in range(64)]
-    carry = [sdir[i] < 0 or left[i] for i in range(64)]
-    involved = [src[i] or left[i] or right[i] for i in range(64)]
-    begins = [involved[i] and not carry[i] for i in range(64)]
-    if not any(begins):
-        return None
-    spos = _positions([not c for c in carry])
-
-    def exp(v):   # biased exponent field
-        return struct.unpack("<Q", struct.pack("<d", v))[0] >> 52
-
-    e = []
-    for i in range(64):
-        seg = range(i - i % W, i - i % W + W)
-        first = next((j for j in seg if begins[j]), i)
-        e.append(exp(z[first]))
-    for i in range(64):
-        if begins[i] and (exp(z[i]) != e[i] or e[i] < 1023 - 500 or e[i] >= 0x7ff):
-            return None
-    w, k = [0.0] * 64, [0.0] * 64
-    for i in range(64):
-        k[i] = math.ldexp(z[i], 1075 - e[i])
-        if src[i]:
-            t = math.ldexp(cost[i], 1075 - e[i])
-            w[i] = float(round(t))   # ties to even, like rint
-            if not abs(t - w[i]) < 0.5:
-                return None
-    q, run = [], 0.0
-    for i in range(64):
-        run += w[i]
-        q.append(run)
-    if not run < 2.0 ** 53:
-        return None
-    y = []
-    for i in range(64):
-        t = k[i] - (q[i] - w[i])
-        y.append(max(y[-1], t) if spos[i] > 0 else t)
-    v = [q[i] + y[i] for i in range(64)]
-    if any(involved[i] and not v[i] < 2.0 ** 53 for i in range(64)):
-        return None
-    vd = [math.ldexp(v[i], e[i] - 1075) for i in range(64)]
-    vr = _shl(vd, 0.0)
-    return [vr[i] if right[i] else (vd[i] if (src[i] or left[i]) else clk[i]) for i in range(64)]
-
-
-def test_scan_over_the_wavefront_equals_steps():
-    rng = random.Random(20261204)
-    taken = declined = 0
-    for trial in range(3000):
-        slot = _random_slot(rng)
-        got = scan(*slot)
-        if got is None:
-            declined += 1
-            continue
-        taken += 1
-        assert got == steps(*slot), trial
-    assert taken > 1500 and declined > 100
 
 
 def bits(v):
