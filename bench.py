@@ -158,17 +158,6 @@ PARAMETRIC = ("tiny_mlp", "large_mlp", "gpt2_small", "gpt2_small_train", "gpt3_1
               "gpt3_175b_mi355x_overlap")
 
 
-_SIDE = []
-
-
-def side_stream(torch):
-    """The second stream that dsim_simulate_parametric accepts (and leaves
-    unused), created once at the default priority."""
-    if not _SIDE:
-        _SIDE.append(torch.cuda.Stream())
-    return _SIDE[0]
-
-
 # Vector issue rate of the chip: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane
 # instructions per second (a wave64 vector instruction occupies a 16-lane
 # SIMD for 4 cycles).  The transform's kernel is bound by the slots' schedule,
@@ -177,7 +166,8 @@ def side_stream(torch):
 # vector instructions it executes (rocprofv3 SQ_INSTS_VALU, 64 lanes each)
 # per second of the live launch time.
 VALU_PEAK_T = 256 * 4 * 16 * 2.4e9 / 1e12
-PARAMETRIC_SRC = [os.path.join(ROOT, "paper_2111_05426_amd", "csrc", f) for f in ("parametric.hip", "model.h")]
+PARAMETRIC_SRC = [os.path.join(ROOT, "paper_2111_05426_amd", "csrc", f)
+                  for f in ("parametric.h", "parametric.hip", "parametric_narrow.hip", "model.h")]
 
 
 def stored_valu(workload):
@@ -212,14 +202,13 @@ def bench_parametric(torch, dsim, W, reps, warmup=1, cpu_budget_s=0.0):
     out_mk = torch.empty(k, dtype=torch.float64, device="cuda")
     found = torch.empty(1, dtype=torch.int32, device="cuda")
     pws = dsim.alloc_parametric_workspace(n)
-    side = side_stream(torch)
     dev = W.device
     ev = []
 
     def step(record):
         e0, e1, e2 = (torch.cuda.Event(enable_timing=True) for _ in range(3))
         e0.record()
-        dsim.dsim_simulate_parametric(W.model, cand, dev, res, workspace=pws, side_stream=side)
+        dsim.dsim_simulate_parametric(W.model, cand, dev, res, workspace=pws)
         e1.record()
         dsim.dsim_argmin(res["makespan"], res["cand_peak"], res["status"], dev.mem_cap_bytes, k, ws, out_idx,
                          out_mk, found)

@@ -29,7 +29,7 @@
 //     it owns and a copy of every other weight while an op reads it.  The
 //     lane tracks the live bytes that do not depend on ownership plus the
 //     largest owned resident, and each block kind's highest point is taken
-//     as the maximum over the replicas in closed form (see zero_block).
+//     as the maximum over the replicas in closed form (see zero_top).
 //
 // The layers of a stage repeat one op sequence (for the MLP with H > 1, one
 // column/row layer pair) that does not depend on the stage, so the lanes of a
@@ -48,9 +48,9 @@
 // Recording a candidate's programs and tables takes a wavefront some
 // thousand instructions however few stages there are, and more candidates in
 // a wavefront do not share them: 100,000 MLP strategies of one stage and up to
-// 64 microbatches took 583 us at 16 lanes each, 539 at 8, 839 at 4.  So in
+// 64 microbatches took 582 us at 16 lanes each, 539 at 8, 839 at 4.  So in
 // the narrow kernel every lane records its own block of each direction, again
-// whenever its kind changes, and sums it binade-wise by itself: 93 us.
+// whenever its kind changes, and sums it binade-wise by itself: 84 us.
 //
 // A counting-sort pre-pass groups the candidates by segment width into a
 // temporary permutation (stable, so the grid's own order keeps wavefronts
@@ -1334,8 +1334,8 @@ __device__ __forceinline__ int64_t update_top(const Ctx &x, int s, const ZStage 
 // GPT-3-shaped strategies 2.03 -> 1.06 ms, with ZeRO 3.10 -> 1.37, two-stream
 // 3.59 -> 1.31, 2,240 MLP ones 350 -> 149 us, 398 GPT-2-small-shaped training
 // ones 195 -> 105 us (selection and pre-pass included); vector instructions
-// per GPT-3-shaped call 929M (before either change) -> 531M, 79% of what the
-// SIMDs issue at the nominal clock.
+// per GPT-3-shaped call 929M (before either change) -> 531M, which keep the
+// SIMDs issuing 83% of the kernel's cycles.
 //
 // NARROW: the body of the narrow launch, for segments of 1 to 8 lanes; w: its
 // wavefront.

@@ -10,11 +10,11 @@ namespace {
 // programs, up to 256 registers: four to eight on a CU) and their recording.
 // Few blocks that take the wavefronts in turn, each class from its last one
 // on (a strategy grid lists microbatch counts ascending), so that a call
-// without any pays little for the launch.  Against 16 lanes a candidate, us:
-// 100,000 MLP strategies of one stage and up to 4, 64, 256 microbatches 389 /
-// 50, 583 / 93, 669 / 134, of up to four stages 389 / 99, 625 / 243, 781 / 352;
-// transformer ones 480 / 62, 687 / 138, 719 / 213 and 495 / 155, 750 / 437,
-// 832 / 702.
+// without any pays little for the launch.  A call against 16 lanes a
+// candidate, us: 100,000 MLP strategies of one stage and up to 4, 64, 256
+// microbatches 389 -> 42, 582 -> 84, 669 -> 126, of up to four stages 388 ->
+// 92, 625 -> 234, 777 -> 343; transformer ones 479 -> 55, 687 -> 130, 721 ->
+// 201 and 495 -> 148, 749 -> 421, 831 -> 686.
 template <bool TF, bool RC, bool ZR, bool OV>
 __global__ __launch_bounds__(kLanes) __attribute__((amdgpu_waves_per_eu(ZR ? 1 : 2))) void k_parametric_narrow(const ParArgs g)
 {

@@ -28,8 +28,8 @@
 // over the banks (a 64-lane b128 read still takes several LDS cycles).
 //
 // The kernel runs close to the rate at which HBM returns its op records
-// (a million 2,048-op programs 7.0 ms, 5.9 TB/s; about 84 vector instructions per op keep the vector units partly busy
-// beside that); it has a fast path for the ops every lane of a wavefront
+// (a million 2,048-op programs 7.0 ms, 5.9 TB/s; about 84 vector
+// instructions per op keep the vector units partly busy beside that); it has a fast path for the ops every lane of a wavefront
 // has, which assumes valid compute, send and all-reduce ops of cost class 0
 // (indices clamped, so even an invalid op stays in bounds) and only tests
 // whether each op is one.  A lane that meets an op it cannot vouch for (a
@@ -38,7 +38,7 @@
 // and every op when the device model has a MatMul regression, nodes or
 // streams take the general path below it: pipelined loads too, each op
 // decoded in full.  (One op at a time with its loads in turn, that path took
-// 1.1 us per op; now 0.65.  40,001 programs of 150 to 600 ops: 960 -> 317 us.)
+// 1.1 us per op; now 0.65.  40,001 programs of 150 to 600 ops: 960 -> 308 us.)
 //
 // A call of few candidates cannot fill the chip with a lane each, and one
 // lane's chain through an op (LDS counters, an eight-device maximum, the
