@@ -299,10 +299,10 @@ dsim_status dsim_argmin(const double *makespan, const uint64_t *cand_peak, const
     if (n < 0 || n > ((int64_t)1 << 40)) return fail(DSIM_EINVAL, "bad n");
     if (!out_idx || !out_makespan || !out_found) return fail(DSIM_EINVAL, "outputs must not be NULL");
     if (n > 0 && (!makespan || !cand_peak || !status)) return fail(DSIM_EINVAL, "inputs must not be NULL");
-    if (!workspace || ws_bytes < argmin_workspace(n, k))
+    if (!workspace || ws_bytes < argmin_workspace_least(n, k))
         return fail(DSIM_ENOSPC, "workspace needs %zu bytes", argmin_workspace(n, k));
-    return launch_argmin(makespan, cand_peak, status, n, mem_cap, k, workspace, out_idx, out_makespan, out_found,
-                         (hipStream_t)hip_stream);
+    return launch_argmin(makespan, cand_peak, status, n, mem_cap, k, workspace, ws_bytes, out_idx, out_makespan,
+                         out_found, (hipStream_t)hip_stream);
 }
 
 dsim_status dsim_materialize_tables(const dsim_model *model, const dsim_strategy *cand, int64_t n_cand,

@@ -63,9 +63,11 @@ dsim_status launch_gen_tables(uint64_t seed, int64_t n_cand, int32_t n_ops, int3
                               uint32_t *code, float *flops, float *bytes, uint32_t *alloc,
                               uint32_t *freeb, uint32_t *n_ops_out, hipStream_t s);
 size_t argmin_workspace(int64_t n, int32_t k);
+// the least workspace accepted: large calls then run with fewer blocks
+size_t argmin_workspace_least(int64_t n, int32_t k);
 dsim_status launch_argmin(const double *mk, const uint64_t *pk, const int32_t *st, int64_t n,
-                          uint64_t cap, int32_t k, void *ws, int64_t *out_idx, double *out_mk,
-                          int32_t *out_found, hipStream_t s);
+                          uint64_t cap, int32_t k, void *ws, size_t ws_bytes, int64_t *out_idx,
+                          double *out_mk, int32_t *out_found, hipStream_t s);
 size_t parametric_workspace(int64_t n_cand);
 // the fixed scratch of dsim_simulate_parametric_static on the current GPU
 // (its address taken once per GPU) and the candidates it holds

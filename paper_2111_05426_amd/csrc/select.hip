@@ -43,6 +43,7 @@ constexpr int kMaxK = 64;
 constexpr int64_t kChunk = 4096;
 constexpr int64_t kMinChunk = 256;
 constexpr int kMaxBlocks = 1024;
+constexpr int kLeastBlocks = 512;  // at most so many where the workspace holds no more lists
 constexpr int kRowK = 16;     // 16 lists stand as one in the merge up to this k: 16 k^2 <= kMaxK^2 keys
 constexpr int kRoundK = 8;    // chunks of one key a thread take rounds up to this k
 constexpr int kFillBlocks = 256;   // one chunk per CU at least, while chunks stay >= kMinChunk
@@ -403,10 +404,10 @@ __global__ __launch_bounds__(kMergeBlock) void k_select_merge(const Key *ws, int
     if (t == 0) *out_found = found;
 }
 
-int64_t n_chunks(int64_t n, int64_t *chunk)
+int64_t n_chunks(int64_t n, int64_t most, int64_t *chunk)
 {
     int64_t c = kChunk;
-    while ((n + c - 1) / c > kMaxBlocks) c *= 2;
+    while ((n + c - 1) / c > most) c *= 2;
     while (c > kMinChunk && (n + c - 1) / c < kFillBlocks) c /= 2;
     *chunk = c;
     const int64_t b = (n + c - 1) / c;
@@ -418,11 +419,17 @@ int64_t n_chunks(int64_t n, int64_t *chunk)
 size_t argmin_workspace(int64_t n, int32_t k)
 {
     int64_t chunk;
-    return (size_t)n_chunks(n, &chunk) * (size_t)k * sizeof(Key);
+    return (size_t)n_chunks(n, kMaxBlocks, &chunk) * (size_t)k * sizeof(Key);
+}
+
+size_t argmin_workspace_least(int64_t n, int32_t k)
+{
+    int64_t chunk;
+    return (size_t)n_chunks(n, kLeastBlocks, &chunk) * (size_t)k * sizeof(Key);
 }
 
 dsim_status launch_argmin(const double *mk, const uint64_t *pk, const int32_t *st, int64_t n,
-                          uint64_t cap, int32_t k, void *ws, int64_t *out_idx, double *out_mk,
+                          uint64_t cap, int32_t k, void *ws, size_t ws_bytes, int64_t *out_idx, double *out_mk,
                           int32_t *out_found, hipStream_t s)
 {
     if (n <= one_block(k)) {
@@ -432,7 +439,7 @@ dsim_status launch_argmin(const double *mk, const uint64_t *pk, const int32_t *s
         return e == hipSuccess ? DSIM_OK : hip_fail(e, "select launch");
     }
     int64_t chunk;
-    const int64_t blocks = n_chunks(n, &chunk);
+    const int64_t blocks = n_chunks(n, ws_bytes >= argmin_workspace(n, k) ? kMaxBlocks : kLeastBlocks, &chunk);
     Key *w = static_cast<Key *>(ws);
     if (chunk >= kChunk)
         hipLaunchKernelGGL(k_select_chunks<kWideBlock>, dim3((unsigned)blocks), dim3(kWideBlock), 0, s, mk, pk, st, n,

@@ -20,8 +20,9 @@ dsim_status launch_gen_tables(uint64_t, int64_t, int32_t, int32_t, uint32_t *, f
     return DSIM_OK;
 }
 size_t argmin_workspace(int64_t n, int32_t k) { return (size_t)(n + 1) * 16 + (size_t)k * 16; }
+size_t argmin_workspace_least(int64_t n, int32_t k) { return argmin_workspace(n, k); }
 dsim_status launch_argmin(const double *, const uint64_t *, const int32_t *, int64_t, uint64_t, int32_t, void *,
-                          int64_t *, double *, int32_t *, hipStream_t)
+                          size_t, int64_t *, double *, int32_t *, hipStream_t)
 {
     ++g_launches;
     return DSIM_OK;

@@ -525,3 +525,34 @@ def test_argmin_bounds_of_the_merge(torch_gpu, k, n, order):
     512 threads (chunks of 4,096 keys and more, from 1,044,481 keys on), more
     than 512 lists, chunks of 8,192."""
     test_argmin_orders_and_block_edges(torch_gpu, n, k, order)
+
+
+@pytest.mark.parametrize("n,k", [(2_097_153, 1), (2_097_153, 64), (2_500_000, 16), (4_194_305, 9), (9_000_001, 33)])
+def test_argmin_with_half_the_workspace(torch_gpu, n, k):
+    """More than two million keys: a workspace of 512 lists of k is enough
+    (fewer blocks then run), a byte less is refused."""
+    from paper_2111_05426_amd import dsim
+    torch = torch_gpu
+    chunk = 4096
+    while -(-n // chunk) > 512:
+        chunk *= 2
+    need = -(-n // chunk) * k * 16
+    assert need < dsim.dsim_argmin_workspace(n, k)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    mk = torch.randint(0, n // 3, (n,), generator=g, device="cuda").to(torch.float64)   # some ties
+    pk, st = torch.zeros(n, dtype=torch.int64, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+    got = []
+    for size in (need, dsim.dsim_argmin_workspace(n, k)):
+        ws = torch.full((size + 256,), 0x5A, dtype=torch.uint8, device="cuda")
+        idx, out = torch.empty(k, dtype=torch.int64, device="cuda"), torch.empty(k, dtype=torch.float64, device="cuda")
+        found = torch.empty(1, dtype=torch.int32, device="cuda")
+        dsim.dsim_argmin(mk, pk, st, 0, k, ws[:size], idx, out, found)
+        torch.cuda.synchronize()
+        assert int(found.item()) == k and bool((ws[size:] == 0x5A).all())
+        got.append((idx.cpu().numpy(), out.cpu().numpy()))
+    order = np.lexsort((np.arange(n), mk.cpu().numpy()))[:k]
+    for idx, out in got:
+        assert np.array_equal(idx, order) and np.array_equal(out, mk.cpu().numpy()[order])
+    idx, out = torch.empty(k, dtype=torch.int64, device="cuda"), torch.empty(k, dtype=torch.float64, device="cuda")
+    with pytest.raises(dsim.DsimError, match="workspace"):
+        dsim.dsim_argmin(mk, pk, st, 0, k, ws[:need - 1], idx, out, found)
